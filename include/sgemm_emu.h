@@ -364,10 +364,11 @@ int givens_emu_batched(int n, int i, int j,
  * U's 32 x 32 block, and the segments and blocks are chained by FP32 running
  * totals.  X: rows x len, row stride ldx >= max(1, len); Y likewise with
  * ldy.  Y may be X itself (ldy == ldx) for an in-place scan; any other
- * overlap is an error.  Rows are independent; a wavefront scans 8 rows, so
- * parallelism comes from the number of rows.  Rows of a multiple of 1024
- * values with 16-byte aligned X and Y rows take 16-byte accesses.  Any
- * number of rows: more than 268,435,424 take several launches.
+ * overlap is an error.  Rows are independent; a wavefront scans 1 to 4 whole
+ * rows, except that fewer than 512 rows of more than 15 blocks are cut into
+ * parts scanned by a wavefront each (three launches on the stream, Y holding
+ * the parts' totals in between).  Any alignment, at the same speed.  Any
+ * number of rows: more than 33,554,428 wavefronts take several launches.
  * Errors: SGEMM_EMU_ERR_DIM, _LD (also when rows x ld runs past the end of
  * the address space), _NULL, _ALIAS, _HIP.
  */

@@ -2,9 +2,9 @@
 // x^T U with the upper-triangular all-ones U (Sec. 4.1, eq. scan-mat, rule
 // u-rule), in emulated FP32 (Sec. 4.4).
 //
-// A wavefront scans whole rows, 1024 values (a block) at a time.  The block
-// is read as a 32 x 32 matrix Z of 32 consecutive segments (Z[n][k] is value
-// 32 n + k of the block) and scanned in two levels:
+// A wavefront scans a run of consecutive values, 1024 (a block) at a time.
+// The block is read as a 32 x 32 matrix Z of 32 consecutive segments
+// (Z[n][k] is value 32 n + k of the block) and scanned in two levels:
 //   * within segments, as the transposed product S^T = U^T Z^T: U^T's
 //     32 x 32 block is the A operand, built once per wave with foreach_ij
 //     from the rule (element (i, k) of U^T is [k <= i]) and never stored; Z
@@ -14,12 +14,28 @@
 //   * across segments, an exclusive scan of the 32 segment totals over the
 //     lanes (five shuffle steps), plus the running total of the row's
 //     earlier blocks, added to every value of the segment.
-// Lane (n, g) = (l % 32, l / 32) holds values 32 n + 16 s + 8 g .. + 7 of the
-// block as its operand and, as its accumulator, outputs 32 n + 8 q + 4 g ..
-// + 3 for q = 0..3: every load and store is 16 bytes, and one wave's
-// instructions together cover a contiguous 4 KiB.  Over whole blocks of
-// 16-byte aligned rows the loads of the next kBuf blocks are in flight while
-// the current one is multiplied.
+//
+// Every block, whole or not, aligned or not, moves between memory and
+// registers in four 1 KiB instructions of 16 bytes per lane, on a buffer
+// descriptor that ends where the row does: a dword past the end reads as
+// zero and is not written, and the accesses need 4-byte alignment only, so
+// one path serves every length, row stride and base.  (The bytes are
+// regrouped into the operand layout, and back, through LDS.)  The blocks of
+// a wave's whole rows form one sequence with the loads of the next kBuf
+// blocks in flight while the current one is multiplied.
+//
+// Rows (scan_kernel, one wave per 1 to 4 whole rows) fill the device when
+// there are many of them.  A few long rows are cut into parts instead, one
+// wave each, in three launches on the stream that need no memory but Y:
+//   scan_total_kernel  each part's plain FP32 sum, left in the part's last
+//                      output;
+//   scan_chain_kernel  those sums scanned along each row, which makes them
+//                      the final outputs at those places;
+//   scan_part_kernel   every other output: the part scanned as above from
+//                      the output just before it.  The part's own last value
+//                      is neither read nor written, so Y may be X.
+// A part is read twice and written once; with 128 MB in the last-level
+// cache the second read does not go to HBM.
 #include "internal.h"
 #include "mfmae/frag.hpp"
 #include "mfmae/tcec.hpp"
@@ -34,12 +50,16 @@ using mfmae::Shape32;
 using mfmae::Use;
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 using FragA = mfmae::fragment<Shape32, Use::A, _Float16>;
 
 constexpr int kWaves = 4;
-
-constexpr int kBuf = 4;         // block buffers per wave
-constexpr int kRowsPerWave = 8;  // rows a wave scans, one after another
+constexpr int kBlock = 1024;  // values scanned at a time
+// Block buffers per wave.  Two of them and four waves per SIMD (101 VGPRs)
+// against four and three (137): 131,072 rows of 2048 take 361 against 397 us
+// (5.9 TB/s), of 512 values 77 against 83, of 200 60 against 68.  With one
+// buffer rows of 2048 gain 10 us more, but 65,536 of 4096 lose 22.
+constexpr int kBuf = 2;
 
 // The 16 values lane (n, g) holds of a block as B operand: block values
 // 32 n + 16 s + 8 g + v, s = 0, 1, v = 0..7.
@@ -47,18 +67,27 @@ struct Block {
     float x[2][8];
 };
 
-// A block as loaded on the whole-block path: lane l holds values
-// 256 i + 4 l .. + 3, i = 0..3, so every load instruction reads 1 KiB of
-// whole cache lines.
+// A block as loaded: lane l holds values 256 i + 4 l .. + 3, i = 0..3, so
+// every load instruction reads 1 KiB of consecutive values.
 struct Raw {
     f32x4 v[4];
 };
 
-// Whole block inside a 16-byte aligned row: four contiguous 16-byte loads.
-__device__ inline void load_fast(Raw& b, const float* row, int c0) {
-    const int l = threadIdx.x & 63;
+// Descriptor of the first `count` floats at p (at most one block): loads past
+// them return zero and stores past them are dropped, dword by dword (raw
+// buffer, no stride; the fourth word as for every gfx9 raw buffer).
+__device__ inline __amdgpu_buffer_rsrc_t block_rsrc(const float* p, int count) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(p), 0,
+                                             4 * max(0, min(count, kBlock)), 0x00020000);
+}
+
+__device__ inline void load_block(Raw& b, const float* p, int count) {
+    const __amdgpu_buffer_rsrc_t r = block_rsrc(p, count);
+    const int off = 16 * (threadIdx.x & 63);
 #pragma unroll
-    for (int i = 0; i < 4; ++i) b.v[i] = *reinterpret_cast<const f32x4*>(row + c0 + 256 * i + 4 * l);
+    for (int i = 0; i < 4; ++i)
+        b.v[i] = __builtin_bit_cast(f32x4,
+                                    __builtin_amdgcn_raw_buffer_load_b128(r, off + 1024 * i, 0, 0));
 }
 
 // The wave's LDS copy of one block: segment n (32 values) at 36 n floats.
@@ -87,19 +116,6 @@ __device__ inline void to_operand(const Raw& r, float* buf, Block& b) {
             b.x[s][v + 4] = v1[v];
         }
     }
-}
-
-// Any block: element loads, zero past the row's end.
-__device__ inline void load_bounded(Block& b, const float* row, int c0, int len) {
-    const int l = threadIdx.x & 63;
-    const int base = c0 + 32 * (l & 31) + 8 * (l >> 5);
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-#pragma unroll
-        for (int v = 0; v < 8; ++v) {
-            const int cc = base + 16 * s + v;
-            b.x[s][v] = cc < len ? row[cc] : 0.0f;
-        }
 }
 
 // y = carry + scan of the block; carry becomes the row's running total
@@ -146,7 +162,8 @@ __device__ inline void scan_block(const Block& b, const half8_t (&Ut)[2], float&
 // is not read again (measured 2.7% faster; the rule-built kernels, whose
 // output stores interleave with the next item's loads, ran 2-3% slower
 // with them).
-__device__ inline void store_fast(float* row, int c0, const float (&y)[16], float* buf) {
+__device__ inline void store_block(float* p, int count, const float (&y)[16], float* buf) {
+    constexpr int kNontemporal = 2;
     const int l = threadIdx.x & 63;
     float* q = buf + kSegPitch * (l & 31) + 4 * (l >> 5);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");  // operand reads done
@@ -155,29 +172,22 @@ __device__ inline void store_fast(float* row, int c0, const float (&y)[16], floa
         *reinterpret_cast<f32x4*>(q + 8 * g) = f32x4{y[4 * g], y[4 * g + 1], y[4 * g + 2],
                                                      y[4 * g + 3]};
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+    const __amdgpu_buffer_rsrc_t r = block_rsrc(p, count);
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-        __builtin_nontemporal_store(*reinterpret_cast<const f32x4*>(buf + staged(256 * i + 4 * l)),
-                                    reinterpret_cast<f32x4*>(row + c0 + 256 * i + 4 * l));
+        __builtin_amdgcn_raw_buffer_store_b128(
+            __builtin_bit_cast(u32x4, *reinterpret_cast<const f32x4*>(buf + staged(256 * i + 4 * l))),
+            r, 16 * l + 1024 * i, 0, kNontemporal);
 }
 
-__device__ inline void store_bounded(float* row, int c0, int len, const float (&y)[16]) {
-    const int l = threadIdx.x & 63;
-    const int base = c0 + 32 * (l & 31) + 4 * (l >> 5);
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
-        const int col = base + 8 * (e >> 2) + (e & 3);
-        if (col < len) row[col] = y[e];
-    }
-}
-
-__global__ __launch_bounds__(64 * kWaves, 2) void scan_kernel(ScanArgs p) {
-    __shared__ __attribute__((aligned(16))) float stage[kWaves][kStageFloats];
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int64_t r_first = ((int64_t)blockIdx.x * kWaves + wave) * kRowsPerWave;
-    if (r_first >= p.rows) return;  // whole wave; no barrier below
-    const int nrows = (int)min((int64_t)kRowsPerWave, p.rows - r_first);
-
+// Scan `nrows` runs of `len` values each, run r at x + r ldx, into y + r ldy,
+// every run starting from `carry0`: one sequence of blocks, kBuf of them in
+// flight.  Loads are unconditional (past the end they re-read the last
+// block) and the first round of steps is peeled, so the loop is entered with
+// the same memory operations pending as on every later iteration and the
+// wait before each block covers that block's loads only.
+__device__ __forceinline__ void scan_rows(const float* x, int64_t ldx, float* y, int64_t ldy, int nrows,
+                                 int len, float carry0, float* sb) {
     // U^T's diagonal block for k step s: element (i, kk) is [16 s + kk <= i];
     // hi only (lo is 0 for 0 and 1).
     half8_t Ut[2];
@@ -187,93 +197,198 @@ __global__ __launch_bounds__(64 * kWaves, 2) void scan_kernel(ScanArgs p) {
             Ut[s][e] = (16 * s + kk <= i) ? (_Float16)1.0f : (_Float16)0.0f;
         });
 
-    float carry = 0.0f;
-    float y[16];
+    const int nb = (len - 1) / kBlock + 1;  // blocks per run
+    const int64_t nf = (int64_t)nrows * nb;
+    int64_t lf = 0;  // load cursor: block lf of the sequence, block lblk of its run
+    int lblk = 0;
+    auto load_next = [&](Raw& b) __attribute__((always_inline)) {
+        load_block(b, x + (int64_t)lblk * kBlock, len - lblk * kBlock);
+        if (lf + 1 < nf) {
+            ++lf;
+            if (++lblk == nb) {
+                lblk = 0;
+                x += ldx;
+            }
+        }
+    };
+    float carry = carry0;
+    int blk = 0;  // block of the run that is scanned next
+    auto scan_next = [&](const Raw& r) __attribute__((always_inline)) {
+        Block b;
+        float out[16];
+        to_operand(r, sb, b);
+        scan_block(b, Ut, carry, out);
+        store_block(y + (int64_t)blk * kBlock, len - blk * kBlock, out, sb);
+        if (++blk == nb) {
+            blk = 0;
+            y += ldy;
+            carry = carry0;
+        }
+    };
+    // the scheduling barrier keeps each step's reload in place, so the
+    // blocks really are loaded kBuf steps ahead
+    auto step = [&](Raw& r) __attribute__((always_inline)) {
+        scan_next(r);
+        load_next(r);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    Raw buf[kBuf];
+#pragma unroll
+    for (int i = 0; i < kBuf; ++i) load_next(buf[i]);
+    int64_t f = 0;
+    if (nf >= kBuf) {
+#pragma unroll
+        for (int i = 0; i < kBuf; ++i) step(buf[i]);
+        for (f = kBuf; f + kBuf <= nf; f += kBuf) {
+#pragma unroll
+            for (int i = 0; i < kBuf; ++i) step(buf[i]);
+        }
+    }
+    // buf[i] holds block f + i for the remaining blocks
+#pragma unroll
+    for (int i = 0; i < kBuf - 1; ++i)
+        if (f + i < nf) scan_next(buf[i]);
+}
 
-    if (p.vec && p.len % 1024 == 0) {
-        // Whole blocks of aligned rows, as one sequence f = (row, block) of
-        // nf blocks: kBuf block buffers in turn.  A step scans one buffer's
-        // block, stores it and reloads the buffer with block f + kBuf.  Loads
-        // are unconditional (past the end they re-read the last block) and
-        // the first round of steps is peeled, so the loop is entered with the
-        // same memory operations pending as on every later iteration and the
-        // wait before each block covers that block's loads only.
-        const int nb = p.len / 1024;
-        const int nf = nrows * nb;
-        const int last = nf - 1;
-        auto row_in = [&](int f) { return p.X + (r_first + f / nb) * p.ldx; };
-        auto row_out = [&](int f) { return p.Y + (r_first + f / nb) * p.ldy; };
-        float* sb = stage[wave];
-        auto load = [&](Raw& b, int f) {
-            const int fc = min(f, last);
-            load_fast(b, row_in(fc), 1024 * (fc % nb));
-        };
-        // the scheduling barrier keeps each step's reload in place, so the
-        // blocks really are loaded kBuf steps ahead
-        auto step = [&](Raw& r, int f) {
-            if (f % nb == 0) carry = 0.0f;
-            Block b;
-            to_operand(r, sb, b);
-            scan_block(b, Ut, carry, y);
-            store_fast(row_out(f), 1024 * (f % nb), y, sb);
-            load(r, f + kBuf);
-            __builtin_amdgcn_sched_barrier(0);
-        };
-        Raw buf[kBuf];
+__global__ __launch_bounds__(64 * kWaves, 4) void scan_kernel(ScanArgs p, int rows_per_wave) {
+    __shared__ __attribute__((aligned(16))) float stage[kWaves][kStageFloats];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t r0 = ((int64_t)blockIdx.x * kWaves + wave) * rows_per_wave;
+    if (r0 >= p.rows) return;  // whole wave; no barrier below
+    scan_rows(p.X + r0 * p.ldx, p.ldx, p.Y + r0 * p.ldy, p.ldy,
+              (int)min((int64_t)rows_per_wave, p.rows - r0), p.len, 0.0f, stage[wave]);
+}
+
+// Part `part` of a row cut into parts of `blocks` blocks: its first value and
+// its number of values (the last part of a row may be shorter).
+struct Part {
+    int64_t row;
+    int part, first, count;
+};
+
+__device__ inline Part part_of(const ScanArgs& p, int blocks, int nparts, int64_t task) {
+    Part q;
+    q.row = task / nparts;
+    q.part = (int)(task - q.row * nparts);
+    q.first = q.part * blocks * kBlock;  // < len: fits
+    q.count = min(blocks * kBlock, p.len - q.first);
+    return q;
+}
+
+__global__ __launch_bounds__(64 * kWaves) void scan_total_kernel(ScanArgs p, int blocks,
+                                                                 int nparts) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t task = (int64_t)blockIdx.x * kWaves + wave;
+    if (task >= p.rows * nparts) return;
+    const Part q = part_of(p, blocks, nparts, task);
+    const float* x = p.X + q.row * p.ldx + q.first;
+    constexpr int kAhead = 4;  // blocks in flight; past the end they read as zero
+    f32x4 sum[4] = {};
+    for (int c = 0; c < q.count; c += kAhead * kBlock) {
+        Raw r[kAhead];
 #pragma unroll
-        for (int i = 0; i < kBuf; ++i) load(buf[i], i);
-        int f = 0;
-        if (nf >= kBuf) {
+        for (int b = 0; b < kAhead; ++b) load_block(r[b], x + c + b * kBlock, q.count - c - b * kBlock);
 #pragma unroll
-            for (int i = 0; i < kBuf; ++i) step(buf[i], i);
-            for (f = kBuf; f + kBuf <= nf; f += kBuf) {
+        for (int b = 0; b < kAhead; ++b)
 #pragma unroll
-                for (int i = 0; i < kBuf; ++i) step(buf[i], f + i);
-            }
-        }
-        // buf[i] holds block f + i for the remaining blocks
-#pragma unroll
-        for (int i = 0; i < kBuf - 1; ++i) {
-            if (f + i < nf) {
-                if ((f + i) % nb == 0) carry = 0.0f;
-                Block b;
-                to_operand(buf[i], sb, b);
-                scan_block(b, Ut, carry, y);
-                store_fast(row_out(f + i), 1024 * ((f + i) % nb), y, sb);
-            }
-        }
-        return;
+            for (int i = 0; i < 4; ++i) sum[i] += r[b].v[i];
     }
-    // any length or alignment: element loads and stores, one block at a time
-    for (int r = 0; r < nrows; ++r) {
-        const float* xin = p.X + (r_first + r) * p.ldx;
-        float* yout = p.Y + (r_first + r) * p.ldy;
-        carry = 0.0f;
-        for (int c0 = 0; c0 < p.len; c0 += 1024) {
-            Block b;
-            load_bounded(b, xin, c0, p.len);
-            scan_block(b, Ut, carry, y);
-            store_bounded(yout, c0, p.len, y);
+    const f32x4 s = (sum[0] + sum[1]) + (sum[2] + sum[3]);
+    float total = (s[0] + s[1]) + (s[2] + s[3]);
+#pragma unroll
+    for (int d = 32; d > 0; d /= 2) total += __shfl_xor(total, d, 64);
+    if ((threadIdx.x & 63) == 0) p.Y[q.row * p.ldy + q.first + q.count - 1] = total;
+}
+
+// One wave per row: the sums of its parts, 64 at a time.
+__global__ __launch_bounds__(64) void scan_chain_kernel(ScanArgs p, int blocks, int nparts) {
+    const int l = threadIdx.x;
+    float* y = p.Y + (int64_t)blockIdx.x * p.ldy;
+    float carry = 0.0f;
+    for (int s0 = 0; s0 < nparts; s0 += 64) {
+        const bool in = s0 + l < nparts;
+        const int64_t end = (int64_t)(s0 + l + 1) * blocks * kBlock;
+        float* at = y + min(end, (int64_t)p.len) - 1;
+        float t = in ? *at : 0.0f;
+#pragma unroll
+        for (int d = 1; d < 64; d *= 2) {
+            const float u = __shfl_up(t, d, 64);
+            if (l >= d) t += u;
         }
+        t += carry;
+        if (in) *at = t;
+        carry = __shfl(t, 63, 64);
     }
+}
+
+__global__ __launch_bounds__(64 * kWaves, 4) void scan_part_kernel(ScanArgs p, int blocks,
+                                                                   int nparts) {
+    __shared__ __attribute__((aligned(16))) float stage[kWaves][kStageFloats];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int64_t task = (int64_t)blockIdx.x * kWaves + wave;
+    if (task >= p.rows * nparts) return;
+    const Part q = part_of(p, blocks, nparts, task);
+    if (q.count == 1) return;  // its one output is final
+    float* y = p.Y + q.row * p.ldy + q.first;
+    const float before = q.part == 0 ? 0.0f : y[-1];
+    scan_rows(p.X + q.row * p.ldx + q.first, 0, y, 0, 1, q.count - 1, before, stage[wave]);
 }
 
 }  // namespace
 
+// Rows a wave takes.  Short rows share the wave's set-up, and two rows of two
+// blocks fill its buffers; longer rows are better spread over more waves
+// (131,072 rows, 1 / 2 / 4 rows per wave: 100 values 72 / 70 / 59 us, 512
+// 82 / 80 / 77, 1000 175 / 187 / 192, 1500 278 / 290 / 310, 2048
+// 375 / 361 / 367; 65,536 rows of 4096: 362 / 366 / 407).
+static int64_t rows_per_wave(int64_t rows, int len) {
+    const int64_t best = len <= 512 ? 4 : len > 1536 && len <= 2048 ? 2 : 1;
+    const int64_t fill = rows / 8192;  // and at least that many waves
+    return fill < 1 ? 1 : fill < best ? fill : best;
+}
+
 hipError_t launch_scan(const ScanArgs& a, hipStream_t stream) {
+    const int64_t nb = (a.len - 1) / kBlock + 1;
+    // A wave takes about 1 us per block of its row whatever the others do, so
+    // nb us for whole rows until they fill the device; in parts a scan takes
+    // 16 us (three launches) or 1.5 times the whole rows' memory time, if
+    // that is longer.  Measured, whole / parts: 16 blocks 19.6 / 17.4 us for
+    // 128 and for 512 rows; 64 blocks 68 / 17 us for 128 rows, 68 / 65 for
+    // 512, 84 / 127 for 1024; 8 blocks 11 / 16 us.
+    if (a.rows < 512 && nb >= 16) {
+        // about 4096 parts in all (16 waves per CU), of at least 4 blocks
+        const int64_t per_row = (4096 + a.rows - 1) / a.rows;
+        int64_t blocks = (nb + per_row - 1) / per_row;
+        if (blocks < 4) blocks = 4;
+        const int nparts = (int)((nb + blocks - 1) / blocks);
+        const dim3 grid((unsigned)((a.rows * nparts + kWaves - 1) / kWaves));
+        hipLaunchKernelGGL(scan_total_kernel, grid, dim3(64 * kWaves), 0, stream, a, (int)blocks,
+                           nparts);
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(scan_chain_kernel, dim3((unsigned)a.rows), dim3(64), 0, stream, a,
+                           (int)blocks, nparts);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(scan_part_kernel, grid, dim3(64 * kWaves), 0, stream, a, (int)blocks,
+                           nparts);
+        return hipGetLastError();
+    }
     // one launch stays below 2^31 work-items (the dispatch packet counts
     // work-items in 32 bits); more rows take several launches, each on its
     // own range of rows
+    const int64_t rpw = rows_per_wave(a.rows, a.len);
     const int64_t max_blocks = (int64_t(1) << 31) / (64 * kWaves) - 1;
-    const int64_t rows_per_launch = max_blocks * kWaves * kRowsPerWave;
+    const int64_t rows_per_launch = max_blocks * kWaves * rpw;
     for (int64_t r0 = 0; r0 < a.rows; r0 += rows_per_launch) {
         ScanArgs c = a;
         c.rows = a.rows - r0 < rows_per_launch ? a.rows - r0 : rows_per_launch;
         c.X = a.X + r0 * a.ldx;
         c.Y = a.Y + r0 * a.ldy;
-        const int64_t waves = (c.rows + kRowsPerWave - 1) / kRowsPerWave;
+        const int64_t waves = (c.rows + rpw - 1) / rpw;
         const int64_t blocks = (waves + kWaves - 1) / kWaves;
-        hipLaunchKernelGGL(scan_kernel, dim3((unsigned)blocks), dim3(64 * kWaves), 0, stream, c);
+        hipLaunchKernelGGL(scan_kernel, dim3((unsigned)blocks), dim3(64 * kWaves), 0, stream, c,
+                           (int)rpw);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

@@ -48,6 +48,28 @@ def test_parity_shapes(rows, length):
     gate(Y, ref, _k_eff(length), f"scan {rows}x{length}", max_gate=False)
 
 
+# Few long rows are scanned in parts (three launches): the smallest such row
+# and the one below it, a last part of one value, of one block and of whole
+# blocks, the most rows taken and one more, parts of more than 4 blocks, odd
+# lengths (rows off 16-byte alignment).
+PART_SHAPES = [(1, 15 * 1024), (1, 15 * 1024 + 1), (3, 16 * 1024 + 1), (2, 17 * 1024),
+               (5, 20 * 1024), (511, 15 * 1024 + 5), (512, 15 * 1024 + 5), (2, 100001),
+               (300, 65 * 1024 + 3)]
+
+
+@pytest.mark.parametrize("in_place", [False, True])
+@pytest.mark.parametrize("shape", PART_SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_rows_in_parts(shape, in_place):
+    rows, length = shape
+    print(f"case scan in parts rows={rows} len={length} in_place={in_place}", flush=True)
+    X = synth.uniform((rows, length), synth.rng(rows + length))
+    Xd = X.to(device())
+    Y = Xd if in_place else torch.full((rows, length), float("nan"), device=device())
+    pkg.sgemm_emu_scan(Xd, Y)
+    ref = oracle.scan(X.numpy())
+    gate(to_np(Y), ref, _k_eff(length), f"scan {rows}x{length}", max_gate=False)
+
+
 @pytest.mark.parametrize("length", [3000, 4096])
 def test_integer_exact_and_in_place(length):
     X = synth.integer_matrix((70, length), synth.rng(5), -1000, 1000)
