@@ -98,16 +98,20 @@ int sgemm_emu_batched(int m, int n, int k,
  *                         REG flow's conditions met, the first of 128x256
  *                         (when it is preferred as above) and 256x128 whose
  *                         whole tiles cover at least 95% of C and number at
- *                         least 256 (batch included):
- *                         that interior (and k rounded down to a multiple
- *                         of 32) runs on the full-tile kernel, the
- *                         remaining k is added to it in place, and the edge
- *                         strips run on the REG flow with 64 x 64 tiles, one
- *                         launch after another on the stream.  Otherwise
- *                         REG whenever its conditions hold: tile 64x64 for
+ *                         least 256 (batch included): SPLIT with that tile.
+ *                         Otherwise REG whenever its conditions hold: tile 64x64 for
  *                         m, n <= 64, else 128x128, else (B rows without
  *                         vector loads, below 2^35 multiply-adds) 64x64.
  *                         Otherwise SPLIT on the general kernel.
+ *                         With tile AUTO too and error correction on, the
+ *                         product then runs on the tile form of the kernel
+ *                         so found wherever that is the faster one: the
+ *                         split flow on workgroup tiles of 64x64 to 128x256
+ *                         chosen by the product's size, whose last tiles
+ *                         overlap their neighbours instead of running past
+ *                         the matrix, k shared among groups of waves where
+ *                         the tiles are few, any alignment.  A named flow or
+ *                         tile runs exactly as named.
  *   SGEMM_EMU_FLOW_SPLIT  FP32 tiles are split in registers between the
  *                         global load and the LDS store; LDS holds hi and lo
  *                         (the same 4 bytes per element as FP32) and the
@@ -177,7 +181,11 @@ int sgemm_emu_batched_ex(int m, int n, int k,
  * string; "" for an empty problem).  A host-only query: no HIP call,
  * nothing is enqueued.  Same validation and errors as sgemm_emu_batched_ex,
  * plus SGEMM_EMU_ERR_NULL for a NULL out; for an empty problem (nothing
- * would run) out receives the policy unresolved.
+ * would run) out receives the policy unresolved.  The answer is the policy
+ * and kernel the product's sizes and alignment resolve to; an automatic call
+ * may run that kernel in its tile form (see FLOW_AUTO), with a workgroup tile
+ * of its own, and "bgemm_big_kernel+bgemm_reg_kernel" (large products of
+ * nearly whole tiles) is one launch of it.
  * With error correction, the split flow with tile 128x128, 256x128 or
  * 128x256, and the direct and staged flows with tile 128x128, run a
  * pipelined full-tile kernel when m and n are multiples of the tile, k is a
@@ -188,8 +196,8 @@ int sgemm_emu_batched_ex(int m, int n, int k,
  * has none: SGEMM_EMU_ERR_POLICY).  Without error correction (ec = 0, for
  * measuring what the correction costs), the split flow with tile 128x128
  * or 128x256 runs the same full-tile kernel under the same conditions, and
- * AUTO picks among those two tiles; the decomposition of large ragged
- * products is made only with error correction. */
+ * AUTO picks among those two tiles; large ragged products resolve to whole
+ * tiles only with error correction. */
 int sgemm_emu_resolve_policy(int m, int n, int k,
                              const float* A, int lda,
                              const float* B, int ldb,

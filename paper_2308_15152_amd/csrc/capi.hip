@@ -8,6 +8,7 @@
 #include "internal.h"
 #include "mfmae/frag.hpp"
 #include "sgemm_emu.h"
+#include "tile_launch.h"
 #include "tiling.hpp"
 
 namespace {
@@ -105,11 +106,8 @@ int check_gemm(int m, int n, int k, const float* A, int lda, const float* B, int
     return SGEMM_EMU_OK;
 }
 
-// The kernels a GEMM call can run.  K_NONE: an empty problem (nothing to
-// run).  K_TILED: a large product whose shape does not fill whole tiles, run
-// as its interior of whole tiles on the full-tile kernel, a k tail (k mod 32
-// values) added in place by the accumulate kernel, and the edge strips on
-// the register-flow kernel.
+// The kernels a GEMM call resolves to.  K_NONE: an empty problem (nothing to
+// run).  K_TILED: a large product whose whole tiles cover nearly all of C.
 enum Kernel { K_NONE, K_REG, K_BIG, K_LDS, K_TILED };
 
 const char* kernel_name(Kernel k) {
@@ -162,17 +160,11 @@ int resolve_gemm(int m, int n, int k, const float* A, int lda, const float* B, i
     a.vec_a = aligned16(A) && lda % 4 == 0 && st.a % 4 == 0;
     a.vec_b = aligned16(B) && ldb % 4 == 0 && st.b % 4 == 0;
     if (flow == SGEMM_EMU_FLOW_AUTO) {
-        // Full tiles take the pipelined split-flow kernel (each element
-        // split once per workgroup).  Other products take the barrier-free
-        // register-direct flow, which keeps the most bytes in flight: 1.8-5x
-        // the general LDS kernel's rate on every shape measured (1100 x 1500
-        // x 2000: 76 against 397 us; 8000^3: 5.9 against 7.2 ms).  From
-        // 2^35 multiply-adds on, a large ragged product whose whole tiles
-        // cover nearly all of C runs faster decomposed: those tiles on the
-        // full-tile kernel, the rest on the accumulate and register-flow
-        // kernels (4000^3: 557 against 613 us; 8000^3: 3.5 against 5.9 ms;
-        // 3000^3: 338 against 320 us).  The general kernel is left for
-        // unaligned operands.
+        // What the product is resolved to, by shape and alignment: full tiles
+        // to the full-tile kernel, ragged ones to the register flow (1.8-5x
+        // the general kernel's rate), large ragged ones that are nearly all
+        // whole tiles to K_TILED, unaligned operands to the general kernel.
+        // tile_form() then says which of them run on the tile kernel.
         int big_tile = SGEMM_EMU_TILE_AUTO;
         const bool wide = k >= 1024 && (int64_t)m * n * batch >= (int64_t)2048 * 2048;
         // 128x256 pays off for long k loops over much output (measured on
@@ -185,14 +177,11 @@ int resolve_gemm(int m, int n, int k, const float* A, int lda, const float* B, i
                 big_tile = t;
         const double work = (double)batch * m * n * k;  // multiply-adds (no overflow)
         const double kDecompose = 34359738368.0;         // 2^35
-        // the decomposition: whole tiles covering at least 95% of C, at least
-        // one per CU (measured: 0.95-0.98 coverage won or tied, 0.92-0.94 lost
-        // to the register-direct flow by 1.2-1.4x)
+        // nearly whole tiles: covering at least 95% of C, at least one per CU
         int tiled = SGEMM_EMU_TILE_AUTO;
         if (big_tile == SGEMM_EMU_TILE_AUTO && ec == 1 && tile == SGEMM_EMU_TILE_AUTO &&
             a.vec_a && a.vec_b && m > 1024 && n > 1024 && k >= 32 &&
             work >= kDecompose && sgemm_emu::reg_flow_supported(a, SGEMM_EMU_TILE_64x64)) {
-            // (the 128 x 128 interior lost on every shape measured)
             for (int t : {order[0], order[1]}) {
                 const Interior in = interior(a, t);
                 const int64_t ntiles =
@@ -244,76 +233,55 @@ int resolve_gemm(int m, int n, int k, const float* A, int lda, const float* B, i
     return SGEMM_EMU_OK;
 }
 
-// An edge strip (at most one tile deep, long k): the barrier-free register
-// flow on 64 x 64 tiles runs 4-6x faster than the LDS-tiled general kernel
-// there (measured on 7936 x 64 x 8000 and 64 x 8000 x 8000), since the
-// strip has too few tiles to hide the general kernel's per-step barriers.
-// The strips share A's row alignment and both leading dimensions with the
-// whole product, which was checked for this flow before K_TILED was chosen.
-hipError_t run_strip(const sgemm_emu::GemmArgs& s, hipStream_t stream) {
-    return sgemm_emu::launch_gemm_reg(s, SGEMM_EMU_TILE_64x64, true, stream);
-}
+namespace tile = sgemm_emu::tile;
 
-// K_TILED, in stream order: the interior C[0:mi, 0:ni] = A[0:mi, 0:ki]
-// B[0:ki, 0:ni] on the full-tile kernel; the k tail C[0:mi, 0:ni] +=
-// A[0:mi, ki:k] B[ki:k, 0:ni] in place; the right strip C[0:mi, ni:n] and
-// the bottom strip C[mi:m, 0:n] over the whole k on the register-flow
-// kernel (64 x 64 tiles).  Every piece is a view of the same operands (same
-// ld and item strides).
-hipError_t run_tiled(const sgemm_emu::GemmArgs& a, int tile, hipStream_t stream) {
-    const Interior in = interior(a, tile);
-    sgemm_emu::GemmArgs g = a;
-    g.m = in.m;
-    g.n = in.n;
-    g.k = in.k;
-    hipError_t e = sgemm_emu::launch_gemm_big(g, tile, SGEMM_EMU_FLOW_SPLIT, true, stream);
-    if (e != hipSuccess) return e;
-    if (in.k < a.k) {
-        sgemm_emu::AccArgs t{};
-        t.m = in.m;
-        t.n = in.n;
-        t.k = a.k - in.k;
-        t.A = a.A + in.k;
-        t.lda = a.lda;
-        t.sa = a.sa;
-        t.B = a.B + (int64_t)in.k * a.ldb;
-        t.ldb = a.ldb;
-        t.sb = a.sb;
-        t.C = a.C;
-        t.ldc = a.ldc;
-        t.sc = a.sc;
-        t.D = a.C;
-        t.ldd = a.ldc;
-        t.sd = a.sc;
-        t.batch = a.batch;
-        t.a_trans = t.b_trans = t.cd_col = false;
-        t.vec_a = a.vec_a;  // ki is a multiple of 32: rows stay 16-byte aligned
-        // row-major B (k x n) and row-major C, D: the fragment loads and
-        // stores move single elements along those layouts, so these flags
-        // only select the whole-tile path and set no alignment requirement
-        t.vec_b = t.vec_c = t.vec_d = true;
-        e = sgemm_emu::launch_gemm_acc(t, MFMAE_SHAPE_32x32x16, true, stream);
-        if (e != hipSuccess) return e;
+// The shape of the tile kernel an automatic call takes in place of the kernel
+// it resolves to, NONE to run that kernel itself.
+tile::Shape tile_form(const sgemm_emu::GemmArgs& a, Kernel kern, int resolved, tile::Problem& p,
+                      tile::Family& family) {
+    p = {a.m,  a.n,   a.k,  a.A, a.lda, a.sa,  true,  a.B,  a.ldb,
+         a.sb, false, nullptr, 0,   0,     a.C, a.ldc, a.sc, a.batch};
+    const int64_t tiles64 = (int64_t)((a.m + 63) / 64) * ((a.n + 63) / 64);
+    switch (kern) {
+        case K_LDS:
+            // unaligned rows: the general kernel loads single elements
+            // (8 x 1001 x 999 x 1003 129 us against 57, 642 x 56 x 3582 312 / 34)
+            family = tile::GENERAL;
+            break;
+        case K_TILED:
+            // interior and edges in one launch, whatever the alignment (8000^3
+            // in three launches 3.39 ms against 2.83, 6000 x 6000 x 960 282 us
+            // / 219, 2 x 2600 x 2600 x 2560 351 / 219)
+            family = tile::BIG;
+            break;
+        case K_REG:
+            // The register flow stays where it waits for HBM: a short k, or
+            // small products that leave much of their 64 x 64 tiles empty
+            // (140 x 670 x 1596 x 32 185 us against 231, 8192 x 32^3 17 / 25,
+            // 1000 x 100^3 27 / 36).  Elsewhere each of its waves loads and
+            // splits its operands by itself (1100 x 1500 x 2000 73 us against
+            // 34, 5 x 256 x 3963 x 4032 498 / 161, 51 x 3390 x 1043 x 88
+            // 410 / 362).
+            if (a.k < 64) return tile::NONE;
+            if (a.k < 256 && tiles64 * 4096 * 10 > (int64_t)a.m * a.n * 13) return tile::NONE;
+            family = tile::REG;
+            break;
+        case K_BIG: {
+            // Up to two rounds of full tiles: smaller ones, or waves that
+            // share a tile's k, keep more of the device busy (1024^3 41 us
+            // against 14, 2048^3 70 / 55, 4 x 256 x 256 x 4096 146 / 32, 32 x
+            // 512^3 35 / 29; 4096^3, two rounds, 367 / 358).  Beyond, the
+            // persistent form and the full-tile kernel's schedule win
+            // (256 x 1024 x 1024 x 128 300 us against 347).
+            const int64_t tiles = (int64_t)(a.m / tile_rows(resolved)) * (a.n / tile_cols(resolved)) *
+                                  a.batch;
+            if (tiles > 512) return tile::NONE;
+            family = tile::BIG;
+            break;
+        }
+        default: return tile::NONE;
     }
-    if (in.n < a.n) {
-        sgemm_emu::GemmArgs r = a;
-        r.m = in.m;
-        r.n = a.n - in.n;
-        r.B = a.B + in.n;
-        r.C = a.C + in.n;
-        r.vec_b = a.vec_b && in.n % 4 == 0;
-        e = run_strip(r, stream);
-        if (e != hipSuccess) return e;
-    }
-    if (in.m < a.m) {
-        sgemm_emu::GemmArgs b = a;
-        b.m = a.m - in.m;
-        b.A = a.A + (int64_t)in.m * a.lda;
-        b.C = a.C + (int64_t)in.m * a.ldc;
-        e = run_strip(b, stream);
-        if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+    return tile::choose(p);
 }
 
 int run_gemm(int m, int n, int k, const float* A, int lda, const float* B, int ldb, float* C,
@@ -321,16 +289,46 @@ int run_gemm(int m, int n, int k, const float* A, int lda, const float* B, int l
              hipStream_t stream) {
     sgemm_emu::GemmArgs a;
     Kernel kern;
+    const bool automatic = flow == SGEMM_EMU_FLOW_AUTO && tile == SGEMM_EMU_TILE_AUTO && ec == 1;
     int rc = resolve_gemm(m, n, k, A, lda, B, ldb, C, ldc, batch, st, flow, ec, tile, a, kern);
     if (rc != SGEMM_EMU_OK || kern == K_NONE) return rc;
     hipError_t e;
-    switch (kern) {
-        case K_REG: e = sgemm_emu::launch_gemm_reg(a, tile, ec != 0, stream); break;
-        case K_BIG: e = sgemm_emu::launch_gemm_big(a, tile, flow, ec != 0, stream); break;
-        case K_TILED: e = run_tiled(a, tile, stream); break;
-        default: e = sgemm_emu::launch_gemm(a, tile, flow, ec != 0, stream); break;
+    tile::Problem p;
+    tile::Family family;
+    const tile::Shape shape = automatic ? tile_form(a, kern, tile, p, family) : tile::NONE;
+    if (shape != tile::NONE) {
+        e = tile::launch(p, shape, family, stream);
+    } else {
+        switch (kern) {
+            case K_REG: e = sgemm_emu::launch_gemm_reg(a, tile, ec != 0, stream); break;
+            case K_BIG: e = sgemm_emu::launch_gemm_big(a, tile, flow, ec != 0, stream); break;
+            case K_TILED:  // C rows too far apart for the tile kernel
+                e = sgemm_emu::launch_gemm_reg(a, SGEMM_EMU_TILE_64x64, true, stream);
+                break;
+            default: e = sgemm_emu::launch_gemm(a, tile, flow, ec != 0, stream); break;
+        }
     }
     return e == hipSuccess ? SGEMM_EMU_OK : hip_fail(e);
+}
+
+// The shape of the tile kernel for an accumulate product, NONE for the kernel
+// written with the fragment interface (whose waves each load and split their
+// own operands: 4096^3 with B transposed 918 us against 379, 4 x 1252 x 168 x
+// 2434 with A transposed 169 / 31, 16384 x 64^3 203 to 233 / 186).
+tile::Shape acc_tile_form(const sgemm_emu::AccArgs& a, tile::Problem& p) {
+    // Both operands contiguous along m and n, whole 64 x 64 blocks and a short
+    // k: the fragment kernel moves whole lines too and waits for HBM without
+    // a barrier (4096 x 128^3: 190 us against 203; 1024 x 256^3: 266 / 243).
+    if (a.a_trans && !a.b_trans && a.m % 64 == 0 && a.n % 64 == 0 && a.k <= 128 && !a.cd_col &&
+        (int64_t)a.m * a.n <= 128 * 128)
+        return tile::NONE;
+    if (!a.cd_col)
+        p = {a.m,  a.n,       a.k, a.A,   a.lda, a.sa, !a.a_trans, a.B,  a.ldb,
+             a.sb, a.b_trans, a.C, a.ldc, a.sc,  a.D,  a.ldd,      a.sd, a.batch};
+    else  // D^T = op(B)^T op(A)^T, and D^T is row-major
+        p = {a.n,  a.m,        a.k, a.B,   a.ldb, a.sb, a.b_trans, a.A,  a.lda,
+             a.sa, !a.a_trans, a.C, a.ldc, a.sc,  a.D,  a.ldd,     a.sd, a.batch};
+    return tile::choose(p);
 }
 
 template <class S>
@@ -516,7 +514,12 @@ int sgemm_emu_batched_acc(int op_a, int op_b, int layout_cd, int m, int n, int k
     a.vec_b = !bt || vec_ok(B, ldb, stride.b);
     a.vec_c = C == nullptr || !cdc || vec_ok(C, ldc, stride.c);
     a.vec_d = !cdc || vec_ok(D, ldd, stride.d);
-    hipError_t e = sgemm_emu::launch_gemm_acc(a, shape, ec == 1, stream);
+    hipError_t e;
+    tile::Problem p;
+    const tile::Shape form =
+        shape == MFMAE_SHAPE_32x32x16 && ec == 1 ? acc_tile_form(a, p) : tile::NONE;
+    if (form != tile::NONE) e = tile::launch(p, form, tile::ACC, stream);
+    else e = sgemm_emu::launch_gemm_acc(a, shape, ec == 1, stream);
     return e == hipSuccess ? SGEMM_EMU_OK : hip_fail(e);
 }
 

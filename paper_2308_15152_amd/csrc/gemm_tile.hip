@@ -1,0 +1,188 @@
+// The tile kernel's instances and the choice among them (tile_gemm.hpp has
+// the kernel).
+//
+// The same code runs under the names of the kernels whose products it takes:
+// whole tiles that are too few for the full-tile kernel to fill the device
+// and large ragged products (bgemm_big_kernel), other ragged products
+// (bgemm_reg_kernel), products with unaligned rows (bgemm_emu_kernel) and the
+// accumulate form with its transposed operands (gemm_acc_kernel).
+#include "tile_gemm.hpp"
+#include "tile_launch.h"
+
+namespace sgemm_emu {
+namespace tile {
+
+namespace {
+
+#define SGEMM_EMU_TILE_KERNEL(NAME)                                                      \
+    template <class CF>                                                                  \
+    __global__ __launch_bounds__(CF::NT, CF::W) void NAME(Params p) {                    \
+        __shared__ __attribute__((aligned(16))) unsigned char smem[CF::LDS_BYTES];       \
+        run<CF>(p, smem);                                                                \
+    }
+SGEMM_EMU_TILE_KERNEL(bgemm_big_kernel)
+SGEMM_EMU_TILE_KERNEL(bgemm_reg_kernel)
+SGEMM_EMU_TILE_KERNEL(bgemm_emu_kernel)
+SGEMM_EMU_TILE_KERNEL(gemm_acc_kernel)
+#undef SGEMM_EMU_TILE_KERNEL
+
+// What a shape costs, in microseconds.  A workgroup takes `first` per chunk
+// when it has a CU to itself, and `chunk` for each of those that share one
+// (at most `fit` do), plus `ends` for filling the pipeline and storing C.
+// Fitted to the times of 100 products from 16 x 64^3 to 6000^2 x 960, odd
+// sizes among them: the shape chosen is 0.4% slower than the best one on
+// average, 13% at worst.  (Without the shapes with k groups 2%: the waves of
+// one group go through reads, products and split in step, and a second group
+// fills the gaps: 1024^3 16.4 -> 13.9 us, 2048^3 64 -> 55, 4 x 256 x 256 x 4096
+// 54 -> 32.)
+struct Cost {
+    int bm, bn, kg, fit;
+    double first, chunk, ends;
+};
+constexpr Cost kCosts[NONE] = {
+    {64, 64, 1, 4, 0.74, 0.457, 0.86},  // T64
+    {64, 64, 2, 2, 0.26, 0.305, 2.57},  // T64_K2
+    {64, 64, 4, 1, 0.25, 0.253, 3.85},  // T64_K4
+    {128, 64, 1, 2, 0.32, 0.427, 4.27}, // T128x64
+    {128, 64, 2, 1, 0.39, 0.394, 3.66}, // T128x64_K2
+    {128, 128, 1, 2, 0.60, 0.597, 4.41},// T128
+    {128, 128, 2, 1, 0.54, 0.539, 4.57},// T128_K2
+    {128, 256, 1, 1, 0.93, 0.934, 5.00},// T128x256
+};
+constexpr double kCus = 256;
+
+double cost(const Cost& c, const Problem& p) {
+    const double tiles = (double)((p.m + c.bm - 1) / c.bm) * ((p.n + c.bn - 1) / c.bn) * p.batch;
+    const int chunks = (p.k + BK - 1) / BK;
+    const double steps = (double)((chunks + c.kg - 1) / c.kg) * c.kg;
+    const double here = __builtin_ceil(tiles / kCus);  // workgroups of the busiest CU
+    double t;
+    if (here <= c.fit) {
+        const double chunk = here * c.chunk > c.first ? here * c.chunk : c.first;
+        t = steps * chunk + c.ends * (1 + 0.5 * (here - 1));
+    } else {
+        const double n = tiles / kCus + (c.fit == 1 ? 0.5 : 0.25);
+        t = (n > c.fit ? n : c.fit) * (steps * c.chunk + c.ends * (c.fit == 1 ? 1.0 : 0.6));
+    }
+    // the memory time, the same for every shape: 5.2 TB/s
+    const double bytes = 4.0 * p.batch *
+                         ((double)p.m * p.k + (double)p.k * p.n +
+                          (double)p.m * p.n * (p.C ? 2 : 1));
+    const double mem = bytes / 5.2e6;
+    return t > mem ? t : mem;
+}
+
+bool fits(const Cost& c, const Problem& p) {
+    // only the smallest tile has an EDGE form
+    if (c.bm + c.bn > 128 && (p.m < c.bm || p.n < c.bn)) return false;
+    return offsets_fit(p.a_kc, c.bm, p.lda) && offsets_fit(p.b_kc, c.bn, p.ldb) &&
+           offsets_fit(true, c.bm, p.ldd + c.bn) &&
+           (p.C == nullptr || offsets_fit(true, c.bm, p.ldc + c.bn));
+}
+
+template <class K>
+hipError_t launch_kernel(K kernel, int bm, int bn, int threads, const Problem& a,
+                         hipStream_t stream) {
+    Params p;
+    p.m = a.m;
+    p.n = a.n;
+    p.k = a.k;
+    p.A = a.A;
+    p.lda = a.lda;
+    p.sa = a.sa;
+    p.B = a.B;
+    p.ldb = a.ldb;
+    p.sb = a.sb;
+    p.C = a.C;
+    p.ldc = a.ldc;
+    p.sc = a.sc;
+    p.D = a.D;
+    p.ldd = a.ldd;
+    p.sd = a.sd;
+    p.tiles_m = cdiv(a.m, bm);
+    p.tiles_n = cdiv(a.n, bn);
+    const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
+    // one launch stays below 2^31 work-items
+    const int64_t max_tasks = (int64_t(1) << 31) / threads - 1;
+    if (tiles > max_tasks) return hipErrorInvalidConfiguration;
+    const int64_t items_per_launch = max_tasks / tiles;
+    for (int64_t i0 = 0; i0 < a.batch; i0 += items_per_launch) {
+        const int64_t items = a.batch - i0 < items_per_launch ? a.batch - i0 : items_per_launch;
+        p.ntasks = (int)(items * tiles);
+        p.item0 = (int)i0;
+        hipLaunchKernelGGL(kernel, dim3((unsigned)p.ntasks), dim3(threads), 0, stream, p);
+        const hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+template <class CF>
+hipError_t launch_cfg(const Problem& a, Family family, hipStream_t stream) {
+    auto go = [&](auto kernel) {
+        return launch_kernel(kernel, CF::BM, CF::BN, CF::NT, a, stream);
+    };
+    if constexpr (CF::ADD) return go(gemm_acc_kernel<CF>);
+    else if (family == BIG) return go(bgemm_big_kernel<CF>);
+    else if (family == REG) return go(bgemm_reg_kernel<CF>);
+    else return go(bgemm_emu_kernel<CF>);
+}
+
+template <bool A_KC, bool B_KC, bool ADD>
+hipError_t launch_shape(const Problem& a, Shape shape, Family f, hipStream_t s) {
+    const bool edge = a.m < 64 || a.n < 64;
+    switch (shape) {
+        case T64:
+            return edge ? launch_cfg<Cfg<64, 64, 2, 2, 1, 4, A_KC, B_KC, ADD, true>>(a, f, s)
+                        : launch_cfg<Cfg<64, 64, 2, 2, 1, 4, A_KC, B_KC, ADD, false>>(a, f, s);
+        case T64_K2:
+            return edge ? launch_cfg<Cfg<64, 64, 2, 2, 2, 4, A_KC, B_KC, ADD, true>>(a, f, s)
+                        : launch_cfg<Cfg<64, 64, 2, 2, 2, 4, A_KC, B_KC, ADD, false>>(a, f, s);
+        case T64_K4:
+            return edge ? launch_cfg<Cfg<64, 64, 2, 2, 4, 4, A_KC, B_KC, ADD, true>>(a, f, s)
+                        : launch_cfg<Cfg<64, 64, 2, 2, 4, 4, A_KC, B_KC, ADD, false>>(a, f, s);
+        case T128x64: return launch_cfg<Cfg<128, 64, 2, 2, 1, 2, A_KC, B_KC, ADD, false>>(a, f, s);
+        case T128x64_K2:
+            return launch_cfg<Cfg<128, 64, 2, 2, 2, 2, A_KC, B_KC, ADD, false>>(a, f, s);
+        case T128: return launch_cfg<Cfg<128, 128, 2, 2, 1, 2, A_KC, B_KC, ADD, false>>(a, f, s);
+        case T128_K2: return launch_cfg<Cfg<128, 128, 2, 2, 2, 2, A_KC, B_KC, ADD, false>>(a, f, s);
+        case T128x256:
+            return launch_cfg<Cfg<128, 256, 2, 4, 1, 2, A_KC, B_KC, ADD, false>>(a, f, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+}  // namespace
+
+Shape choose(const Problem& p, double* time) {
+    const int lim = 1 << 30;  // row, column and k indices are formed in 32 bits
+    if (p.m < 1 || p.n < 1 || p.k < 1 || p.m >= lim || p.n >= lim || p.k >= lim) return NONE;
+    if ((!p.a_kc && p.m < 4) || (!p.b_kc && p.n < 4)) return NONE;
+    Shape best = NONE;
+    double best_time = 0;
+    for (int s = 0; s < NONE; ++s) {
+        if (!fits(kCosts[s], p)) continue;
+        const double t = cost(kCosts[s], p);
+        if (best == NONE || t < best_time) {
+            best = (Shape)s;
+            best_time = t;
+        }
+    }
+    if (time) *time = best_time;
+    return best;
+}
+
+hipError_t launch(const Problem& p, Shape shape, Family family, hipStream_t stream) {
+    if (shape == NONE) return hipErrorInvalidValue;
+    if (family != ACC)  // A stored m x k, B stored k x n, nothing added
+        return p.a_kc && !p.b_kc && !p.C ? launch_shape<true, false, false>(p, shape, family, stream)
+                                         : hipErrorInvalidValue;
+    if (p.a_kc)
+        return p.b_kc ? launch_shape<true, true, true>(p, shape, family, stream)
+                      : launch_shape<true, false, true>(p, shape, family, stream);
+    return p.b_kc ? launch_shape<false, true, true>(p, shape, family, stream)
+                  : launch_shape<false, false, true>(p, shape, family, stream);
+}
+
+}  // namespace tile
+}  // namespace sgemm_emu

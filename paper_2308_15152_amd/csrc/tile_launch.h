@@ -1,0 +1,46 @@
+// Host side of the tile kernel (tile_gemm.hpp): which products it takes, with
+// which workgroup tile, and its launch.
+#pragma once
+
+#include <stdint.h>
+
+#include <hip/hip_runtime.h>
+
+namespace sgemm_emu {
+namespace tile {
+
+// D_t = op(A_t) op(B_t) + C_t, t < batch, D row-major.  a_kc: op(A)'s rows are
+// contiguous along k (A stored m x k), otherwise along m (stored k x m);
+// b_kc: op(B)'s columns are contiguous along k (B stored n x k), otherwise
+// its rows along n (stored k x n).  C null: nothing is added.
+struct Problem {
+    int m, n, k;
+    const float* A;
+    int64_t lda, sa;
+    bool a_kc;
+    const float* B;
+    int64_t ldb, sb;
+    bool b_kc;
+    const float* C;
+    int64_t ldc, sc;
+    float* D;
+    int64_t ldd, sd;
+    int batch;
+};
+
+// Workgroup tile and number of wave groups that share its k chunks.
+enum Shape { T64, T64_K2, T64_K4, T128x64, T128x64_K2, T128, T128_K2, T128x256, NONE };
+
+// The kernel the product is launched under (the same code).
+enum Family { BIG, REG, GENERAL, ACC };
+
+// The shape expected to be the fastest for this product, NONE if no shape
+// takes it (sizes or leading dimensions out of range, or fewer than four
+// values along an operand's contiguous m or n).  *time: its estimated time in
+// microseconds on a device otherwise idle.
+Shape choose(const Problem& p, double* time = nullptr);
+
+hipError_t launch(const Problem& p, Shape shape, Family family, hipStream_t stream);
+
+}  // namespace tile
+}  // namespace sgemm_emu

@@ -1,0 +1,173 @@
+"""The tile form of the GEMM and accumulate kernels (automatic policy): one
+workgroup tile of 64 x 64 to 128 x 256, chosen by the product's size, with its
+last tiles moved back over their neighbours, the k tail as the first chunk, k
+shared among wave groups where tiles are few, and buffer loads of any
+alignment.
+
+The bar is that of the GEMM tests (gpu_util.gate): each FP32 addition moves a
+result by at most an ulp of a partial sum bounded by N, whatever the order of
+the sums, and the wave groups' partial sums add at most three more additions,
+within the bar's k + 2 and k + 8 for every k here from 31 on; below that one
+group computes the product.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+import paper_2308_15152_amd as pkg
+import synth
+from gpu_util import device, gate, gate_applies, to_np
+
+pytestmark = pytest.mark.gpu
+
+GUARD = 64
+
+
+def _strided(X, pad, offset):
+    """X ([batch, r, c]) on the device with rows c + pad apart, starting
+    `offset` floats into a buffer."""
+    b, r, c = X.shape
+    flat = torch.full((b * r * (c + pad) + offset,), float("nan"), device=device())
+    view = flat[offset:].view(b, r, c + pad)[:, :, :c]
+    view.copy_(X)
+    return view
+
+
+def _output(b, r, c, pad, offset):
+    """A NaN output of that kind with guard values around it."""
+    flat = torch.full((b * r * (c + pad) + offset + 2 * GUARD,), float("nan"), device=device())
+    body = flat[GUARD + offset:GUARD + offset + b * r * (c + pad)].view(b, r, c + pad)
+    return flat, body, body[:, :, :c]
+
+
+def _check_untouched(flat, body, c, offset):
+    assert torch.isnan(flat[:GUARD + offset]).all()
+    assert torch.isnan(flat[GUARD + offset + body.numel():]).all()
+    assert torch.isnan(body[:, :, c:]).all()
+
+
+# batch, m, n, k, row padding, offset of the bases: tiles moved back by one line
+# and by all but one, one tile exactly and one line more, matrices smaller than
+# a tile in m, n or both, k of one chunk, one value more or less and of odd and
+# even numbers of chunks per wave group, and grids that take each tile shape
+# (64 x 64 with one, two and four groups, 128 x 64, 128 x 128, 128 x 256)
+SHAPES = [
+    (1, 64, 64, 66, 0, 0), (3, 65, 65, 65, 0, 0), (2, 127, 129, 95, 0, 1), (1, 63, 200, 97, 3, 2),
+    (2, 200, 61, 130, 1, 0), (5, 33, 35, 129, 2, 3), (4, 1, 4, 70, 1, 1), (2, 3, 300, 31, 0, 0),
+    (1, 70, 4, 33, 1, 0), (2, 66, 5, 1, 0, 0), (2, 68, 68, 6, 1, 1), (1, 100, 100, 1027, 0, 0),
+    (1, 131, 70, 2050, 0, 0), (300, 130, 67, 67, 0, 0), (600, 129, 131, 99, 1, 1),
+    (40, 300, 260, 287, 0, 0), (3, 1025, 1000, 161, 1, 0), (8, 1001, 999, 97, 0, 0),
+    (1, 1100, 1500, 200, 0, 0), (1, 512, 512, 512, 0, 0), (20, 128, 640, 768, 0, 0)]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_products(shape):
+    b, m, n, k, pad, offset = shape
+    print(f"case tile {shape}", flush=True)
+    A, B = synth.gemm_inputs(b, m, n, k, seed=b + m + n + k)
+    flat, body, C = _output(b, m, n, pad, offset)
+    pkg.sgemm_emu_batched(_strided(A, pad, offset), _strided(B, pad, offset), C)
+    _check_untouched(flat, body, n, offset)
+    items = sorted({0, b // 2, b - 1})
+    ref = oracle.gemm(A[items].numpy(), B[items].numpy())
+    gate(to_np(C[items]), ref, k, f"tile {shape}", max_gate=gate_applies(ref))
+    # every item against the general kernel, which takes any form of operand:
+    # both within the bar's distance of the same exact sums
+    general = pkg.sgemm_emu_batched(_strided(A, pad, offset), _strided(B, pad, offset),
+                                    policy=pkg.Policy(pkg.FLOW_SPLIT, 1, pkg.TILE_64x64))
+    N = torch.bmm(A.abs().to(device()).double(), B.abs().to(device()).double())
+    assert bool(((C.double() - general).abs() <= 2 * (k + 2) * 2.0 ** -23 * N).all())
+
+
+def test_shared_operands():
+    """One A or one B for the whole batch (item stride 0)."""
+    A, B = synth.gemm_inputs(6, 150, 170, 203, seed=5)
+    dev = device()
+    for a, b in ((A, B[0]), (A[0], B)):
+        C = to_np(pkg.sgemm_emu_batched(a.to(dev), b.to(dev)))
+        an = A.numpy() if a.dim() == 3 else np.repeat(A[:1].numpy(), 6, axis=0)
+        bn = B.numpy() if b.dim() == 3 else np.repeat(B[:1].numpy(), 6, axis=0)
+        gate(C, oracle.gemm(an, bn), 203, "tile, shared operand")
+
+
+def test_integers_exact():
+    """Small integers: every product and sum is exact in any order (also with
+    the k tail and the wave groups' sums), so the result is."""
+    g = synth.rng(8)
+    A = synth.integer_matrix((2, 150, 1031), g, -8, 8)
+    B = synth.integer_matrix((2, 1031, 90), g, -8, 8)
+    C = to_np(pkg.sgemm_emu_batched(A.to(device()), B.to(device())))
+    ref = np.einsum("bik,bkj->bij", A.numpy().astype(np.int64), B.numpy().astype(np.int64))
+    assert np.array_equal(C, ref.astype(np.float32))
+
+
+def test_far_rows():
+    """C rows further apart than the tile kernel's 32-bit offsets reach (64
+    rows of 2^23 floats): the calls take the kernels that address with 64-bit
+    pointers."""
+    m, n, k = 66, 68, 80
+    A, B = synth.gemm_inputs(1, m, n, k, seed=6)
+    buf = torch.full(((m - 1) * (1 << 23) + n,), float("nan"), device=device())
+    C = buf.as_strided((1, m, n), (0, 1 << 23, 1))
+    ref = oracle.gemm(A.numpy(), B.numpy())
+    for kk in (80, 79):
+        pkg.sgemm_emu_batched(A[:, :, :kk].to(device()), B[:, :kk].to(device()), C)
+        ref = oracle.gemm(A[:, :, :kk].contiguous().numpy(), B[:, :kk].contiguous().numpy())
+        gate(to_np(C), ref, kk, f"tile, far rows k={kk}")
+    del buf, C
+    torch.cuda.empty_cache()
+
+
+ACC_SHAPES = [(1, 64, 64, 96, 0, 0), (2, 65, 66, 67, 1, 1), (3, 130, 63, 300, 0, 0),
+              (2, 5, 131, 40, 2, 3), (1, 129, 260, 1000, 0, 0), (300, 140, 70, 64, 0, 0),
+              (30, 270, 520, 130, 1, 2), (2, 4, 4, 9, 0, 0), (1, 2050, 1030, 97, 0, 0)]
+
+
+@pytest.mark.parametrize("shape", ACC_SHAPES, ids=lambda s: "x".join(map(str, s)))
+@pytest.mark.parametrize("ta", [0, 1])
+@pytest.mark.parametrize("tb", [0, 1])
+@pytest.mark.parametrize("col", [0, 1])
+def test_accumulate(shape, ta, tb, col):
+    """Every operand and output layout; C apart, C in place and no C."""
+    b, m, n, k, pad, offset = shape
+    print(f"case tile acc {shape} ta={ta} tb={tb} col={col}", flush=True)
+    g = synth.rng(m + n + k)
+    A, B = synth.uniform((b, m, k), g), synth.uniform((b, k, n), g)
+    C = synth.uniform((b, m, n), g)
+    stored = lambda X, t: X.transpose(1, 2).contiguous() if t else X  # noqa: E731
+    Ad = _strided(stored(A, ta), pad, offset)
+    Bd = _strided(stored(B, tb), pad, offset)
+    Cs = stored(C, col)
+    r, c = Cs.shape[1:]
+    kw = dict(op_a=ta, op_b=tb, layout=col)
+    items = sorted({0, b // 2, b - 1})
+    logical = lambda D: to_np(D[items]).transpose(0, 2, 1) if col else to_np(D[items])  # noqa: E731
+    an, bn, cn = A[items].numpy(), B[items].numpy(), C[items].numpy()
+    ref = oracle.gemm_acc(an, bn, cn)
+    flat, body, D = _output(b, r, c, pad, offset)
+    pkg.sgemm_emu_batched_acc(Ad, Bd, _strided(Cs, pad, offset), D, **kw)
+    _check_untouched(flat, body, c, offset)
+    gate(logical(D), ref, k, f"tile acc {shape}", max_gate=gate_applies(ref))
+    apart = D.clone()
+    D.copy_(Cs)
+    pkg.sgemm_emu_batched_acc(Ad, Bd, D, D, **kw)  # in place: the same sums
+    _check_untouched(flat, body, c, offset)
+    assert torch.equal(D, apart)
+    pkg.sgemm_emu_batched_acc(Ad, Bd, None, D, **kw)
+    ref0 = oracle.gemm(an, bn)
+    gate(logical(D), ref0, k, f"tile acc, no C {shape}", max_gate=gate_applies(ref0))
+
+
+def test_in_place_where_tiles_overlap():
+    """Tiles moved back over their neighbours read and write only their own
+    outputs: D += A B in place gives the same bits every time."""
+    g = synth.rng(12)
+    A, B = synth.uniform((4, 321, 70), g).to(device()), synth.uniform((4, 70, 333), g).to(device())
+    C = synth.uniform((4, 321, 333), g).to(device())
+    first = None
+    for _ in range(5):
+        D = C.clone()
+        pkg.sgemm_emu_batched_acc(A, B, D, D)
+        first = D if first is None else first
+        assert torch.equal(D, first)
