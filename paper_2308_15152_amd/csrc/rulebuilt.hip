@@ -19,17 +19,27 @@
 //     (i, j) embedded at compile time every map() folds to a constant.  The
 //     baseline writes G to LDS and loads the fragments from there.
 //
-// One wavefront handles one batch item and up to 64 columns of B.  B is
-// read straight from global memory into the B-operand registers.  When rows
-// allow 8-byte accesses the two 32-column blocks interleave their columns,
-// so for a fixed k the 32 lanes of a half-wave read one 256-byte row segment
-// with one 8-byte load each (and C is written the same way); otherwise lane
-// l holds column l % 32 of each block (128-byte segments).  The kernels are
-// bound by HBM traffic (B read once, C written once).
+// One wavefront handles one batch item and up to 64 columns of B, in two
+// 32-column blocks, or in one if at most 32 columns are left (CB): products of
+// few columns are bound by the vector instructions of building the left
+// operand and of splitting B, not by HBM traffic (B read once, C written once)
+// as those of 64 are.  262,144 items with 24 columns: 1100 us with two blocks,
+// half empty, and one value split at a time.
+// B is read straight from global memory into the B-operand registers.  When
+// rows allow 8-byte accesses the two 32-column blocks interleave their
+// columns, so for a fixed k the 32 lanes of a half-wave read one 256-byte row
+// segment with one 8-byte load each (and C is written the same way); otherwise
+// lane l holds column l % 32 of each block (128-byte segments).  Loads and
+// stores are buffer accesses on the item's corner: a scalar row offset and a
+// lane offset, which for a lane without a column lies past the descriptor's
+// end (its loads return zero, its stores are dropped).  Row pitches of 2^22
+// floats and more, which 32-bit offsets don't reach, take 64-bit pointers
+// (FAR).
 #include "internal.h"
 #include "mfmae/frag.hpp"
 #include "mfmae/tcec.hpp"
 #include "sgemm_emu.h"
+#include "tiling.hpp"
 
 namespace sgemm_emu {
 
@@ -87,18 +97,19 @@ struct HouseholderRule {
     }
 
     __device__ void build(int s, half8_t (&hh)[2], half8_t (&hl)[2]) const {
+        float h[2][8];
         mfmae::foreach_ij<FragA>([&](int e, int i, int jj) {
             const int gj = 16 * s + jj;
             const float uj = __shfl(ulane, gj);
 #pragma unroll
             for (int tm = 0; tm < 2; ++tm) {
-                const float h = __builtin_fmaf(urow[tm], uj, (32 * tm + i) == gj ? 1.0f : 0.0f);
-                _Float16 vh, vl;
-                mfmae::tcec::split_rounded(h, vh, vl);
-                hh[tm][e] = vh;
-                hl[tm][e] = vl;
+                // the diagonal crosses block tm in its own two k steps only
+                const float delta = s >> 1 == tm && 32 * tm + i == gj ? 1.0f : 0.0f;
+                h[tm][e] = mfmae::tcec::as_fp32(__builtin_fmaf(urow[tm], uj, delta));
             }
         });
+#pragma unroll
+        for (int tm = 0; tm < 2; ++tm) mfmae::tcec::split8(h[tm], hh[tm], hl[tm]);
     }
 };
 
@@ -119,16 +130,13 @@ __device__ inline void set_entry(FragA (&f)[2], int s, int r, int q, _Float16 v)
             if (t == tm && e == elem) f[t].x[e] = v;
 }
 
-// Givens rotation through map().  EMBED: the plane (I, J) is a compile-time
-// constant; otherwise it comes from the kernel arguments.
-template <bool EMBED, int I, int J>
+// Givens rotation through map(), the plane (I, J) a compile-time constant.
+template <int I, int J>
 struct GivensMapRule {
-    int gi, gj;
+    static constexpr int gi = I, gj = J;
     _Float16 ch, cl, sh, sl, nsh, nsl;  // hi/lo of c, s and -s
 
     __device__ void init(const RuleParams& p, int64_t item, unsigned char*) {
-        gi = EMBED ? I : p.gi;
-        gj = EMBED ? J : p.gj;
         const float c = p.c[item * p.scs];
         const float s = p.s[item * p.scs];
         mfmae::tcec::split(c, ch, cl);
@@ -159,6 +167,64 @@ struct GivensMapRule {
         for (int t = 0; t < 2; ++t) {
             hh[t] = mfmae::pack(fh[t]);
             hl[t] = mfmae::pack(fl[t]);
+        }
+    }
+};
+
+// Givens rotation with the plane as kernel arguments.  Where map() would find
+// the lane and element of each nonzero entry, a lane asks the same of the two
+// rows it holds (r = 32 tm + l % 32): the diagonal entry, 1 or c, and in rows
+// i and j one more, -s or s.  An operand row is 32 words of two halves, word
+// 8 s + 4 (l / 32) + w in the lane's registers of k step s, so placing an
+// entry is one compare and one select per word (a select per element of every
+// entry took 1995 vector instructions per wave).
+struct GivensArgRule {
+    uint32_t diag[2], diag_lo[2];  // the entry's hi and lo, in their half of the word
+    uint32_t off[2], off_lo[2];
+    int diag_word[2], off_word[2];  // the word of the row that holds it
+
+    __device__ void init(const RuleParams& p, int64_t item, unsigned char*) {
+        const float c = p.c[item * p.scs];
+        const float s = p.s[item * p.scs];
+        const int l = threadIdx.x & 63;
+#pragma unroll
+        for (int tm = 0; tm < 2; ++tm) {
+            const int r = 32 * tm + (l & 31);
+            const bool in_i = r == p.gi, in_j = r == p.gj;
+            put(in_i || in_j ? c : 1.0f, r, diag[tm], diag_lo[tm], diag_word[tm]);
+            put(in_i ? -s : in_j ? s : 0.0f, in_i ? p.gj : p.gi, off[tm], off_lo[tm],
+                off_word[tm]);
+            if (!in_i && !in_j) off_word[tm] = -1;
+        }
+    }
+
+    __device__ static void put(float v, int col, uint32_t& hi, uint32_t& lo, int& word) {
+        _Float16 h, x;
+        mfmae::tcec::split(v, h, x);
+        hi = (uint32_t)__builtin_bit_cast(uint16_t, h) << (16 * (col & 1));
+        lo = (uint32_t)__builtin_bit_cast(uint16_t, x) << (16 * (col & 1));
+        word = col >> 1;
+    }
+
+    __device__ void build(int s, half8_t (&hh)[2], half8_t (&hl)[2]) const {
+        typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+        const int first = 8 * s + 4 * ((threadIdx.x & 63) >> 5);
+#pragma unroll
+        for (int tm = 0; tm < 2; ++tm) {
+            u32x4 h, x;
+#pragma unroll
+            for (int w = 0; w < 4; ++w) {
+                const bool o = off_word[tm] == first + w;
+                h[w] = o ? off[tm] : 0u;
+                x[w] = o ? off_lo[tm] : 0u;
+                if (s >> 1 == tm) {
+                    const bool d = diag_word[tm] == first + w;
+                    h[w] |= d ? diag[tm] : 0u;
+                    x[w] |= d ? diag_lo[tm] : 0u;
+                }
+            }
+            hh[tm] = __builtin_bit_cast(half8_t, h);
+            hl[tm] = __builtin_bit_cast(half8_t, x);
         }
     }
 };
@@ -257,87 +323,128 @@ struct HouseholderLdsRule : LdsOperand {
 };
 
 // ---------------------------------------------------------------------------
-// The common body: one wave = one item and one group of 64 columns.
+// The common body: one wave = one item and one group of up to 32 CB columns.
 // PAIR: the two 32-column blocks interleave their columns (column j of
 // block cb is c0 + 2 j + cb), so one 8-byte load of a B row and one 8-byte
-// store of a C row serve both blocks; needs 8-byte aligned, even-length B
-// and C rows.  Otherwise block cb holds columns c0 + 32 cb + j.
+// store of a C row serve both blocks (buffer accesses: 4-byte alignment is
+// enough); needs an even number of columns.  Otherwise block cb holds columns
+// c0 + 32 cb + j.
 // ---------------------------------------------------------------------------
-template <class Rule, bool PAIR>
-__device__ inline void rule64_body(const RuleParams& p, unsigned char* lds) {
-    // wave index as a wave-uniform (scalar) value, so that the per-item base
-    // pointers below live in SGPRs and loads use scalar-base addressing
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int l = threadIdx.x & 63;
-    const int64_t task = (int64_t)blockIdx.x * kWaves + wave;
-    const int ngroups = (p.ncols + 63) / 64;
-    const int64_t local = task / ngroups;
-    const int c0 = (int)(task - local * ngroups) * 64;
-    if (local >= p.batch) return;  // whole wave; the kernels have no barrier
-    const int64_t item = local + p.item0;
+constexpr uint32_t kPastEnd = 0x80000000;  // no buffer offset in use reaches this
 
-    const float* __restrict__ Bi = p.B + item * p.sb;
-    float* __restrict__ Ci = p.C + item * p.sc;
+// One B or C item from column c0 on: rows ld apart, the lane's first column
+// (and, PAIR, its neighbour) or both of its columns.
+template <int CB, bool PAIR, bool FAR, bool LINES>
+struct Rows {
+    // streaming accesses: neither B nor C is touched twice
+    static constexpr int kCache = LINES ? 2 : 0;
 
-    Rule rule;
-    rule.init(p, item, lds);
+    float* p;
+    int64_t ld;
+    uint32_t off[CB];  // bytes from the item's corner to (lane row, column); FAR: floats
+    bool ok[CB];
 
-    const int j = l & 31;
-    // first column of this lane in block 0, and whether it (and, paired,
-    // its neighbour) lies inside B
-    const int col0 = PAIR ? c0 + 2 * j : c0 + j;
-    const bool ok0 = col0 < p.ncols;
-    const bool ok1 = PAIR ? ok0 : col0 + 32 < p.ncols;
-
-    f32x16_t acc[2][2], cor[2][2];
+    // The lane's rows are `row` and what a scalar row offset adds to it.
+    __device__ void init(float* base, int64_t ld_, int row, int ncols) {
+        p = base;
+        ld = ld_;
+        const int j = threadIdx.x & 31;
 #pragma unroll
-    for (int tm = 0; tm < 2; ++tm)
+        for (int cb = 0; cb < CB; ++cb) {
+            const int col = PAIR ? 2 * j : 32 * cb + j;
+            ok[cb] = col < ncols;
+            if constexpr (FAR) off[cb] = (uint32_t)col;
+            else off[cb] = ok[cb] ? (uint32_t)(row * ld + col) * 4u : kPastEnd;
+        }
+        if constexpr (FAR) p += row * ld;
+    }
+
+    __device__ __amdgpu_buffer_rsrc_t rsrc() const {
+        return __builtin_amdgcn_make_buffer_rsrc(p, 0, (int)kPastEnd, 0x00020000);
+    }
+
+    __device__ void load(int row, float (&x)[CB]) const {
+        const int s = (int)((uint32_t)ld * 4u * (uint32_t)row);
+        if constexpr (FAR) {
 #pragma unroll
-        for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-            for (int e = 0; e < 16; ++e) {
-                acc[tm][cb][e] = 0.0f;
-                cor[tm][cb][e] = 0.0f;
+            for (int cb = 0; cb < CB; ++cb) {
+                const float* q = p + row * ld + off[PAIR ? 0 : cb] + (PAIR ? cb : 0);
+                x[cb] = ok[cb] ? *q : 0.0f;
             }
-
+        } else if constexpr (PAIR) {
+            const f32x2 v = __builtin_bit_cast(
+                f32x2, __builtin_amdgcn_raw_buffer_load_b64(rsrc(), off[0], s, kCache));
+            x[0] = v[0];
+            x[1] = v[1];
+        } else {
 #pragma unroll
-    for (int s = 0; s < 4; ++s) {
-        // B operands of this 16-wide k step for both column blocks: lane l
-        // holds rows 16 s + 8 (l / 32) + e; the row start of (s, e) is
-        // wave-uniform and the lane part is a 32-bit offset.
-        half8_t bh[2], bl[2];
-        const int lane_off = 8 * (l >> 5) * (int)p.ldb + col0;
+            for (int cb = 0; cb < CB; ++cb)
+                x[cb] = __builtin_bit_cast(
+                    float, __builtin_amdgcn_raw_buffer_load_b32(rsrc(), off[cb], s, kCache));
+        }
+    }
+
+    __device__ void store(int row, const float (&x)[CB]) const {
+        typedef uint32_t u32x2 __attribute__((ext_vector_type(2)));
+        const int s = (int)((uint32_t)ld * 4u * (uint32_t)row);
+        if constexpr (FAR) {
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+                if (ok[cb]) p[row * ld + off[PAIR ? 0 : cb] + (PAIR ? cb : 0)] = x[cb];
+        } else if constexpr (PAIR) {
+            __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, f32x2{x[0], x[1]}),
+                                                  rsrc(), off[0], s, kCache);
+        } else {
+#pragma unroll
+            for (int cb = 0; cb < CB; ++cb)
+                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x[cb]), rsrc(),
+                                                      off[cb], s, kCache);
+        }
+    }
+};
+
+template <class Rule, int CB, bool PAIR, bool FAR, bool LINES>
+__device__ __forceinline__ void rule64_group(const RuleParams& p, const Rule& rule, int64_t item,
+                                             int c0) {
+    const int l = threadIdx.x & 63;
+    Rows<CB, PAIR, FAR, LINES> B, C;
+    // operand rows 8 (l / 32) + .., accumulator rows 4 (l / 32) + ..
+    B.init(const_cast<float*>(p.B + item * p.sb + c0), p.ldb, 8 * (l >> 5), p.ncols - c0);
+    C.init(p.C + item * p.sc + c0, p.ldc, 4 * (l >> 5), p.ncols - c0);
+
+    // B of the whole group: lane l holds rows 16 s + 8 (l / 32) + e of k step s.
+    // With one block all of it goes out ahead of the products (the scheduling
+    // barrier keeps it there: 262,144 items of 24 columns 585 us against 621);
+    // with two the scheduler's order, one k step at a time, is the better one
+    // (64 columns 1536 us against 1663).
+    float x[4][CB][8];
+#pragma unroll
+    for (int s = 0; s < 4; ++s)
 #pragma unroll
         for (int e = 0; e < 8; ++e) {
-            const float* rowp = Bi + (int64_t)(16 * s + e) * p.ldb;
-            float x[2];
-            if constexpr (PAIR) {
-                f32x2 v = {0.0f, 0.0f};
-                if (ok0) v = *reinterpret_cast<const f32x2*>(rowp + lane_off);
-                x[0] = v[0];
-                x[1] = v[1];
-            } else {
-                x[0] = ok0 ? rowp[lane_off] : 0.0f;
-                x[1] = ok1 ? rowp[lane_off + 32] : 0.0f;
-            }
+            float v[CB];
+            B.load(16 * s + e, v);
 #pragma unroll
-            for (int cb = 0; cb < 2; ++cb) {
-                _Float16 vh, vl;
-                mfmae::tcec::split(x[cb], vh, vl);
-                bh[cb][e] = vh;
-                bl[cb][e] = vl;
-            }
+            for (int cb = 0; cb < CB; ++cb) x[s][cb][e] = v[cb];
         }
-        half8_t hh[2], hl[2];
+    if constexpr (CB == 1) __builtin_amdgcn_sched_barrier(0);
+
+    f32x16_t acc[2][CB], cor[2][CB];
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+        half8_t bh[CB], bl[CB], hh[2], hl[2];
+#pragma unroll
+        for (int cb = 0; cb < CB; ++cb) mfmae::tcec::split8(x[s][cb], bh[cb], bl[cb]);
         rule.build(s, hh, hl);
+        const f32x16_t zero = {};
 #pragma unroll
         for (int tm = 0; tm < 2; ++tm)
 #pragma unroll
-            for (int cb = 0; cb < 2; ++cb) {
-                acc[tm][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(hh[tm], bh[cb], acc[tm][cb],
-                                                                     0, 0, 0);
-                cor[tm][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(hl[tm], bh[cb], cor[tm][cb],
-                                                                     0, 0, 0);
+            for (int cb = 0; cb < CB; ++cb) {
+                acc[tm][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+                    hh[tm], bh[cb], s == 0 ? zero : acc[tm][cb], 0, 0, 0);
+                cor[tm][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(
+                    hl[tm], bh[cb], s == 0 ? zero : cor[tm][cb], 0, 0, 0);
                 cor[tm][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(hh[tm], bl[cb], cor[tm][cb],
                                                                      0, 0, 0);
             }
@@ -349,48 +456,72 @@ __device__ inline void rule64_body(const RuleParams& p, unsigned char* lds) {
     for (int tm = 0; tm < 2; ++tm)
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
-            const int row = 32 * tm + mfmae::layout<Shape32, Use::Acc>::row(l, e);
-            float v[2];
+            float v[CB];
 #pragma unroll
-            for (int cb = 0; cb < 2; ++cb)
+            for (int cb = 0; cb < CB; ++cb)
                 v[cb] = __builtin_fmaf(cor[tm][cb][e], mfmae::tcec::kLoScaleInv, acc[tm][cb][e]);
-            float* dst = Ci + (int64_t)row * p.ldc + col0;
-            if constexpr (PAIR) {
-                if (ok0) *reinterpret_cast<f32x2*>(dst) = f32x2{v[0], v[1]};
-            } else {
-                if (ok0) dst[0] = v[0];
-                if (ok1) dst[32] = v[1];
-            }
+            C.store(32 * tm + 8 * (e >> 2) + (e & 3), v);
         }
 }
 
-template <bool PAIR>
-__global__ __launch_bounds__(64 * kWaves, 2) void householder64_kernel(RuleParams p) {
-    rule64_body<HouseholderRule, PAIR>(p, nullptr);
+// The workgroup's place in the batch: 32 consecutive ones on each XCD of every
+// 256 dispatched together (in order where no whole 256 are left).
+__device__ inline int xcd_blocks(int b, int G) {
+    return (b | 255) < G ? (b & ~255) + (b & 7) * 32 + ((b & 255) >> 3) : b;
 }
 
-template <bool PAIR>
+// CB: 32-column blocks of a wave's group; a last group of up to 32 columns
+// takes one.
+template <class Rule, int CB, bool PAIR, bool FAR, bool LINES>
+__device__ __forceinline__ void rule64_body(const RuleParams& p, unsigned char* lds) {
+    // wave index as a wave-uniform (scalar) value, so that the per-item base
+    // pointers live in SGPRs
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    // Every XCD takes one contiguous range of the batch, or, with one block, 32
+    // workgroups in a row of every 256: 64 columns 1491 against 1536 us in
+    // dispatch order (1426 with streaming stores, 1387 with streaming loads
+    // too), 40,000 items of 444 columns 1690 / 1974, 24 columns 574 / 585.
+    const int wg = CB == 1 ? xcd_blocks(blockIdx.x, gridDim.x) : xcd_task(blockIdx.x, gridDim.x);
+    const int64_t task = (int64_t)wg * kWaves + wave;
+    const int ngroups = (p.ncols + 32 * CB - 1) / (32 * CB);
+    const int64_t local = task / ngroups;
+    const int c0 = (int)(task - local * ngroups) * 32 * CB;
+    if (local >= p.batch) return;  // whole wave; the kernels have no barrier
+    const int64_t item = local + p.item0;
+    Rule rule;
+    rule.init(p, item, lds);
+    if (CB > 1 && p.ncols - c0 <= 32) rule64_group<Rule, 1, false, FAR, LINES>(p, rule, item, c0);
+    else rule64_group<Rule, CB, PAIR, FAR, LINES>(p, rule, item, c0);
+}
+
+// One block per wave leaves registers for four waves per SIMD.
+template <int CB, bool PAIR, bool FAR, bool LINES>
+__global__ __launch_bounds__(64 * kWaves, CB == 1 ? 4 : 2) void householder64_kernel(RuleParams p) {
+    rule64_body<HouseholderRule, CB, PAIR, FAR, LINES>(p, nullptr);
+}
+
+template <int CB, bool PAIR, bool FAR, bool LINES>
 __global__ __launch_bounds__(64 * kWaves, 2) void householder64_lds_kernel(RuleParams p) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[kWaves][2 * 64 * 128];
-    rule64_body<HouseholderLdsRule, PAIR>(p, lds[threadIdx.x >> 6]);
+    rule64_body<HouseholderLdsRule, CB, PAIR, FAR, LINES>(p, lds[threadIdx.x >> 6]);
 }
 
-template <bool EMBED, int I, int J, bool PAIR>
-__global__ __launch_bounds__(64 * kWaves, 2) void givens64_kernel(RuleParams p) {
-    rule64_body<GivensMapRule<EMBED, I, J>, PAIR>(p, nullptr);
+template <class Rule, int CB, bool PAIR, bool FAR, bool LINES>
+__global__ __launch_bounds__(64 * kWaves, CB == 1 ? 4 : 2) void givens64_kernel(RuleParams p) {
+    rule64_body<Rule, CB, PAIR, FAR, LINES>(p, nullptr);
 }
 
-template <bool PAIR>
+template <int CB, bool PAIR, bool FAR, bool LINES>
 __global__ __launch_bounds__(64 * kWaves, 2) void givens64_lds_kernel(RuleParams p) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[kWaves][2 * 64 * 128];
-    rule64_body<GivensLdsRule, PAIR>(p, lds[threadIdx.x >> 6]);
+    rule64_body<GivensLdsRule, CB, PAIR, FAR, LINES>(p, lds[threadIdx.x >> 6]);
 }
 
 // Launch `kernel` over the batch in pieces below 2^31 work-items (the
 // dispatch packet counts work-items in 32 bits).
 template <class K>
-hipError_t launch_rule(K kernel, RuleParams p, int64_t batch, hipStream_t stream) {
-    const int64_t ngroups = (p.ncols + 63) / 64;
+hipError_t launch_rule(K kernel, int cols, RuleParams p, int64_t batch, hipStream_t stream) {
+    const int64_t ngroups = (p.ncols + cols - 1) / cols;
     const int64_t max_blocks = (int64_t(1) << 31) / (64 * kWaves) - 1;
     const int64_t items_per_launch = max_blocks * kWaves / ngroups;
     if (items_per_launch == 0) return hipErrorInvalidConfiguration;
@@ -406,23 +537,35 @@ hipError_t launch_rule(K kernel, RuleParams p, int64_t batch, hipStream_t stream
     return hipSuccess;
 }
 
-bool pairs_ok(const float* B, int64_t ldb, int64_t sb, const float* C, int64_t ldc, int64_t sc,
-              int ncols) {
-    return ((uintptr_t)B % 8 == 0) && ((uintptr_t)C % 8 == 0) && ldb % 2 == 0 && ldc % 2 == 0 &&
-           sb % 2 == 0 && sc % 2 == 0 && ncols % 2 == 0;
+// Byte offsets of 64 rows and 64 columns below kPastEnd.
+bool near(const RuleParams& p) { return p.ldb < (1 << 22) && p.ldc < (1 << 22); }
+
+// Whether B's and C's rows are whole 128-byte lines: they are then streamed
+// past the caches.  Otherwise the pieces of a line meet there (40,000 items of
+// 444 columns 1690 us against 2263 streamed).
+bool whole_lines(const RuleParams& p) {
+    return ((uintptr_t)p.B % 128 == 0) && ((uintptr_t)p.C % 128 == 0) && p.ldb % 32 == 0 &&
+           p.ldc % 32 == 0 && p.sb % 32 == 0 && p.sc % 32 == 0 && p.ncols % 32 == 0;
 }
+
+// Launches KERNEL(CB, PAIR, FAR, LINES), a kernel instance, by shape and
+// strides.
+#define SGEMM_EMU_RULE_LAUNCH(KERNEL)                                                          \
+    (!near(p)           ? launch_rule(KERNEL(2, false, true, false), 64, p, batch, stream)     \
+     : p.ncols <= 32    ? launch_rule(KERNEL(1, false, false, false), 32, p, batch, stream)    \
+     : whole_lines(p)   ? launch_rule(KERNEL(2, true, false, true), 64, p, batch, stream)      \
+     : p.ncols % 2 == 0 ? launch_rule(KERNEL(2, true, false, false), 64, p, batch, stream)     \
+                        : launch_rule(KERNEL(2, false, false, false), 64, p, batch, stream))
 
 // The rotation planes (i, j) with a compile-time instance of the Givens
 // kernel.
 #define SGEMM_EMU_GIVENS_PLANES(X) X(5, 37) X(37, 5) X(0, 1) X(31, 32) X(62, 63)
 
-template <bool PAIR>
-hipError_t launch_givens_embedded(const RuleParams& p, int64_t batch, hipStream_t stream) {
-#define SGEMM_EMU_GIVENS_CASE(I, J) \
-    if (p.gi == I && p.gj == J) return launch_rule(givens64_kernel<true, I, J, PAIR>, p, batch, stream);
-    SGEMM_EMU_GIVENS_PLANES(SGEMM_EMU_GIVENS_CASE)
-#undef SGEMM_EMU_GIVENS_CASE
-    return hipErrorInvalidValue;
+template <class Rule>
+hipError_t launch_givens(const RuleParams& p, int64_t batch, hipStream_t stream) {
+#define SGEMM_EMU_KERNEL(CB, PAIR, FAR, LINES) givens64_kernel<Rule, CB, PAIR, FAR, LINES>
+    return SGEMM_EMU_RULE_LAUNCH(SGEMM_EMU_KERNEL);
+#undef SGEMM_EMU_KERNEL
 }
 
 }  // namespace
@@ -446,12 +589,13 @@ hipError_t launch_householder64(const HouseholderArgs& a, hipStream_t stream) {
     p.C = a.C;
     p.ldc = a.ldc;
     p.sc = a.sc;
-    const bool pair = pairs_ok(a.B, a.ldb, a.sb, a.C, a.ldc, a.sc, a.ncols);
-    if (a.mode == SGEMM_EMU_HOUSEHOLDER_LDS)
-        return pair ? launch_rule(householder64_lds_kernel<true>, p, a.batch, stream)
-                    : launch_rule(householder64_lds_kernel<false>, p, a.batch, stream);
-    return pair ? launch_rule(householder64_kernel<true>, p, a.batch, stream)
-                : launch_rule(householder64_kernel<false>, p, a.batch, stream);
+    const int64_t batch = a.batch;
+#define SGEMM_EMU_KERNEL(CB, PAIR, FAR, LINES) householder64_kernel<CB, PAIR, FAR, LINES>
+#define SGEMM_EMU_LDS_KERNEL(CB, PAIR, FAR, LINES) householder64_lds_kernel<CB, PAIR, FAR, LINES>
+    if (a.mode == SGEMM_EMU_HOUSEHOLDER_LDS) return SGEMM_EMU_RULE_LAUNCH(SGEMM_EMU_LDS_KERNEL);
+    return SGEMM_EMU_RULE_LAUNCH(SGEMM_EMU_KERNEL);
+#undef SGEMM_EMU_KERNEL
+#undef SGEMM_EMU_LDS_KERNEL
 }
 
 hipError_t launch_givens64(const GivensArgs& a, hipStream_t stream) {
@@ -468,18 +612,18 @@ hipError_t launch_givens64(const GivensArgs& a, hipStream_t stream) {
     p.C = a.C;
     p.ldc = a.ldc;
     p.sc = a.sc;
-    const bool pair = pairs_ok(a.B, a.ldb, a.sb, a.C, a.ldc, a.sc, a.ncols);
-    switch (a.mode) {
-        case SGEMM_EMU_GIVENS_EMBEDDED:
-            return pair ? launch_givens_embedded<true>(p, a.batch, stream)
-                        : launch_givens_embedded<false>(p, a.batch, stream);
-        case SGEMM_EMU_GIVENS_LDS:
-            return pair ? launch_rule(givens64_lds_kernel<true>, p, a.batch, stream)
-                        : launch_rule(givens64_lds_kernel<false>, p, a.batch, stream);
-        default:
-            return pair ? launch_rule(givens64_kernel<false, 0, 0, true>, p, a.batch, stream)
-                        : launch_rule(givens64_kernel<false, 0, 0, false>, p, a.batch, stream);
+    const int64_t batch = a.batch;
+    if (a.mode == SGEMM_EMU_GIVENS_EMBEDDED) {
+#define SGEMM_EMU_GIVENS_CASE(I, J) \
+    if (p.gi == I && p.gj == J) return launch_givens<GivensMapRule<I, J>>(p, batch, stream);
+        SGEMM_EMU_GIVENS_PLANES(SGEMM_EMU_GIVENS_CASE)
+#undef SGEMM_EMU_GIVENS_CASE
+        return hipErrorInvalidValue;
     }
+#define SGEMM_EMU_LDS_KERNEL(CB, PAIR, FAR, LINES) givens64_lds_kernel<CB, PAIR, FAR, LINES>
+    if (a.mode == SGEMM_EMU_GIVENS_LDS) return SGEMM_EMU_RULE_LAUNCH(SGEMM_EMU_LDS_KERNEL);
+#undef SGEMM_EMU_LDS_KERNEL
+    return launch_givens<GivensArgRule>(p, batch, stream);
 }
 
 }  // namespace sgemm_emu
