@@ -64,8 +64,8 @@ SCAN_METRIC = "inclusive scan of FP32 rows, elements/s (batched)"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 
 
-KERNEL_SOURCES = {  # the translation unit of each kernel; shared headers are added
-    "bgemm_reg_kernel": "bgemm_reg.hip",
+KERNEL_SOURCES = {  # the translation unit(s) of each kernel; shared headers are added
+    "bgemm_reg_kernel": ("bgemm_reg.hip", "gemm_tile.hip"),
     "bgemm_big_kernel": "bgemm_big.hip",
     "bgemm_big_stream_kernel": "bgemm_big.hip",
     "bgemm_emu_kernel": "bgemm.hip",
@@ -88,11 +88,13 @@ def _code_text(text: str) -> str:
 
 def kernel_source_hash(kernel: str) -> str:
     """SHA-256 over the code (comments and layout ignored) a kernel is built
-    from: its translation unit and every header it includes (transitively,
+    from: its translation units and every header they include (transitively,
     quoted includes found in the package's csrc/ or in include/)."""
     csrc = os.path.join(ROOT, "paper_2308_15152_amd", "csrc")
     inc = os.path.join(ROOT, "include")
-    seen, todo = set(), [os.path.join(csrc, KERNEL_SOURCES[kernel])]
+    units = KERNEL_SOURCES[kernel]
+    units = (units,) if isinstance(units, str) else units
+    seen, todo = set(), [os.path.join(csrc, u) for u in units]
     while todo:
         f = todo.pop()
         if f in seen:

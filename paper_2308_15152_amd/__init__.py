@@ -87,6 +87,8 @@ class Policy(ctypes.Structure):
 
 
 _lib = None
+_fast = {}     # entry points with plain C argument types, see load()
+_torch = None  # imported by the first call that takes tensors
 _NO_SWITCH = contextlib.nullcontext()
 
 
@@ -162,6 +164,16 @@ def load():
         fn = getattr(lib, name)
         fn.argtypes = args
         fn.restype = ctypes.c_int if res is i32 else res  # plain int results
+    # The entry points called once per launch again, with plain C types: the
+    # checked ones convert every argument in Python, 5 us a call.  Their
+    # callers below check the ranges themselves.
+    plain = {i32: ctypes.c_int, i64: ctypes.c_int64}
+    for name in ("sgemm_emu_batched", "sgemm_emu_batched_ex", "sgemm_emu_batched_acc",
+                 "sgemm_emu_scan", "householder_emu_batched_ex", "givens_emu_batched"):
+        fn = lib[name]  # a function object of its own
+        fn.argtypes = [plain.get(a, a) for a in sig[name][0]]
+        fn.restype = ctypes.c_int
+        _fast[name] = fn
     _lib = lib
     return lib
 
@@ -197,25 +209,62 @@ def _ptr(t) -> ctypes.c_void_p:
     return ctypes.c_void_p(0 if t is None else int(t.data_ptr()))
 
 
+def _load_torch():
+    global _torch
+    if _torch is None:
+        import torch
+
+        _torch = torch
+    return _torch
+
+
+def _device_index(*ts) -> int:
+    """Index of the one device every tensor given (None skipped) is on."""
+    dev = -1
+    for t in ts:
+        if t is None:
+            continue
+        d = t.get_device() if t.is_cuda else -1
+        if d < 0:
+            raise ValueError("every operand must be a device tensor")
+        if dev >= 0 and d != dev:
+            raise ValueError(f"operands on different devices: cuda:{dev} and cuda:{d}")
+        dev = d
+    return dev
+
+
 def _on_device(*ts):
     """Context for a launch on the tensors' device: every tensor given (None
     skipped) must be a device tensor of one device, which is made current so
     that the kernels and the current stream are that device's."""
-    import torch
-
-    dev = None
-    for t in ts:
-        if t is None:
-            continue
-        if not t.is_cuda:
-            raise ValueError("every operand must be a device tensor")
-        if dev is None:
-            dev = t.device
-        elif t.device != dev:
-            raise ValueError(f"operands on different devices: {dev} and {t.device}")
-    if dev is None or dev.index == torch.cuda.current_device():
+    dev = _device_index(*ts)
+    torch = _load_torch()
+    if dev < 0 or dev == torch.cuda.current_device():
         return _NO_SWITCH
     return torch.cuda.device(dev)
+
+
+def _launch(name: str, dev: int, stream, args) -> None:
+    """Call a launching entry point (its last argument, the stream, left out
+    of ``args``) on device ``dev``."""
+    torch = _torch
+    fn = _fast[name]
+    if dev == torch._C._cuda_getDevice():
+        rc = fn(*args, torch._C._cuda_getCurrentRawStream(dev) if stream is None else int(stream))
+    else:
+        with torch.cuda.device(dev):
+            rc = fn(*args, torch._C._cuda_getCurrentRawStream(dev) if stream is None
+                    else int(stream))
+    if rc != 0:
+        raise SgemmEmuError(rc, name)
+
+
+def _check_ints(*values) -> None:
+    """Every value must fit the C ABI's int (the plain entry points would take
+    2^32 + 8 as 8)."""
+    for v in values:
+        if not -(1 << 31) <= v < (1 << 31):
+            raise ctypes.ArgumentError(f"{v} does not fit the 32-bit int argument")
 
 
 def _check_shape(t, shape, name: str) -> None:
@@ -229,31 +278,30 @@ def _check_shape(t, shape, name: str) -> None:
 def _matrix_view(t, name: str):
     """(batch, rows, cols, ld, batch_stride) of a 2-D or 3-D FP32 tensor whose
     rows are contiguous."""
-    import torch
-
-    if t.dtype != torch.float32:
+    if t.dtype is not _load_torch().float32:
         raise TypeError(f"{name} must be float32, got {t.dtype}")
     if not t.is_cuda:
         raise ValueError(f"{name} must be a device tensor")
-    if t.dim() == 2:
-        rows, cols = t.shape
-        if cols > 1 and t.stride(1) != 1:
-            raise ValueError(f"{name} rows must be contiguous (stride 1 along the last dim)")
-        return None, rows, cols, t.stride(0) if rows > 1 else max(cols, 1), 0
-    if t.dim() != 3:
+    shape = t.shape
+    if len(shape) == 3:
+        b, rows, cols = shape
+        sb, ld, step = t.stride()
+    elif len(shape) == 2:
+        b = None
+        rows, cols = shape
+        ld, step = t.stride()
+    else:
         raise ValueError(f"{name} must be 2-D or 3-D")
-    b, rows, cols = t.shape
-    if cols > 1 and t.stride(2) != 1:
+    if step != 1 and cols > 1:
         raise ValueError(f"{name} rows must be contiguous (stride 1 along the last dim)")
-    ld = t.stride(1) if rows > 1 else max(cols, 1)
-    return b, rows, cols, ld, t.stride(0) if b > 1 else 0
+    if rows <= 1:
+        ld = cols if cols > 1 else 1
+    return b, rows, cols, ld, sb if b is not None and b > 1 else 0
 
 
 def _gemm_args(A, B, C):
     """(m, n, k, lda, ldb, ldc, batch, stride, C) of a batched product; C is
     allocated if None."""
-    import torch
-
     ba, m, k, lda, sa = _matrix_view(A, "A")
     bb, kb, n, ldb, sb = _matrix_view(B, "B")
     if kb != k:
@@ -262,11 +310,13 @@ def _gemm_args(A, B, C):
     if ba is not None and bb is not None and ba != bb:
         raise ValueError("batch sizes differ")
     if C is None:
-        C = torch.empty((batch, m, n), dtype=torch.float32, device=A.device)
-    bc, mc, nc, ldc, sc = _matrix_view(C if C.dim() == 3 else C.unsqueeze(0), "C")
-    if (mc, nc) != (m, n) or (bc if bc is not None else 1) != batch:
+        C = _torch.empty((batch, m, n), dtype=_torch.float32, device=A.device)
+    bc, mc, nc, ldc, sc = _matrix_view(C, "C")
+    if mc != m or nc != n or (bc if bc is not None else 1) != batch:
         raise ValueError("C has the wrong shape")
     st = Stride(sa, sb, sc if batch > 1 else 0)
+    if (m | n | k | lda | ldb | ldc | batch) >> 31:
+        _check_ints(m, n, k, lda, ldb, ldc, batch)
     return m, n, k, lda, ldb, ldc, batch, st, C
 
 
@@ -279,17 +329,17 @@ def sgemm_emu_batched(A, B, C=None, *, policy: Policy | None = None, stream=None
     taken from the tensors' strides.  Runs on the current torch stream unless
     ``stream`` (a hipStream_t handle) is given.  With ``policy`` the call goes
     to sgemm_emu_batched_ex."""
+    if _lib is None:
+        load()
     m, n, k, lda, ldb, ldc, batch, st, C = _gemm_args(A, B, C)
-    lib = load()
-    with _on_device(A, B, C):
-        if policy is None:
-            rc = lib.sgemm_emu_batched(m, n, k, _ptr(A), lda, _ptr(B), ldb, _ptr(C), ldc, batch,
-                                       st, _stream(stream))
-            _check(rc, "sgemm_emu_batched")
-        else:
-            rc = lib.sgemm_emu_batched_ex(m, n, k, _ptr(A), lda, _ptr(B), ldb, _ptr(C), ldc,
-                                          batch, st, ctypes.byref(policy), _stream(stream))
-            _check(rc, "sgemm_emu_batched_ex")
+    dev = _device_index(A, B, C)
+    if policy is None:
+        _launch("sgemm_emu_batched", dev, stream,
+                (m, n, k, A.data_ptr(), lda, B.data_ptr(), ldb, C.data_ptr(), ldc, batch, st))
+    else:
+        _launch("sgemm_emu_batched_ex", dev, stream,
+                (m, n, k, A.data_ptr(), lda, B.data_ptr(), ldb, C.data_ptr(), ldc, batch, st,
+                 ctypes.byref(policy)))
     return C
 
 
@@ -413,8 +463,6 @@ def sgemm_emu_batched_acc(A, B, C=None, D=None, *, op_a: int = OP_N, op_b: int =
     B is [k, n] or [n, k]; C and D are [m, n] (layout ROW_MAJOR) or [n, m]
     (COL_MAJOR).  C may be None (zero) or D itself (in place); D is
     allocated if None."""
-    import torch
-
     ba, ar, ac, lda, sa = _matrix_view(A, "A")
     bb, br, bc, ldb, sb = _matrix_view(B, "B")
     m, k = (ac, ar) if op_a == OP_T else (ar, ac)
@@ -428,7 +476,7 @@ def sgemm_emu_batched_acc(A, B, C=None, D=None, *, op_a: int = OP_N, op_b: int =
     stored = (n, m) if layout == COL_MAJOR else (m, n)
     if D is None:
         shape_d = (batch, *stored) if (ba is not None or bb is not None) else stored
-        D = torch.empty(shape_d, dtype=torch.float32, device=A.device)
+        D = _torch.empty(shape_d, dtype=_torch.float32, device=A.device)
     bd, dr, dc, ldd, sd = _matrix_view(D, "D")
     if (dr, dc) != stored or (bd or 1) != batch:
         raise ValueError("D has the wrong shape")
@@ -438,11 +486,15 @@ def sgemm_emu_batched_acc(A, B, C=None, D=None, *, op_a: int = OP_N, op_b: int =
         if (cr, ccol) != stored or (bcx is not None and bcx != batch):
             raise ValueError("C has the wrong shape")
     st = Stride4(sa, sb, sc, sd)
-    with _on_device(A, B, C, D):
-        rc = load().sgemm_emu_batched_acc(int(op_a), int(op_b), int(layout), m, n, k, _ptr(A),
-                                          lda, _ptr(B), ldb, _ptr(C), ldc, _ptr(D), ldd, batch,
-                                          st, int(shape), int(ec), _stream(stream))
-    _check(rc, "sgemm_emu_batched_acc")
+    op_a, op_b, layout, shape, ec = int(op_a), int(op_b), int(layout), int(shape), int(ec)
+    _check_ints(op_a, op_b, layout, shape, ec)
+    if (m | n | k | lda | ldb | ldc | ldd | batch) >> 31:
+        _check_ints(m, n, k, lda, ldb, ldc, ldd, batch)
+    if _lib is None:
+        load()
+    _launch("sgemm_emu_batched_acc", _device_index(A, B, C, D), stream,
+            (op_a, op_b, layout, m, n, k, A.data_ptr(), lda, B.data_ptr(), ldb,
+             None if C is None else C.data_ptr(), ldc, D.data_ptr(), ldd, batch, st, shape, ec))
     return D
 
 
@@ -452,8 +504,7 @@ def sgemm_emu_scan(X, Y=None, *, stream=None):
     X: float32 device tensor whose last dimension is the row and whose rows
     are evenly spaced (2-D with contiguous rows, or any contiguous tensor).
     Y: same shape (allocated if None); Y may be X (in place)."""
-    import torch
-
+    torch = _load_torch()
     if X.dtype != torch.float32 or not X.is_cuda:
         raise ValueError("X must be a float32 device tensor")
     if X.dim() == 2:
@@ -479,9 +530,11 @@ def sgemm_emu_scan(X, Y=None, *, stream=None):
         if not Y.is_contiguous():
             raise ValueError("Y must be contiguous (or 2-D with contiguous rows)")
         ldy = max(length, 1)
-    with _on_device(X, Y):
-        rc = load().sgemm_emu_scan(rows, length, _ptr(X), ldx, _ptr(Y), ldy, _stream(stream))
-    _check(rc, "sgemm_emu_scan")
+    _check_ints(length)
+    if _lib is None:
+        load()
+    _launch("sgemm_emu_scan", _device_index(X, Y), stream,
+            (rows, length, X.data_ptr(), ldx, Y.data_ptr(), ldy))
     return Y
 
 
@@ -489,8 +542,7 @@ def householder_emu_batched(u, B, C=None, *, mode: int = HOUSEHOLDER_RULE, strea
     """C[t] := (I - 2 u[t] u[t]^T) @ B[t]; u: [batch, 64], B: [batch, 64, ncols].
     mode: HOUSEHOLDER_RULE (reflector built in registers) or HOUSEHOLDER_LDS
     (baseline through LDS)."""
-    import torch
-
+    torch = _load_torch()
     if u.dtype != torch.float32 or not u.is_cuda or u.dim() != 2:
         raise ValueError("u must be a [batch, n] float32 device tensor")
     batch, n = u.shape
@@ -506,10 +558,12 @@ def householder_emu_batched(u, B, C=None, *, mode: int = HOUSEHOLDER_RULE, strea
         raise ValueError("a 2-D C holds one item")
     _, _, _, ldc, sc = _matrix_view(C, "C")
     su = u.stride(0) if batch > 1 else 0
-    with _on_device(u, B, C):
-        rc = load().householder_emu_batched_ex(n, _ptr(u), su, _ptr(B), ldb, sb, ncols, _ptr(C),
-                                               ldc, sc, batch, int(mode), _stream(stream))
-    _check(rc, "householder_emu_batched_ex")
+    mode = int(mode)
+    _check_ints(n, ldb, ncols, ldc, batch, mode)
+    if _lib is None:
+        load()
+    _launch("householder_emu_batched_ex", _device_index(u, B, C), stream,
+            (n, u.data_ptr(), su, B.data_ptr(), ldb, sb, ncols, C.data_ptr(), ldc, sc, batch, mode))
     return C
 
 
@@ -520,8 +574,7 @@ def householder_emu_batched_ex(u, B, C=None, *, mode: int, stream=None):
 def givens_emu_batched(i, j, c, s, B, C=None, *, mode: int = GIVENS_AUTO, stream=None):
     """C[t] := G(i, j, theta_t) @ B[t] with c[t] = cos theta_t, s[t] = sin theta_t;
     c, s: [batch] float32, B: [batch, n, ncols]."""
-    import torch
-
+    torch = _load_torch()
     for name, v in (("c", c), ("s", s)):
         if v.dtype != torch.float32 or not v.is_cuda or v.dim() != 1:
             raise ValueError(f"{name} must be a [batch] float32 device tensor")
@@ -538,11 +591,13 @@ def givens_emu_batched(i, j, c, s, B, C=None, *, mode: int = GIVENS_AUTO, stream
         raise ValueError("a 2-D C holds one item")
     _, _, _, ldc, sc = _matrix_view(C, "C")
     scs = c.stride(0) if batch > 1 else 0
-    with _on_device(c, s, B, C):
-        rc = load().givens_emu_batched(n, int(i), int(j), _ptr(c), _ptr(s), scs, _ptr(B), ldb,
-                                       sb, ncols, _ptr(C), ldc, sc, batch, int(mode),
-                                       _stream(stream))
-    _check(rc, "givens_emu_batched")
+    i, j, mode = int(i), int(j), int(mode)
+    _check_ints(n, i, j, ldb, ncols, ldc, batch, mode)
+    if _lib is None:
+        load()
+    _launch("givens_emu_batched", _device_index(c, s, B, C), stream,
+            (n, i, j, c.data_ptr(), s.data_ptr(), scs, B.data_ptr(), ldb, sb, ncols, C.data_ptr(),
+             ldc, sc, batch, mode))
     return C
 
 
