@@ -73,7 +73,7 @@ KERNEL_SOURCES = {  # the translation unit(s) of each kernel; shared headers are
     "householder64_lds_kernel": "rulebuilt.hip",
     "givens64_kernel": "rulebuilt.hip",
     "givens64_lds_kernel": "rulebuilt.hip",
-    "gemm_acc_kernel": "gemm_acc.hip",
+    "gemm_acc_kernel": ("gemm_acc.hip", "gemm_tile.hip"),
     "scan_kernel": "scan.hip",
 }
 

@@ -244,9 +244,11 @@ int sgemm_emu_block_order(int tiles_m, int tiles_n, int* tile_row, int* tile_col
  * Batched multiply-accumulate in emulated FP32 with transposable operands:
  *   for t in [0, batch):  D_t := op(A_t) . op(B_t) + C_t
  * the matrix-multiply-accumulate of a fragment API (Sec. 2.3.1) computed by
- * the method of Sec. 4.4 through the library's fragment interface
- * (mfmae/wmma_tcec.hpp; the kernel is written with its load_matrix_sync,
- * mma_sync and store_matrix_sync).  op(A) is m x k, op(B) is k x n.
+ * the method of Sec. 4.4: with error correction and 32x32x16 on LDS tiles
+ * shared by a workgroup's waves, otherwise through the library's fragment
+ * interface (mfmae/wmma_tcec.hpp; the kernel is written with its
+ * load_matrix_sync, mma_sync and store_matrix_sync).  op(A) is m x k, op(B)
+ * is k x n.
  *   op_a: SGEMM_EMU_OP_N  A_t is stored m x k row-major, lda >= max(1, k)
  *         SGEMM_EMU_OP_T  A_t is stored as its transpose, k x m row-major
  *                         (A column-major), lda >= max(1, m)

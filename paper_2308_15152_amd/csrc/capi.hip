@@ -255,15 +255,24 @@ tile::Shape tile_form(const sgemm_emu::GemmArgs& a, Kernel kern, int resolved, t
             family = tile::BIG;
             break;
         case K_REG:
-            // The register flow stays where it waits for HBM: a short k, or
-            // small products that leave much of their 64 x 64 tiles empty
-            // (140 x 670 x 1596 x 32 185 us against 231, 8192 x 32^3 17 / 25,
-            // 1000 x 100^3 27 / 36).  Elsewhere each of its waves loads and
+            // The register flow stays where it waits for HBM: a short k, small
+            // products that leave much of their 64 x 64 tiles empty, and, of
+            // those that fill the device, products within one of its tiles and
+            // up to 32 rows (three of its four waves then have nothing to do
+            // and leave): 140 x 670 x 1596 x 32 185 us against 231, 8192 x 32^3
+            // 17 / 25, 1000 x 100^3 27 / 36, 500 x 80 x 80 x 300 23 / 34, 500 x
+            // 32 x 512 x 256 58 / 72.  Elsewhere each of its waves loads and
             // splits its operands by itself (1100 x 1500 x 2000 73 us against
             // 34, 5 x 256 x 3963 x 4032 498 / 161, 51 x 3390 x 1043 x 88
-            // 410 / 362).
+            // 410 / 362, 71 x 40 x 1364 x 3200 370 / 281).
             if (a.k < 64) return tile::NONE;
-            if (a.k < 256 && tiles64 * 4096 * 10 > (int64_t)a.m * a.n * 13) return tile::NONE;
+            if (tiles64 * 4096 * 10 > (int64_t)a.m * a.n * 13) {
+                const int64_t tiles128 =
+                    (int64_t)((a.m + 127) / 128) * ((a.n + 127) / 128) * a.batch;
+                if (a.k < 256) return tile::NONE;
+                if (tiles128 >= 256 && (a.m <= 32 || (a.m <= 128 && a.n <= 128)))
+                    return tile::NONE;
+            }
             family = tile::REG;
             break;
         case K_BIG: {
@@ -314,13 +323,16 @@ int run_gemm(int m, int n, int k, const float* A, int lda, const float* B, int l
 // The shape of the tile kernel for an accumulate product, NONE for the kernel
 // written with the fragment interface (whose waves each load and split their
 // own operands: 4096^3 with B transposed 918 us against 379, 4 x 1252 x 168 x
-// 2434 with A transposed 169 / 31, 16384 x 64^3 203 to 233 / 186).
+// 2434 with A transposed 169 / 31, 16384 x 64^3 203 to 233 / 184, 1024 x 256^3
+// 266 to 410 / 209).
 tile::Shape acc_tile_form(const sgemm_emu::AccArgs& a, tile::Problem& p) {
-    // Both operands contiguous along m and n, whole 64 x 64 blocks and a short
-    // k: the fragment kernel moves whole lines too and waits for HBM without
-    // a barrier (4096 x 128^3: 190 us against 203; 1024 x 256^3: 266 / 243).
-    if (a.a_trans && !a.b_trans && a.m % 64 == 0 && a.n % 64 == 0 && a.k <= 128 && !a.cd_col &&
-        (int64_t)a.m * a.n <= 128 * 128)
+    // With A transposed, at most 32 columns (or 32 rows, B as stored) and enough
+    // tiles to fill the device the product waits for HBM, and half of every
+    // 64 x 64 tile is empty (A^T B: 64 x 4096 x 32 x 1024 206 us against 236, 500
+    // x 512 x 32 x 256 68 / 76; A^T B^T: 222 / 245, 71 / 72.  With fewer tiles,
+    // 20 x 1730 x 32 x 788, 69 / 31; 33 columns, 200 x 1000 x 33 x 500, 142 / 111).
+    if (a.a_trans && !a.cd_col && (a.n <= 32 || (!a.b_trans && a.m <= 32)) &&
+        (int64_t)((a.m + 63) / 64) * ((a.n + 63) / 64) * a.batch >= 2048)
         return tile::NONE;
     if (!a.cd_col)
         p = {a.m,  a.n,       a.k, a.A,   a.lda, a.sa, !a.a_trans, a.B,  a.ldb,

@@ -29,25 +29,27 @@ SGEMM_EMU_TILE_KERNEL(gemm_acc_kernel)
 // What a shape costs, in microseconds.  A workgroup takes `first` per chunk
 // when it has a CU to itself, and `chunk` for each of those that share one
 // (at most `fit` do), plus `ends` for filling the pipeline and storing C.
-// Fitted to the times of 100 products from 16 x 64^3 to 6000^2 x 960, odd
-// sizes among them: the shape chosen is 0.4% slower than the best one on
-// average, 13% at worst.  (Without the shapes with k groups 2%: the waves of
-// one group go through reads, products and split in step, and a second group
-// fills the gaps: 1024^3 16.4 -> 13.9 us, 2048^3 64 -> 55, 4 x 256 x 256 x 4096
-// 54 -> 32.)
+// Fitted to the times of 160 products from 16 x 64^3 to 6000^2 x 960, odd
+// sizes and transposed operands among them: the shape chosen is 0.9% slower
+// than the best one on average, 15% at worst.  (Where memory is what takes the
+// time the estimate is too low, but for every shape, and the one with the
+// least to do still is the best.)  (Without the shapes with k
+// groups 2%: the waves of one group go through reads, products and split in
+// step, and a second group fills the gaps: 1024^3 16.4 -> 13.9 us, 2048^3
+// 64 -> 55, 4 x 256 x 256 x 4096 54 -> 32.)
 struct Cost {
     int bm, bn, kg, fit;
     double first, chunk, ends;
 };
 constexpr Cost kCosts[NONE] = {
-    {64, 64, 1, 4, 0.74, 0.457, 0.86},  // T64
-    {64, 64, 2, 2, 0.26, 0.305, 2.57},  // T64_K2
-    {64, 64, 4, 1, 0.25, 0.253, 3.85},  // T64_K4
-    {128, 64, 1, 2, 0.32, 0.427, 4.27}, // T128x64
-    {128, 64, 2, 1, 0.39, 0.394, 3.66}, // T128x64_K2
-    {128, 128, 1, 2, 0.60, 0.597, 4.41},// T128
-    {128, 128, 2, 1, 0.54, 0.539, 4.57},// T128_K2
-    {128, 256, 1, 1, 0.93, 0.934, 5.00},// T128x256
+    {64, 64, 1, 4, 0.55, 0.357, 0.97},    // T64
+    {64, 64, 2, 2, 0.34, 0.298, 3.78},    // T64_K2
+    {64, 64, 4, 1, 0.29, 0.290, 5.07},    // T64_K4
+    {128, 64, 1, 2, 0.54, 0.420, 5.75},   // T128x64
+    {128, 64, 2, 1, 0.52, 0.515, 3.02},   // T128x64_K2
+    {128, 128, 1, 2, 0.67, 0.576, 4.37},  // T128
+    {128, 128, 2, 1, 0.58, 0.584, 5.68},  // T128_K2
+    {128, 256, 1, 1, 0.93, 0.933, 4.80},  // T128x256
 };
 constexpr double kCus = 256;
 
@@ -56,20 +58,16 @@ double cost(const Cost& c, const Problem& p) {
     const int chunks = (p.k + BK - 1) / BK;
     const double steps = (double)((chunks + c.kg - 1) / c.kg) * c.kg;
     const double here = __builtin_ceil(tiles / kCus);  // workgroups of the busiest CU
-    double t;
     if (here <= c.fit) {
         const double chunk = here * c.chunk > c.first ? here * c.chunk : c.first;
-        t = steps * chunk + c.ends * (1 + 0.5 * (here - 1));
-    } else {
-        const double n = tiles / kCus + (c.fit == 1 ? 0.5 : 0.25);
-        t = (n > c.fit ? n : c.fit) * (steps * c.chunk + c.ends * (c.fit == 1 ? 1.0 : 0.6));
+        return steps * chunk + c.ends * (1 + 0.5 * (here - 1));
     }
-    // the memory time, the same for every shape: 5.2 TB/s
-    const double bytes = 4.0 * p.batch *
-                         ((double)p.m * p.k + (double)p.k * p.n +
-                          (double)p.m * p.n * (p.C ? 2 : 1));
-    const double mem = bytes / 5.2e6;
-    return t > mem ? t : mem;
+    const double n = tiles / kCus + (c.fit == 1 ? 0.5 : 0.25);
+    // the ends overlap other workgroups' chunks, or, with one on the CU, wait
+    // for C besides (1024 x 256^3 with C: 128 x 128 209 us, 128 x 256 235;
+    // without 195 / 174)
+    const double ends = c.ends * (c.fit > 1 ? 0.6 : p.C ? 1.5 : 1.0);
+    return (n > c.fit ? n : c.fit) * (steps * c.chunk + ends);
 }
 
 bool fits(const Cost& c, const Problem& p) {
@@ -154,7 +152,7 @@ hipError_t launch_shape(const Problem& a, Shape shape, Family f, hipStream_t s) 
 
 }  // namespace
 
-Shape choose(const Problem& p, double* time) {
+Shape choose(const Problem& p) {
     const int lim = 1 << 30;  // row, column and k indices are formed in 32 bits
     if (p.m < 1 || p.n < 1 || p.k < 1 || p.m >= lim || p.n >= lim || p.k >= lim) return NONE;
     if ((!p.a_kc && p.m < 4) || (!p.b_kc && p.n < 4)) return NONE;
@@ -168,7 +166,6 @@ Shape choose(const Problem& p, double* time) {
             best_time = t;
         }
     }
-    if (time) *time = best_time;
     return best;
 }
 

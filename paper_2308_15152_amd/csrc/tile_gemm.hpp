@@ -396,19 +396,6 @@ __device__ __forceinline__ void run(const Params& p, unsigned char* smem) {
                 acc[tm][tn][e] = 0.0f;
                 cor[tm][tn][e] = 0.0f;
             }
-    // C starts the main sum
-    if (CF::ADD && p.C && kg == 0) {
-        const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
-            const_cast<float*>(p.C + it * p.sc + (int64_t)(m0 + wrow) * p.ldc + n0 + wcol), 0,
-            (int)kPastEnd, 0x00020000);
-        auto add = [&](int tm, int tn, int e, uint32_t v, int s) __attribute__((always_inline)) {
-            acc[tm][tn][e] =
-                __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rc, v, s, 0));
-        };
-        if (whole) outputs(p.ldc, Bool<false>{}, add);
-        else outputs(p.ldc, Bool<true>{}, add);
-    }
-
     // Chunks: the k tail, if there is one, then the whole chunks; group kg
     // takes chunks kg, kg + KG, ...
     const int tail = p.k % BK;
@@ -505,19 +492,60 @@ __device__ __forceinline__ void run(const Params& p, unsigned char* smem) {
             }
     }
 
-    // D = main + corr * 2^-11.  D is not read again here: where the tile's rows
-    // are whole 128-byte lines it is stored nontemporally (4096 x 128^3 158
-    // against 166 us, 1024 x 256^3 174 / 192).  Otherwise the pieces of a line
-    // meet in the L2 (8 x 1001 x 999 x 1003 64 against 56 us, 174 x 651 x 2213 x
-    // 128 611 / 488).
+    // main + C + corr * 2^-11, C in the registers the staged chunks have left.
+    // (C in the accumulators from the start spilled 50 registers per lane:
+    // 4096 x 128^3 with 128 x 128 tiles 225 us against 189, 1024 x 256^3
+    // 268 / 209.)  The rounding error of main + C joins the correction, so
+    // that the result is rounded once, as when C starts the main sum.
+    if (CF::ADD && p.C) {
+        __builtin_amdgcn_sched_barrier(0);  // not ahead of the groups' sums
+        const __amdgpu_buffer_rsrc_t rc = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float*>(p.C + it * p.sc + (int64_t)(m0 + wrow) * p.ldc + n0 + wcol), 0,
+            (int)kPastEnd, 0x00020000);
+        f32x16_t add[CF::TM][CF::TN];
+        auto get = [&](int tm, int tn, int e, uint32_t v, int s) __attribute__((always_inline)) {
+            add[tm][tn][e] =
+                __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rc, v, s, 0));
+        };
+        if (whole) outputs(p.ldc, Bool<false>{}, get);
+        else outputs(p.ldc, Bool<true>{}, get);
+#pragma unroll
+        for (int tm = 0; tm < CF::TM; ++tm)
+#pragma unroll
+            for (int tn = 0; tn < CF::TN; ++tn)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    // two-sum (Knuth): a + c = s + err exactly, except where
+                    // a step overflows
+                    const float a = acc[tm][tn][e], c = add[tm][tn][e];
+                    const float s = a + c, t = s - a;
+                    const float err = (a - (s - t)) + (c - t);
+                    acc[tm][tn][e] =
+                        s + __builtin_fmaf(cor[tm][tn][e], mfmae::tcec::kLoScaleInv,
+                                           __builtin_isfinite(err) ? err : 0.0f);
+                }
+    } else {
+#pragma unroll
+        for (int tm = 0; tm < CF::TM; ++tm)
+#pragma unroll
+            for (int tn = 0; tn < CF::TN; ++tn)
+#pragma unroll
+                for (int e = 0; e < 16; ++e)
+                    acc[tm][tn][e] =
+                        __builtin_fmaf(cor[tm][tn][e], mfmae::tcec::kLoScaleInv, acc[tm][tn][e]);
+    }
+
+    // D is not read again here: where the tile's rows are whole 128-byte lines
+    // it is stored nontemporally (4096 x 128^3 158 against 166 us, 1024 x 256^3
+    // 174 / 192).  Otherwise the pieces of a line meet in the L2 (8 x 1001 x 999
+    // x 1003 64 against 56 us, 174 x 651 x 2213 x 128 611 / 488).
     float* const Di = p.D + it * p.sd + (int64_t)(m0 + wrow) * p.ldd + n0 + wcol;
     const __amdgpu_buffer_rsrc_t rd =
         __builtin_amdgcn_make_buffer_rsrc(Di, 0, (int)kPastEnd, 0x00020000);
     const bool lines = ((uintptr_t)Di % 128 == 0) & (p.ldd % 32 == 0);
     auto put = [&](auto nontemporal) __attribute__((always_inline)) {
         return [&](int tm, int tn, int e, uint32_t v, int s) __attribute__((always_inline)) {
-            const float d =
-                __builtin_fmaf(cor[tm][tn][e], mfmae::tcec::kLoScaleInv, acc[tm][tn][e]);
+            const float d = acc[tm][tn][e];
             __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, d), rd, v, s,
                                                   decltype(nontemporal)::value ? kNontemporal : 0);
         };

@@ -36,9 +36,8 @@ enum Family { BIG, REG, GENERAL, ACC };
 
 // The shape expected to be the fastest for this product, NONE if no shape
 // takes it (sizes or leading dimensions out of range, or fewer than four
-// values along an operand's contiguous m or n).  *time: its estimated time in
-// microseconds on a device otherwise idle.
-Shape choose(const Problem& p, double* time = nullptr);
+// values along an operand's contiguous m or n).
+Shape choose(const Problem& p);
 
 hipError_t launch(const Problem& p, Shape shape, Family family, hipStream_t stream);
 

@@ -159,6 +159,33 @@ def test_accumulate(shape, ta, tb, col):
     gate(logical(D), ref0, k, f"tile acc, no C {shape}", max_gate=gate_applies(ref0))
 
 
+@pytest.mark.parametrize("shape", [(2, 65, 66, 40), (1, 129, 260, 300)])
+def test_addend_extremes(shape):
+    """C entries of any size: infinities (an additive mask) stay what they are,
+    the largest and lowest FP32 values and 1e30 absorb a product far below half
+    their ulp, NaN stays NaN, and every other output is as without them.  The
+    kernel written with the fragment interface gives the same on all of them."""
+    b, m, n, k = shape
+    g = synth.rng(14)
+    A, B = synth.uniform((b, m, k), g).to(device()), synth.uniform((b, k, n), g).to(device())
+    C = synth.uniform((b, m, n), g).to(device())
+    plain = pkg.sgemm_emu_batched_acc(A, B, C)
+    top = torch.finfo(torch.float32).max
+    values = [float("inf"), float("-inf"), top, -top, 1e30, -1e30, float("nan")]
+    Cx = C.clone()
+    marked = torch.zeros_like(C, dtype=torch.bool)
+    for i, v in enumerate(values):
+        Cx[:, i::11, (3 * i)::13] = v
+        marked[:, i::11, (3 * i)::13] = True
+    fragments = pkg.sgemm_emu_batched_acc(A, B, Cx, shape=pkg.SHAPE_16x16x32)
+    D = pkg.sgemm_emu_batched_acc(A, B, Cx)
+    assert torch.equal(D[~marked], plain[~marked])
+    for X in (D, fragments):
+        assert torch.equal(torch.nan_to_num(X[marked], nan=7.0),
+                           torch.nan_to_num(Cx[marked], nan=7.0))
+        assert torch.equal(torch.isnan(X), torch.isnan(Cx))
+
+
 def test_in_place_where_tiles_overlap():
     """Tiles moved back over their neighbours read and write only their own
     outputs: D += A B in place gives the same bits every time."""
