@@ -379,6 +379,9 @@ int givens_emu_batched(int n, int i, int j,
  * parts scanned by a wavefront each (three launches on the stream, Y holding
  * the parts' totals in between).  Any alignment, at the same speed.  Any
  * number of rows: more than 33,554,428 wavefronts take several launches.
+ * After a value the split does not represent (infinite, NaN, or 65520 and
+ * more in magnitude) its row is NaN to the end; so are the other outputs of
+ * its 32-value segment, except where a part ends with that value.
  * Errors: SGEMM_EMU_ERR_DIM, _LD (also when rows x ld runs past the end of
  * the address space), _NULL, _ALIAS, _HIP.
  */

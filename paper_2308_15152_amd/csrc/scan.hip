@@ -55,6 +55,9 @@ using FragA = mfmae::fragment<Shape32, Use::A, _Float16>;
 
 constexpr int kWaves = 4;
 constexpr int kBlock = 1024;  // values scanned at a time
+// Magnitudes from here on round to infinity as binary16: their split is
+// (infinity, NaN), and so is every sum it enters.
+constexpr float kSplitEnd = 65520.0f;
 // Block buffers per wave.  Two of them and four waves per SIMD (101 VGPRs)
 // against four and three (137): 131,072 rows of 2048 take 361 against 397 us
 // (5.9 TB/s), of 512 values 77 against 83, of 200 60 against 68.  With one
@@ -283,6 +286,7 @@ __global__ __launch_bounds__(64 * kWaves) void scan_total_kernel(ScanArgs p, int
     const float* x = p.X + q.row * p.ldx + q.first;
     constexpr int kAhead = 4;  // blocks in flight; past the end they read as zero
     f32x4 sum[4] = {};
+    float peak = 0.0f;
     for (int c = 0; c < q.count; c += kAhead * kBlock) {
         Raw r[kAhead];
 #pragma unroll
@@ -290,12 +294,19 @@ __global__ __launch_bounds__(64 * kWaves) void scan_total_kernel(ScanArgs p, int
 #pragma unroll
         for (int b = 0; b < kAhead; ++b)
 #pragma unroll
-            for (int i = 0; i < 4; ++i) sum[i] += r[b].v[i];
+            for (int i = 0; i < 4; ++i) {
+                sum[i] += r[b].v[i];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) peak = fmaxf(peak, fabsf(r[b].v[i][e]));
+            }
     }
     const f32x4 s = (sum[0] + sum[1]) + (sum[2] + sum[3]);
     float total = (s[0] + s[1]) + (s[2] + s[3]);
 #pragma unroll
     for (int d = 32; d > 0; d /= 2) total += __shfl_xor(total, d, 64);
+    // A value the split does not represent makes the rest of its row NaN, as
+    // in a scan of whole rows (a NaN is in the sum already).
+    if (__any(!(peak < kSplitEnd))) total = __builtin_nanf("");
     if ((threadIdx.x & 63) == 0) p.Y[q.row * p.ldy + q.first + q.count - 1] = total;
 }
 

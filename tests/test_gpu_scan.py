@@ -70,6 +70,32 @@ def test_rows_in_parts(shape, in_place):
     gate(to_np(Y), ref, _k_eff(length), f"scan {rows}x{length}", max_gate=False)
 
 
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan"), 65520.0, -1e30])
+@pytest.mark.parametrize("rows", [8, 600])
+def test_values_outside_the_split(rows, value):
+    """A value whose split is not finite makes its row NaN to the end, whether
+    the row is scanned whole (600 rows) or in parts (8 rows, whose totals are
+    plain FP32 sums); what lies before its 32-value segment stays as it was.
+    65519 is the largest magnitude on the other side, and stays finite."""
+    length = 20 * 1024 + 7
+    X = synth.uniform((rows, length), synth.rng(31))
+    Xx = X.clone()
+    at = [0, 100, 4095, 4096, 9000, length - 1]  # 4095: the last value of a part
+    for r, j in enumerate(at):
+        Xx[r, j] = value
+    Xx[len(at), 5000] = 65519.0
+    plain = to_np(pkg.sgemm_emu_scan(X.to(device())))
+    Y = pkg.sgemm_emu_scan(Xx.to(device()))
+    in_place = Xx.to(device())
+    pkg.sgemm_emu_scan(in_place, in_place)
+    for out in (to_np(Y), to_np(in_place)):
+        for r, j in enumerate(at):
+            assert np.isnan(out[r, j:]).all(), (r, j, int(np.isfinite(out[r, j:]).sum()))
+            assert np.array_equal(out[r, :j - j % 32], plain[r, :j - j % 32])
+        assert np.isfinite(out[len(at):]).all()
+        assert np.array_equal(out[len(at) + 1:], plain[len(at) + 1:])
+
+
 @pytest.mark.parametrize("length", [3000, 4096])
 def test_integer_exact_and_in_place(length):
     X = synth.integer_matrix((70, length), synth.rng(5), -1000, 1000)
