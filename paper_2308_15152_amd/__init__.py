@@ -311,7 +311,8 @@ def _gemm_args(A, B, C):
         raise ValueError("batch sizes differ")
     if C is None:
         C = _torch.empty((batch, m, n), dtype=_torch.float32, device=A.device)
-    bc, mc, nc, ldc, sc = _matrix_view(C, "C")
+    # one row may come as a vector
+    bc, mc, nc, ldc, sc = _matrix_view(C if len(C.shape) != 1 else C.unsqueeze(0), "C")
     if mc != m or nc != n or (bc if bc is not None else 1) != batch:
         raise ValueError("C has the wrong shape")
     st = Stride(sa, sb, sc if batch > 1 else 0)

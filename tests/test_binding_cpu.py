@@ -6,6 +6,7 @@ checked entry points, and the library's own validation answers through them
 import ctypes
 
 import pytest
+import torch
 
 import paper_2308_15152_amd as pkg
 
@@ -47,3 +48,35 @@ def test_out_of_range_integers_are_refused():
     for bad in ((1 << 31), -(1 << 31) - 1, (1 << 32) + 8):
         with pytest.raises(ctypes.ArgumentError):
             pkg._check_ints(4, bad)
+
+
+class _OnDevice:
+    """A host tensor that passes for a device tensor where only its type,
+    shape and strides are looked at."""
+
+    is_cuda = True
+
+    def __init__(self, t):
+        self.t = t
+
+    def __getattr__(self, name):
+        return getattr(self.t, name)
+
+    def unsqueeze(self, dim):
+        return _OnDevice(self.t.unsqueeze(dim))
+
+
+def test_output_forms_of_a_product():
+    """C may be 3-D, 2-D (one item) or, for one row, a contiguous vector;
+    anything else is refused."""
+    A, B = _OnDevice(torch.zeros(1, 8)), _OnDevice(torch.zeros(8, 5))
+    for C in (torch.zeros(5), torch.zeros(1, 5), torch.zeros(1, 1, 5)):
+        m, n, k, lda, ldb, ldc, batch, st, out = pkg._gemm_args(A, B, _OnDevice(C))
+        assert (m, n, k, batch, ldc, st.c) == (1, 5, 8, 1, 5, 0)
+    for C in (torch.zeros(4), torch.zeros(()), torch.zeros(2, 5), torch.zeros(10)[::2],
+              torch.zeros(1, 1, 1, 5)):
+        with pytest.raises(ValueError):
+            pkg._gemm_args(A, B, _OnDevice(C))
+    two = _OnDevice(torch.zeros(2, 8))
+    with pytest.raises(ValueError):
+        pkg._gemm_args(two, B, _OnDevice(torch.zeros(5)))
