@@ -64,8 +64,9 @@ SCAN_METRIC = "inclusive scan of FP32 rows, elements/s (batched)"
 TRAFFIC_FILE = os.path.join(ROOT, "profiles", "traffic.json")
 
 
-KERNEL_SOURCES = {  # the translation unit(s) of each kernel; shared headers are added
-    "bgemm_reg_kernel": ("bgemm_reg.hip", "gemm_tile.hip"),
+KERNEL_SOURCES = {  # the translation unit of each kernel; shared headers are added
+    "gemm_tile_kernel": "gemm_tile.hip",
+    "bgemm_reg_kernel": "bgemm_reg.hip",
     "bgemm_big_kernel": "bgemm_big.hip",
     "bgemm_big_stream_kernel": "bgemm_big.hip",
     "bgemm_emu_kernel": "bgemm.hip",
@@ -73,7 +74,7 @@ KERNEL_SOURCES = {  # the translation unit(s) of each kernel; shared headers are
     "householder64_lds_kernel": "rulebuilt.hip",
     "givens64_kernel": "rulebuilt.hip",
     "givens64_lds_kernel": "rulebuilt.hip",
-    "gemm_acc_kernel": ("gemm_acc.hip", "gemm_tile.hip"),
+    "gemm_acc_kernel": "gemm_acc.hip",
     "scan_kernel": "scan.hip",
 }
 
@@ -88,13 +89,11 @@ def _code_text(text: str) -> str:
 
 def kernel_source_hash(kernel: str) -> str:
     """SHA-256 over the code (comments and layout ignored) a kernel is built
-    from: its translation units and every header they include (transitively,
+    from: its translation unit and every header it includes (transitively,
     quoted includes found in the package's csrc/ or in include/)."""
     csrc = os.path.join(ROOT, "paper_2308_15152_amd", "csrc")
     inc = os.path.join(ROOT, "include")
-    units = KERNEL_SOURCES[kernel]
-    units = (units,) if isinstance(units, str) else units
-    seen, todo = set(), [os.path.join(csrc, u) for u in units]
+    seen, todo = set(), [os.path.join(csrc, KERNEL_SOURCES[kernel])]
     while todo:
         f = todo.pop()
         if f in seen:
@@ -633,17 +632,19 @@ def bench_workload(args, name: str, cpu: bool) -> dict:
         roof = {"bound": "hbm", "achieved": bytes_alg / (ms_step * 1e-3) / 1e9,
                 "peak": PEAK_HBM_GBS, "unit": "GB/s"}
     roof["frac"] = roof["achieved"] / roof["peak"]
-    resolved, kernel = None, ("householder64_lds_kernel" if hh_mode == pkg.HOUSEHOLDER_LDS
-                              else "householder64_kernel")
+    resolved, form = None, None
+    kernel = ("householder64_lds_kernel" if hh_mode == pkg.HOUSEHOLDER_LDS
+              else "householder64_kernel")
     if w.kind == "givens":
         kernel = "givens64_lds_kernel" if givens_mode == pkg.GIVENS_LDS else "givens64_kernel"
     elif w.kind == "gemm_acc":
-        kernel = "gemm_acc_kernel"
+        kernel, form = pkg.sgemm_emu_acc_launch_form(*dev_inputs, C, op_a=pkg.OP_T)
     elif w.kind == "scan":
         kernel = "scan_kernel"
     elif w.kind == "gemm":
         A, B = dev_inputs
-        resolved, kernel = pkg.sgemm_emu_resolve_policy(A, B, C, policy=policy)
+        resolved, _ = pkg.sgemm_emu_resolve_policy(A, B, C, policy=policy)
+        kernel, form = pkg.sgemm_emu_launch_form(A, B, C, policy=policy)
     roof["kernel"] = kernel
     tkey = w.name
     if w.kind == "givens" and args.givens_mode != "auto":
@@ -674,6 +675,8 @@ def bench_workload(args, name: str, cpu: bool) -> dict:
                    "policy": None if resolved is None else
                    {"flow": resolved.flow, "ec": resolved.ec, "tile": resolved.tile,
                     "requested": "auto" if policy is None else "explicit"},
+                   **({"tile": {"rows": form[0], "cols": form[1], "k_groups": form[2]}}
+                      if form else {}),
                    **({"givens": {"plane": list(w.plane), "mode": args.givens_mode}}
                       if w.kind == "givens" else {}),
                    **({"householder_mode": args.householder_mode}

@@ -104,14 +104,15 @@ int sgemm_emu_batched(int m, int n, int k,
  *                         vector loads, below 2^35 multiply-adds) 64x64.
  *                         Otherwise SPLIT on the general kernel.
  *                         With tile AUTO too and error correction on, the
- *                         product then runs on the tile form of the kernel
- *                         so found wherever that is the faster one: the
- *                         split flow on workgroup tiles of 64x64 to 128x256
- *                         chosen by the product's size, whose last tiles
- *                         overlap their neighbours instead of running past
- *                         the matrix, k shared among groups of waves where
- *                         the tiles are few, any alignment.  A named flow or
- *                         tile runs exactly as named.
+ *                         product then runs on the tile kernel wherever
+ *                         that is faster than the kernel so found
+ *                         (sgemm_emu_launch_form says which): the split flow
+ *                         on workgroup tiles of 64x64 to 128x256 chosen by
+ *                         the product's size, whose last tiles overlap their
+ *                         neighbours instead of running past the matrix, k
+ *                         shared among groups of waves where the tiles are
+ *                         few, any alignment.  A named flow or tile runs
+ *                         exactly as named.
  *   SGEMM_EMU_FLOW_SPLIT  FP32 tiles are split in registers between the
  *                         global load and the LDS store; LDS holds hi and lo
  *                         (the same 4 bytes per element as FP32) and the
@@ -175,17 +176,16 @@ int sgemm_emu_batched_ex(int m, int n, int k,
                          const sgemm_emu_policy_t* policy,
                          hipStream_t stream);
 
-/* The policy sgemm_emu_batched_ex would run for these arguments, with AUTO
- * flow and tile replaced by the library's choice (ec is copied), and, if
- * `kernel` is not NULL, the name of the kernel it would launch (a static
- * string; "" for an empty problem).  A host-only query: no HIP call,
- * nothing is enqueued.  Same validation and errors as sgemm_emu_batched_ex,
- * plus SGEMM_EMU_ERR_NULL for a NULL out; for an empty problem (nothing
- * would run) out receives the policy unresolved.  The answer is the policy
- * and kernel the product's sizes and alignment resolve to; an automatic call
- * may run that kernel in its tile form (see FLOW_AUTO), with a workgroup tile
- * of its own, and "bgemm_big_kernel+bgemm_reg_kernel" (large products of
- * nearly whole tiles) is one launch of it.
+/* The policy these arguments resolve to: AUTO flow and tile replaced by the
+ * library's choice by size and alignment (ec is copied), and, if `kernel` is
+ * not NULL, the name of the kernel that carries that policy (a static string;
+ * "" for an empty problem; "bgemm_big_kernel+bgemm_reg_kernel" for large
+ * products of nearly whole tiles).  A named policy runs on that kernel; an
+ * automatic call may run on the tile kernel instead (see FLOW_AUTO), which no
+ * policy names: sgemm_emu_launch_form reports what runs.  A host-only query:
+ * no HIP call, nothing is enqueued.  Same validation and errors as
+ * sgemm_emu_batched_ex, plus SGEMM_EMU_ERR_NULL for a NULL out; for an empty
+ * problem (nothing would run) out receives the policy unresolved.
  * With error correction, the split flow with tile 128x128, 256x128 or
  * 128x256, and the direct and staged flows with tile 128x128, run a
  * pipelined full-tile kernel when m and n are multiples of the tile, k is a
@@ -206,6 +206,20 @@ int sgemm_emu_resolve_policy(int m, int n, int k,
                              const sgemm_emu_policy_t* policy,
                              sgemm_emu_policy_t* out,
                              const char** kernel);
+
+/* What sgemm_emu_batched_ex launches for these arguments: the kernel's name
+ * (static; "gemm_tile_kernel" for the tile kernel, "" for an empty problem)
+ * and, in form[0..2], the rows and columns of its workgroup tile and the
+ * number of wave groups that share the tile's k (0, 0, 0 if empty).  kernel
+ * or form may be NULL.  A host-only query with the validation and errors of
+ * sgemm_emu_batched_ex. */
+int sgemm_emu_launch_form(int m, int n, int k,
+                          const float* A, int lda,
+                          const float* B, int ldb,
+                          float* C, int ldc,
+                          int batch, sgemm_emu_stride_t stride,
+                          const sgemm_emu_policy_t* policy,
+                          const char** kernel, int* form);
 
 /*
  * Work distribution of the GEMM kernels, computed on the host by the same
@@ -244,10 +258,11 @@ int sgemm_emu_block_order(int tiles_m, int tiles_n, int* tile_row, int* tile_col
  * Batched multiply-accumulate in emulated FP32 with transposable operands:
  *   for t in [0, batch):  D_t := op(A_t) . op(B_t) + C_t
  * the matrix-multiply-accumulate of a fragment API (Sec. 2.3.1) computed by
- * the method of Sec. 4.4: with error correction and 32x32x16 on LDS tiles
- * shared by a workgroup's waves, otherwise through the library's fragment
- * interface (mfmae/wmma_tcec.hpp; the kernel is written with its
- * load_matrix_sync, mma_sync and store_matrix_sync).  op(A) is m x k, op(B)
+ * the method of Sec. 4.4: with error correction and 32x32x16 mostly on LDS
+ * tiles shared by a workgroup's waves (sgemm_emu_acc_launch_form says which),
+ * otherwise through the library's fragment interface (mfmae/wmma_tcec.hpp;
+ * the kernel is written with its load_matrix_sync, mma_sync and
+ * store_matrix_sync).  op(A) is m x k, op(B)
  * is k x n.
  *   op_a: SGEMM_EMU_OP_N  A_t is stored m x k row-major, lda >= max(1, k)
  *         SGEMM_EMU_OP_T  A_t is stored as its transpose, k x m row-major
@@ -289,6 +304,19 @@ int sgemm_emu_batched_acc(int op_a, int op_b, int layout_cd,
                           float* D, int ldd,
                           int batch, sgemm_emu_stride4_t stride,
                           int shape, int ec, hipStream_t stream);
+
+/* What sgemm_emu_batched_acc launches for these arguments, as
+ * sgemm_emu_launch_form reports it ("gemm_tile_kernel", or "gemm_acc_kernel"
+ * with the tile of one wave). */
+int sgemm_emu_acc_launch_form(int op_a, int op_b, int layout_cd,
+                              int m, int n, int k,
+                              const float* A, int lda,
+                              const float* B, int ldb,
+                              const float* C, int ldc,
+                              float* D, int ldd,
+                              int batch, sgemm_emu_stride4_t stride,
+                              int shape, int ec,
+                              const char** kernel, int* form);
 
 /*
  * Batched Householder application with the reflector built in registers

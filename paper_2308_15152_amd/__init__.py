@@ -20,6 +20,7 @@ import os
 __all__ = [
     "SgemmEmuError", "lib_path", "load",
     "sgemm_emu_batched", "sgemm_emu_batched_ex", "sgemm_emu_resolve_policy",
+    "sgemm_emu_launch_form", "sgemm_emu_acc_launch_form",
     "sgemm_emu_batched_acc", "sgemm_emu_scan",
     "householder_emu_batched", "householder_emu_batched_ex", "givens_emu_batched",
     "sgemm_emu_split", "mfmae_num_elements", "mfmae_map", "mfmae_foreach", "mfmae_mma_probe",
@@ -51,6 +52,7 @@ ROW_MAJOR, COL_MAJOR = 0, 1
 # Every symbol declared in include/sgemm_emu.h.
 EXPORTED_SYMBOLS = (
     "sgemm_emu_batched", "sgemm_emu_batched_ex", "sgemm_emu_resolve_policy",
+    "sgemm_emu_launch_form", "sgemm_emu_acc_launch_form",
     "sgemm_emu_batched_acc", "sgemm_emu_scan",
     "householder_emu_batched", "householder_emu_batched_ex", "givens_emu_batched",
     "sgemm_emu_split", "mfmae_num_elements", "mfmae_map", "mfmae_foreach", "mfmae_mma_probe",
@@ -139,6 +141,12 @@ def load():
         "sgemm_emu_resolve_policy": ([i32, i32, i32, P, i32, P, i32, P, i32, i32, Stride,
                                       ctypes.POINTER(Policy), ctypes.POINTER(Policy),
                                       ctypes.POINTER(ctypes.c_char_p)], i32),
+        "sgemm_emu_launch_form": ([i32, i32, i32, P, i32, P, i32, P, i32, i32, Stride,
+                                   ctypes.POINTER(Policy), ctypes.POINTER(ctypes.c_char_p), ip],
+                                  i32),
+        "sgemm_emu_acc_launch_form": ([i32, i32, i32, i32, i32, i32, P, i32, P, i32, P, i32, P,
+                                       i32, i32, Stride4, i32, i32,
+                                       ctypes.POINTER(ctypes.c_char_p), ip], i32),
         "sgemm_emu_batched_acc": ([i32, i32, i32, i32, i32, i32, P, i32, P, i32, P, i32, P, i32,
                                    i32, Stride4, i32, i32, P], i32),
         "sgemm_emu_scan": ([i64, i32, P, i64, P, i64, P], i32),
@@ -345,8 +353,10 @@ def sgemm_emu_batched(A, B, C=None, *, policy: Policy | None = None, stream=None
 
 
 def sgemm_emu_resolve_policy(A, B, C, *, policy: Policy | None = None):
-    """(policy, kernel name) the library would run for this product, with
-    AUTO flow and tile resolved (a host-side query; nothing is launched)."""
+    """(policy, kernel name) this product resolves to, with AUTO flow and tile
+    replaced by the library's choice (a host-side query; nothing is launched).
+    A named policy runs on that kernel; an automatic call may run on the tile
+    kernel instead, which sgemm_emu_launch_form reports."""
     m, n, k, lda, ldb, ldc, batch, st, C = _gemm_args(A, B, C)
     out = Policy()
     kern = ctypes.c_char_p()
@@ -356,6 +366,19 @@ def sgemm_emu_resolve_policy(A, B, C, *, policy: Policy | None = None):
                                          ctypes.byref(kern))
     _check(rc, "sgemm_emu_resolve_policy")
     return out, (kern.value or b"").decode()
+
+
+def sgemm_emu_launch_form(A, B, C, *, policy: Policy | None = None):
+    """(kernel name, (rows, cols, k groups)) that ``sgemm_emu_batched`` launches
+    for this product: its workgroup tile and the wave groups that share the
+    tile's k (a host-side query; nothing is launched)."""
+    m, n, k, lda, ldb, ldc, batch, st, C = _gemm_args(A, B, C)
+    kern, form = ctypes.c_char_p(), (ctypes.c_int * 3)()
+    rc = load().sgemm_emu_launch_form(m, n, k, _ptr(A), lda, _ptr(B), ldb, _ptr(C), ldc, batch, st,
+                                      None if policy is None else ctypes.byref(policy),
+                                      ctypes.byref(kern), form)
+    _check(rc, "sgemm_emu_launch_form")
+    return (kern.value or b"").decode(), tuple(form)
 
 
 def sgemm_emu_xcd_order(grid: int):
@@ -454,15 +477,8 @@ def sgemm_emu_batched_ex(A, B, C=None, *, policy: Policy, stream=None):
     return sgemm_emu_batched(A, B, C, policy=policy, stream=stream)
 
 
-def sgemm_emu_batched_acc(A, B, C=None, D=None, *, op_a: int = OP_N, op_b: int = OP_N,
-                          layout: int = ROW_MAJOR, shape: int = SHAPE_32x32x16, ec: int = 1,
-                          stream=None):
-    """D := op(A) @ op(B) + C per batch item.
-
-    A, B, C, D are 2-D or 3-D float32 device tensors with contiguous rows,
-    given in their stored form: A is [m, k] (op_a OP_N) or [k, m] (OP_T),
-    B is [k, n] or [n, k]; C and D are [m, n] (layout ROW_MAJOR) or [n, m]
-    (COL_MAJOR).  C may be None (zero) or D itself (in place); D is
+def _acc_args(A, B, C, D, op_a, op_b, layout, shape, ec):
+    """(D, the arguments of sgemm_emu_batched_acc but the stream); D is
     allocated if None."""
     ba, ar, ac, lda, sa = _matrix_view(A, "A")
     bb, br, bc, ldb, sb = _matrix_view(B, "B")
@@ -486,17 +502,41 @@ def sgemm_emu_batched_acc(A, B, C=None, D=None, *, op_a: int = OP_N, op_b: int =
         bcx, cr, ccol, ldc, sc = _matrix_view(C, "C")
         if (cr, ccol) != stored or (bcx is not None and bcx != batch):
             raise ValueError("C has the wrong shape")
-    st = Stride4(sa, sb, sc, sd)
     op_a, op_b, layout, shape, ec = int(op_a), int(op_b), int(layout), int(shape), int(ec)
     _check_ints(op_a, op_b, layout, shape, ec)
     if (m | n | k | lda | ldb | ldc | ldd | batch) >> 31:
         _check_ints(m, n, k, lda, ldb, ldc, ldd, batch)
+    return D, (op_a, op_b, layout, m, n, k, A.data_ptr(), lda, B.data_ptr(), ldb,
+               None if C is None else C.data_ptr(), ldc, D.data_ptr(), ldd, batch,
+               Stride4(sa, sb, sc, sd), shape, ec)
+
+
+def sgemm_emu_batched_acc(A, B, C=None, D=None, *, op_a: int = OP_N, op_b: int = OP_N,
+                          layout: int = ROW_MAJOR, shape: int = SHAPE_32x32x16, ec: int = 1,
+                          stream=None):
+    """D := op(A) @ op(B) + C per batch item.
+
+    A, B, C, D are 2-D or 3-D float32 device tensors with contiguous rows,
+    given in their stored form: A is [m, k] (op_a OP_N) or [k, m] (OP_T),
+    B is [k, n] or [n, k]; C and D are [m, n] (layout ROW_MAJOR) or [n, m]
+    (COL_MAJOR).  C may be None (zero) or D itself (in place); D is
+    allocated if None."""
     if _lib is None:
         load()
-    _launch("sgemm_emu_batched_acc", _device_index(A, B, C, D), stream,
-            (op_a, op_b, layout, m, n, k, A.data_ptr(), lda, B.data_ptr(), ldb,
-             None if C is None else C.data_ptr(), ldc, D.data_ptr(), ldd, batch, st, shape, ec))
+    D, args = _acc_args(A, B, C, D, op_a, op_b, layout, shape, ec)
+    _launch("sgemm_emu_batched_acc", _device_index(A, B, C, D), stream, args)
     return D
+
+
+def sgemm_emu_acc_launch_form(A, B, C=None, D=None, *, op_a: int = OP_N, op_b: int = OP_N,
+                              layout: int = ROW_MAJOR, shape: int = SHAPE_32x32x16, ec: int = 1):
+    """(kernel name, (rows, cols, k groups)) that ``sgemm_emu_batched_acc``
+    launches for these arguments (a host-side query; nothing is launched)."""
+    _, args = _acc_args(A, B, C, D, op_a, op_b, layout, shape, ec)
+    kern, form = ctypes.c_char_p(), (ctypes.c_int * 3)()
+    _check(load().sgemm_emu_acc_launch_form(*args, ctypes.byref(kern), form),
+           "sgemm_emu_acc_launch_form")
+    return (kern.value or b"").decode(), tuple(form)
 
 
 def sgemm_emu_scan(X, Y=None, *, stream=None):

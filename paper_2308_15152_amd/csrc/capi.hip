@@ -110,18 +110,24 @@ int check_gemm(int m, int n, int k, const float* A, int lda, const float* B, int
 // run).  K_TILED: a large product whose whole tiles cover nearly all of C.
 enum Kernel { K_NONE, K_REG, K_BIG, K_LDS, K_TILED };
 
-const char* kernel_name(Kernel k) {
+const char* kernel_name(const sgemm_emu::GemmArgs& a, Kernel k, int tile, int flow) {
     switch (k) {
         case K_REG: return "bgemm_reg_kernel";
-        case K_BIG: return "bgemm_big_kernel";
+        case K_BIG:
+            return sgemm_emu::big_streams(a, tile, flow) ? "bgemm_big_stream_kernel"
+                                                         : "bgemm_big_kernel";
         case K_LDS: return "bgemm_emu_kernel";
         case K_TILED: return "bgemm_big_kernel+bgemm_reg_kernel";
         default: return "";
     }
 }
 
-int tile_rows(int tile) { return tile == SGEMM_EMU_TILE_256x128 ? 256 : 128; }
-int tile_cols(int tile) { return tile == SGEMM_EMU_TILE_128x256 ? 256 : 128; }
+int tile_rows(int tile) {
+    return tile == SGEMM_EMU_TILE_256x128 ? 256 : tile == SGEMM_EMU_TILE_64x64 ? 64 : 128;
+}
+int tile_cols(int tile) {
+    return tile == SGEMM_EMU_TILE_128x256 ? 256 : tile == SGEMM_EMU_TILE_64x64 ? 64 : 128;
+}
 
 // Interior of whole tiles and whole 32-deep k chunks.
 struct Interior {
@@ -237,8 +243,7 @@ namespace tile = sgemm_emu::tile;
 
 // The shape of the tile kernel an automatic call takes in place of the kernel
 // it resolves to, NONE to run that kernel itself.
-tile::Shape tile_form(const sgemm_emu::GemmArgs& a, Kernel kern, int resolved, tile::Problem& p,
-                      tile::Family& family) {
+tile::Shape tile_form(const sgemm_emu::GemmArgs& a, Kernel kern, int resolved, tile::Problem& p) {
     p = {a.m,  a.n,   a.k,  a.A, a.lda, a.sa,  true,  a.B,  a.ldb,
          a.sb, false, nullptr, 0,   0,     a.C, a.ldc, a.sc, a.batch};
     const int64_t tiles64 = (int64_t)((a.m + 63) / 64) * ((a.n + 63) / 64);
@@ -246,13 +251,11 @@ tile::Shape tile_form(const sgemm_emu::GemmArgs& a, Kernel kern, int resolved, t
         case K_LDS:
             // unaligned rows: the general kernel loads single elements
             // (8 x 1001 x 999 x 1003 129 us against 57, 642 x 56 x 3582 312 / 34)
-            family = tile::GENERAL;
             break;
         case K_TILED:
             // interior and edges in one launch, whatever the alignment (8000^3
             // in three launches 3.39 ms against 2.83, 6000 x 6000 x 960 282 us
             // / 219, 2 x 2600 x 2600 x 2560 351 / 219)
-            family = tile::BIG;
             break;
         case K_REG:
             // The register flow stays where it waits for HBM: a short k, small
@@ -273,7 +276,6 @@ tile::Shape tile_form(const sgemm_emu::GemmArgs& a, Kernel kern, int resolved, t
                 if (tiles128 >= 256 && (a.m <= 32 || (a.m <= 128 && a.n <= 128)))
                     return tile::NONE;
             }
-            family = tile::REG;
             break;
         case K_BIG: {
             // Up to two rounds of full tiles: smaller ones, or waves that
@@ -285,7 +287,6 @@ tile::Shape tile_form(const sgemm_emu::GemmArgs& a, Kernel kern, int resolved, t
             const int64_t tiles = (int64_t)(a.m / tile_rows(resolved)) * (a.n / tile_cols(resolved)) *
                                   a.batch;
             if (tiles > 512) return tile::NONE;
-            family = tile::BIG;
             break;
         }
         default: return tile::NONE;
@@ -293,32 +294,61 @@ tile::Shape tile_form(const sgemm_emu::GemmArgs& a, Kernel kern, int resolved, t
     return tile::choose(p);
 }
 
+// What a call runs: the kernel it resolves to, or the tile kernel with `shape`.
+struct GemmLaunch {
+    sgemm_emu::GemmArgs a;
+    Kernel kern;
+    int flow, tile;
+    tile::Shape shape;
+    tile::Problem p;
+};
+
+int resolve_launch(int m, int n, int k, const float* A, int lda, const float* B, int ldb, float* C,
+                   int ldc, int batch, sgemm_emu_stride_t st, int flow, int ec, int tile,
+                   GemmLaunch& l) {
+    const bool automatic = flow == SGEMM_EMU_FLOW_AUTO && tile == SGEMM_EMU_TILE_AUTO && ec == 1;
+    int rc = resolve_gemm(m, n, k, A, lda, B, ldb, C, ldc, batch, st, flow, ec, tile, l.a, l.kern);
+    if (rc != SGEMM_EMU_OK) return rc;
+    l.shape = automatic && l.kern != K_NONE ? tile_form(l.a, l.kern, tile, l.p) : tile::NONE;
+    if (l.kern == K_TILED && l.shape == tile::NONE) {  // C rows too far apart for the tile kernel
+        l.kern = K_REG;
+        flow = SGEMM_EMU_FLOW_REG;
+        tile = SGEMM_EMU_TILE_64x64;
+    }
+    l.flow = flow;
+    l.tile = tile;
+    return SGEMM_EMU_OK;
+}
+
 int run_gemm(int m, int n, int k, const float* A, int lda, const float* B, int ldb, float* C,
              int ldc, int batch, sgemm_emu_stride_t st, int flow, int ec, int tile,
              hipStream_t stream) {
-    sgemm_emu::GemmArgs a;
-    Kernel kern;
-    const bool automatic = flow == SGEMM_EMU_FLOW_AUTO && tile == SGEMM_EMU_TILE_AUTO && ec == 1;
-    int rc = resolve_gemm(m, n, k, A, lda, B, ldb, C, ldc, batch, st, flow, ec, tile, a, kern);
-    if (rc != SGEMM_EMU_OK || kern == K_NONE) return rc;
+    GemmLaunch l;
+    int rc = resolve_launch(m, n, k, A, lda, B, ldb, C, ldc, batch, st, flow, ec, tile, l);
+    if (rc != SGEMM_EMU_OK || l.kern == K_NONE) return rc;
     hipError_t e;
-    tile::Problem p;
-    tile::Family family;
-    const tile::Shape shape = automatic ? tile_form(a, kern, tile, p, family) : tile::NONE;
-    if (shape != tile::NONE) {
-        e = tile::launch(p, shape, family, stream);
+    if (l.shape != tile::NONE) {
+        e = tile::launch(l.p, l.shape, stream);
     } else {
-        switch (kern) {
-            case K_REG: e = sgemm_emu::launch_gemm_reg(a, tile, ec != 0, stream); break;
-            case K_BIG: e = sgemm_emu::launch_gemm_big(a, tile, flow, ec != 0, stream); break;
-            case K_TILED:  // C rows too far apart for the tile kernel
-                e = sgemm_emu::launch_gemm_reg(a, SGEMM_EMU_TILE_64x64, true, stream);
-                break;
-            default: e = sgemm_emu::launch_gemm(a, tile, flow, ec != 0, stream); break;
+        switch (l.kern) {
+            case K_REG: e = sgemm_emu::launch_gemm_reg(l.a, l.tile, ec != 0, stream); break;
+            case K_BIG: e = sgemm_emu::launch_gemm_big(l.a, l.tile, l.flow, ec != 0, stream); break;
+            default: e = sgemm_emu::launch_gemm(l.a, l.tile, l.flow, ec != 0, stream); break;
         }
     }
     return e == hipSuccess ? SGEMM_EMU_OK : hip_fail(e);
 }
+
+void set_form(const char* name, tile::Form f, const char** kernel, int* form) {
+    if (kernel) *kernel = name;
+    if (form) {
+        form[0] = f.rows;
+        form[1] = f.cols;
+        form[2] = f.groups;
+    }
+}
+
+constexpr const char* kTileKernel = "gemm_tile_kernel";
 
 // The shape of the tile kernel for an accumulate product, NONE for the kernel
 // written with the fragment interface (whose waves each load and split their
@@ -341,6 +371,85 @@ tile::Shape acc_tile_form(const sgemm_emu::AccArgs& a, tile::Problem& p) {
         p = {a.n,  a.m,        a.k, a.B,   a.ldb, a.sb, a.b_trans, a.A,  a.lda,
              a.sa, !a.a_trans, a.C, a.ldc, a.sc,  a.D,  a.ldd,     a.sd, a.batch};
     return tile::choose(p);
+}
+
+// What an accumulate call runs: the tile kernel with `shape`, or (NONE) the
+// kernel written with the fragment interface.
+struct AccLaunch {
+    sgemm_emu::AccArgs a;
+    tile::Shape shape;
+    tile::Problem p;
+};
+
+// Validate and fill the launch; `empty`: nothing to run.
+int resolve_acc(int op_a, int op_b, int layout_cd, int m, int n, int k, const float* A, int lda,
+                const float* B, int ldb, const float* C, int ldc, float* D, int ldd, int batch,
+                sgemm_emu_stride4_t stride, int shape, int ec, AccLaunch& l, bool& empty) {
+    empty = true;
+    if ((op_a != SGEMM_EMU_OP_N && op_a != SGEMM_EMU_OP_T) ||
+        (op_b != SGEMM_EMU_OP_N && op_b != SGEMM_EMU_OP_T) ||
+        (layout_cd != SGEMM_EMU_ROW_MAJOR && layout_cd != SGEMM_EMU_COL_MAJOR) ||
+        (shape != MFMAE_SHAPE_16x16x32 && shape != MFMAE_SHAPE_32x32x16) || (ec != 0 && ec != 1))
+        return SGEMM_EMU_ERR_POLICY;
+    if (m < 0 || n < 0 || k < 0 || batch < 0) return SGEMM_EMU_ERR_DIM;
+    const bool at = op_a == SGEMM_EMU_OP_T, bt = op_b == SGEMM_EMU_OP_T;
+    const bool cdc = layout_cd == SGEMM_EMU_COL_MAJOR;
+    // stored shapes (rows x cols, row-major with the given ld)
+    const int ar = at ? k : m, ac = at ? m : k;
+    const int br = bt ? n : k, bc = bt ? k : n;
+    const int cr = cdc ? n : m, cc = cdc ? m : n;
+    auto ld_ok = [](int ld, int cols) { return ld >= (cols > 1 ? cols : 1); };
+    if (!ld_ok(lda, ac) || !ld_ok(ldb, bc) || !ld_ok(ldd, cc) || (C && !ld_ok(ldc, cc)))
+        return SGEMM_EMU_ERR_LD;
+    if (m == 0 || n == 0 || batch == 0) return SGEMM_EMU_OK;
+    // tile and k-step indices are formed in 32 bits with room for one tile
+    if (m >= (1 << 30) || n >= (1 << 30) || k >= (1 << 30)) return SGEMM_EMU_ERR_UNSUPPORTED;
+    if (D == nullptr || (k > 0 && (A == nullptr || B == nullptr))) return SGEMM_EMU_ERR_NULL;
+    if (stride.a < 0 || stride.b < 0 || stride.c < 0 || stride.d < 0) return SGEMM_EMU_ERR_STRIDE;
+    if (batch > 1 && stride.d < (int64_t)(cr - 1) * ldd + cc) return SGEMM_EMU_ERR_STRIDE;
+    const Extent ed = extent(D, batch, cr, cc, ldd, stride.d);
+    const Extent none{0, 0, true};
+    const Extent ea = k > 0 ? extent(A, stride.a == 0 ? 1 : batch, ar, ac, lda, stride.a) : none;
+    const Extent eb = k > 0 ? extent(B, stride.b == 0 ? 1 : batch, br, bc, ldb, stride.b) : none;
+    const Extent ecx = C ? extent(C, stride.c == 0 ? 1 : batch, cr, cc, ldc, stride.c) : none;
+    if (!all_ok({ed, ea, eb, ecx})) return SGEMM_EMU_ERR_STRIDE;
+    if (overlap(ed, ea) || overlap(ed, eb)) return SGEMM_EMU_ERR_ALIAS;
+    if (C) {
+        const bool in_place = C == D && ldc == ldd && stride.c == stride.d;
+        if (!in_place && overlap(ed, ecx)) return SGEMM_EMU_ERR_ALIAS;
+    }
+    auto vec_ok = [](const void* p, int64_t ld, int64_t s) {
+        return ((uintptr_t)p % 16 == 0) && ld % 4 == 0 && s % 4 == 0;
+    };
+    sgemm_emu::AccArgs& a = l.a;
+    a.m = m;
+    a.n = n;
+    a.k = k;
+    a.A = A;
+    a.lda = lda;
+    a.sa = stride.a;
+    a.B = B;
+    a.ldb = ldb;
+    a.sb = stride.b;
+    a.C = C;
+    a.ldc = ldc;
+    a.sc = stride.c;
+    a.D = D;
+    a.ldd = ldd;
+    a.sd = stride.d;
+    a.batch = batch;
+    a.a_trans = at;
+    a.b_trans = bt;
+    a.cd_col = cdc;
+    // 16-byte accesses happen only along a contiguous direction: A stored
+    // m x k, B stored n x k, C and D stored column-major
+    a.vec_a = at || vec_ok(A, lda, stride.a);
+    a.vec_b = !bt || vec_ok(B, ldb, stride.b);
+    a.vec_c = C == nullptr || !cdc || vec_ok(C, ldc, stride.c);
+    a.vec_d = !cdc || vec_ok(D, ldd, stride.d);
+    l.shape = shape == MFMAE_SHAPE_32x32x16 && ec == 1 ? acc_tile_form(a, l.p) : tile::NONE;
+    empty = false;
+    return SGEMM_EMU_OK;
 }
 
 template <class S>
@@ -420,10 +529,24 @@ int sgemm_emu_resolve_policy(int m, int n, int k, const float* A, int lda, const
                           pol.tile, a, kern);
     if (rc != SGEMM_EMU_OK) return rc;
     *out = pol;
-    if (kernel)
-        *kernel = kern == K_BIG && sgemm_emu::big_streams(a, pol.tile, pol.flow)
-                      ? "bgemm_big_stream_kernel"
-                      : kernel_name(kern);
+    if (kernel) *kernel = kernel_name(a, kern, pol.tile, pol.flow);
+    return SGEMM_EMU_OK;
+}
+
+int sgemm_emu_launch_form(int m, int n, int k, const float* A, int lda, const float* B, int ldb,
+                          float* C, int ldc, int batch, sgemm_emu_stride_t stride,
+                          const sgemm_emu_policy_t* policy, const char** kernel, int* form) {
+    sgemm_emu_policy_t pol{SGEMM_EMU_FLOW_AUTO, 1, SGEMM_EMU_TILE_AUTO};
+    if (policy) pol = *policy;
+    GemmLaunch l;
+    int rc = resolve_launch(m, n, k, A, lda, B, ldb, C, ldc, batch, stride, pol.flow, pol.ec,
+                            pol.tile, l);
+    if (rc != SGEMM_EMU_OK) return rc;
+    if (l.kern == K_NONE) set_form("", {0, 0, 0}, kernel, form);
+    else if (l.shape != tile::NONE) set_form(kTileKernel, tile::form(l.shape), kernel, form);
+    else
+        set_form(kernel_name(l.a, l.kern, l.tile, l.flow),
+                 {tile_rows(l.tile), tile_cols(l.tile), 1}, kernel, form);
     return SGEMM_EMU_OK;
 }
 
@@ -465,74 +588,32 @@ int sgemm_emu_batched_acc(int op_a, int op_b, int layout_cd, int m, int n, int k
                           int lda, const float* B, int ldb, const float* C, int ldc, float* D,
                           int ldd, int batch, sgemm_emu_stride4_t stride, int shape, int ec,
                           hipStream_t stream) {
-    if ((op_a != SGEMM_EMU_OP_N && op_a != SGEMM_EMU_OP_T) ||
-        (op_b != SGEMM_EMU_OP_N && op_b != SGEMM_EMU_OP_T) ||
-        (layout_cd != SGEMM_EMU_ROW_MAJOR && layout_cd != SGEMM_EMU_COL_MAJOR) ||
-        (shape != MFMAE_SHAPE_16x16x32 && shape != MFMAE_SHAPE_32x32x16) || (ec != 0 && ec != 1))
-        return SGEMM_EMU_ERR_POLICY;
-    if (m < 0 || n < 0 || k < 0 || batch < 0) return SGEMM_EMU_ERR_DIM;
-    const bool at = op_a == SGEMM_EMU_OP_T, bt = op_b == SGEMM_EMU_OP_T;
-    const bool cdc = layout_cd == SGEMM_EMU_COL_MAJOR;
-    // stored shapes (rows x cols, row-major with the given ld)
-    const int ar = at ? k : m, ac = at ? m : k;
-    const int br = bt ? n : k, bc = bt ? k : n;
-    const int cr = cdc ? n : m, cc = cdc ? m : n;
-    auto ld_ok = [](int ld, int cols) { return ld >= (cols > 1 ? cols : 1); };
-    if (!ld_ok(lda, ac) || !ld_ok(ldb, bc) || !ld_ok(ldd, cc) || (C && !ld_ok(ldc, cc)))
-        return SGEMM_EMU_ERR_LD;
-    if (m == 0 || n == 0 || batch == 0) return SGEMM_EMU_OK;
-    // tile and k-step indices are formed in 32 bits with room for one tile
-    if (m >= (1 << 30) || n >= (1 << 30) || k >= (1 << 30)) return SGEMM_EMU_ERR_UNSUPPORTED;
-    if (D == nullptr || (k > 0 && (A == nullptr || B == nullptr))) return SGEMM_EMU_ERR_NULL;
-    if (stride.a < 0 || stride.b < 0 || stride.c < 0 || stride.d < 0) return SGEMM_EMU_ERR_STRIDE;
-    if (batch > 1 && stride.d < (int64_t)(cr - 1) * ldd + cc) return SGEMM_EMU_ERR_STRIDE;
-    const Extent ed = extent(D, batch, cr, cc, ldd, stride.d);
-    const Extent none{0, 0, true};
-    const Extent ea = k > 0 ? extent(A, stride.a == 0 ? 1 : batch, ar, ac, lda, stride.a) : none;
-    const Extent eb = k > 0 ? extent(B, stride.b == 0 ? 1 : batch, br, bc, ldb, stride.b) : none;
-    const Extent ecx = C ? extent(C, stride.c == 0 ? 1 : batch, cr, cc, ldc, stride.c) : none;
-    if (!all_ok({ed, ea, eb, ecx})) return SGEMM_EMU_ERR_STRIDE;
-    if (overlap(ed, ea) || overlap(ed, eb)) return SGEMM_EMU_ERR_ALIAS;
-    if (C) {
-        const bool in_place = C == D && ldc == ldd && stride.c == stride.d;
-        if (!in_place && overlap(ed, ecx)) return SGEMM_EMU_ERR_ALIAS;
-    }
-    auto vec_ok = [](const void* p, int64_t ld, int64_t s) {
-        return ((uintptr_t)p % 16 == 0) && ld % 4 == 0 && s % 4 == 0;
-    };
-    sgemm_emu::AccArgs a;
-    a.m = m;
-    a.n = n;
-    a.k = k;
-    a.A = A;
-    a.lda = lda;
-    a.sa = stride.a;
-    a.B = B;
-    a.ldb = ldb;
-    a.sb = stride.b;
-    a.C = C;
-    a.ldc = ldc;
-    a.sc = stride.c;
-    a.D = D;
-    a.ldd = ldd;
-    a.sd = stride.d;
-    a.batch = batch;
-    a.a_trans = at;
-    a.b_trans = bt;
-    a.cd_col = cdc;
-    // 16-byte accesses happen only along a contiguous direction: A stored
-    // m x k, B stored n x k, C and D stored column-major
-    a.vec_a = at || vec_ok(A, lda, stride.a);
-    a.vec_b = !bt || vec_ok(B, ldb, stride.b);
-    a.vec_c = C == nullptr || !cdc || vec_ok(C, ldc, stride.c);
-    a.vec_d = !cdc || vec_ok(D, ldd, stride.d);
-    hipError_t e;
-    tile::Problem p;
-    const tile::Shape form =
-        shape == MFMAE_SHAPE_32x32x16 && ec == 1 ? acc_tile_form(a, p) : tile::NONE;
-    if (form != tile::NONE) e = tile::launch(p, form, tile::ACC, stream);
-    else e = sgemm_emu::launch_gemm_acc(a, shape, ec == 1, stream);
+    AccLaunch l;
+    bool empty;
+    const int rc = resolve_acc(op_a, op_b, layout_cd, m, n, k, A, lda, B, ldb, C, ldc, D, ldd,
+                               batch, stride, shape, ec, l, empty);
+    if (rc != SGEMM_EMU_OK || empty) return rc;
+    const hipError_t e = l.shape != tile::NONE
+                             ? tile::launch(l.p, l.shape, stream)
+                             : sgemm_emu::launch_gemm_acc(l.a, shape, ec == 1, stream);
     return e == hipSuccess ? SGEMM_EMU_OK : hip_fail(e);
+}
+
+int sgemm_emu_acc_launch_form(int op_a, int op_b, int layout_cd, int m, int n, int k,
+                              const float* A, int lda, const float* B, int ldb, const float* C,
+                              int ldc, float* D, int ldd, int batch, sgemm_emu_stride4_t stride,
+                              int shape, int ec, const char** kernel, int* form) {
+    AccLaunch l;
+    bool empty;
+    const int rc = resolve_acc(op_a, op_b, layout_cd, m, n, k, A, lda, B, ldb, C, ldc, D, ldd,
+                               batch, stride, shape, ec, l, empty);
+    if (rc != SGEMM_EMU_OK) return rc;
+    // a wave of the fragment kernel takes 2 x 2 blocks of its shape
+    const int side = shape == MFMAE_SHAPE_32x32x16 ? 64 : 32;
+    if (empty) set_form("", {0, 0, 0}, kernel, form);
+    else if (l.shape != tile::NONE) set_form(kTileKernel, tile::form(l.shape), kernel, form);
+    else set_form("gemm_acc_kernel", {side, side, 1}, kernel, form);
+    return SGEMM_EMU_OK;
 }
 
 int householder_emu_batched(int n, const float* u, int64_t stride_u, const float* B, int ldb,

@@ -1,11 +1,9 @@
 // The tile kernel's instances and the choice among them (tile_gemm.hpp has
 // the kernel).
 //
-// The same code runs under the names of the kernels whose products it takes:
-// whole tiles that are too few for the full-tile kernel to fill the device
-// and large ragged products (bgemm_big_kernel), other ragged products
-// (bgemm_reg_kernel), products with unaligned rows (bgemm_emu_kernel) and the
-// accumulate form with its transposed operands (gemm_acc_kernel).
+// It takes whole tiles that are too few for the full-tile kernel to fill the
+// device, ragged products, products with unaligned rows and the accumulate
+// form with its transposed operands.
 #include "tile_gemm.hpp"
 #include "tile_launch.h"
 
@@ -14,17 +12,11 @@ namespace tile {
 
 namespace {
 
-#define SGEMM_EMU_TILE_KERNEL(NAME)                                                      \
-    template <class CF>                                                                  \
-    __global__ __launch_bounds__(CF::NT, CF::W) void NAME(Params p) {                    \
-        __shared__ __attribute__((aligned(16))) unsigned char smem[CF::LDS_BYTES];       \
-        run<CF>(p, smem);                                                                \
-    }
-SGEMM_EMU_TILE_KERNEL(bgemm_big_kernel)
-SGEMM_EMU_TILE_KERNEL(bgemm_reg_kernel)
-SGEMM_EMU_TILE_KERNEL(bgemm_emu_kernel)
-SGEMM_EMU_TILE_KERNEL(gemm_acc_kernel)
-#undef SGEMM_EMU_TILE_KERNEL
+template <class CF>
+__global__ __launch_bounds__(CF::NT, CF::W) void gemm_tile_kernel(Params p) {
+    __shared__ __attribute__((aligned(16))) unsigned char smem[CF::LDS_BYTES];
+    run<CF>(p, smem);
+}
 
 // What a shape costs, in microseconds.  A workgroup takes `first` per chunk
 // when it has a CU to itself, and `chunk` for each of those that share one
@@ -78,9 +70,8 @@ bool fits(const Cost& c, const Problem& p) {
            (p.C == nullptr || offsets_fit(true, c.bm, p.ldc + c.bn));
 }
 
-template <class K>
-hipError_t launch_kernel(K kernel, int bm, int bn, int threads, const Problem& a,
-                         hipStream_t stream) {
+template <class CF>
+hipError_t launch_cfg(const Problem& a, hipStream_t stream) {
     Params p;
     p.m = a.m;
     p.n = a.n;
@@ -97,55 +88,45 @@ hipError_t launch_kernel(K kernel, int bm, int bn, int threads, const Problem& a
     p.D = a.D;
     p.ldd = a.ldd;
     p.sd = a.sd;
-    p.tiles_m = cdiv(a.m, bm);
-    p.tiles_n = cdiv(a.n, bn);
+    p.tiles_m = cdiv(a.m, CF::BM);
+    p.tiles_n = cdiv(a.n, CF::BN);
     const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
     // one launch stays below 2^31 work-items
-    const int64_t max_tasks = (int64_t(1) << 31) / threads - 1;
+    const int64_t max_tasks = (int64_t(1) << 31) / CF::NT - 1;
     if (tiles > max_tasks) return hipErrorInvalidConfiguration;
     const int64_t items_per_launch = max_tasks / tiles;
     for (int64_t i0 = 0; i0 < a.batch; i0 += items_per_launch) {
         const int64_t items = a.batch - i0 < items_per_launch ? a.batch - i0 : items_per_launch;
         p.ntasks = (int)(items * tiles);
         p.item0 = (int)i0;
-        hipLaunchKernelGGL(kernel, dim3((unsigned)p.ntasks), dim3(threads), 0, stream, p);
+        hipLaunchKernelGGL(gemm_tile_kernel<CF>, dim3((unsigned)p.ntasks), dim3(CF::NT), 0, stream,
+                           p);
         const hipError_t e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
     return hipSuccess;
 }
 
-template <class CF>
-hipError_t launch_cfg(const Problem& a, Family family, hipStream_t stream) {
-    auto go = [&](auto kernel) {
-        return launch_kernel(kernel, CF::BM, CF::BN, CF::NT, a, stream);
-    };
-    if constexpr (CF::ADD) return go(gemm_acc_kernel<CF>);
-    else if (family == BIG) return go(bgemm_big_kernel<CF>);
-    else if (family == REG) return go(bgemm_reg_kernel<CF>);
-    else return go(bgemm_emu_kernel<CF>);
-}
-
 template <bool A_KC, bool B_KC, bool ADD>
-hipError_t launch_shape(const Problem& a, Shape shape, Family f, hipStream_t s) {
+hipError_t launch_shape(const Problem& a, Shape shape, hipStream_t s) {
     const bool edge = a.m < 64 || a.n < 64;
     switch (shape) {
         case T64:
-            return edge ? launch_cfg<Cfg<64, 64, 2, 2, 1, 4, A_KC, B_KC, ADD, true>>(a, f, s)
-                        : launch_cfg<Cfg<64, 64, 2, 2, 1, 4, A_KC, B_KC, ADD, false>>(a, f, s);
+            return edge ? launch_cfg<Cfg<64, 64, 2, 2, 1, 4, A_KC, B_KC, ADD, true>>(a, s)
+                        : launch_cfg<Cfg<64, 64, 2, 2, 1, 4, A_KC, B_KC, ADD, false>>(a, s);
         case T64_K2:
-            return edge ? launch_cfg<Cfg<64, 64, 2, 2, 2, 4, A_KC, B_KC, ADD, true>>(a, f, s)
-                        : launch_cfg<Cfg<64, 64, 2, 2, 2, 4, A_KC, B_KC, ADD, false>>(a, f, s);
+            return edge ? launch_cfg<Cfg<64, 64, 2, 2, 2, 4, A_KC, B_KC, ADD, true>>(a, s)
+                        : launch_cfg<Cfg<64, 64, 2, 2, 2, 4, A_KC, B_KC, ADD, false>>(a, s);
         case T64_K4:
-            return edge ? launch_cfg<Cfg<64, 64, 2, 2, 4, 4, A_KC, B_KC, ADD, true>>(a, f, s)
-                        : launch_cfg<Cfg<64, 64, 2, 2, 4, 4, A_KC, B_KC, ADD, false>>(a, f, s);
-        case T128x64: return launch_cfg<Cfg<128, 64, 2, 2, 1, 2, A_KC, B_KC, ADD, false>>(a, f, s);
+            return edge ? launch_cfg<Cfg<64, 64, 2, 2, 4, 4, A_KC, B_KC, ADD, true>>(a, s)
+                        : launch_cfg<Cfg<64, 64, 2, 2, 4, 4, A_KC, B_KC, ADD, false>>(a, s);
+        case T128x64: return launch_cfg<Cfg<128, 64, 2, 2, 1, 2, A_KC, B_KC, ADD, false>>(a, s);
         case T128x64_K2:
-            return launch_cfg<Cfg<128, 64, 2, 2, 2, 2, A_KC, B_KC, ADD, false>>(a, f, s);
-        case T128: return launch_cfg<Cfg<128, 128, 2, 2, 1, 2, A_KC, B_KC, ADD, false>>(a, f, s);
-        case T128_K2: return launch_cfg<Cfg<128, 128, 2, 2, 2, 2, A_KC, B_KC, ADD, false>>(a, f, s);
+            return launch_cfg<Cfg<128, 64, 2, 2, 2, 2, A_KC, B_KC, ADD, false>>(a, s);
+        case T128: return launch_cfg<Cfg<128, 128, 2, 2, 1, 2, A_KC, B_KC, ADD, false>>(a, s);
+        case T128_K2: return launch_cfg<Cfg<128, 128, 2, 2, 2, 2, A_KC, B_KC, ADD, false>>(a, s);
         case T128x256:
-            return launch_cfg<Cfg<128, 256, 2, 4, 1, 2, A_KC, B_KC, ADD, false>>(a, f, s);
+            return launch_cfg<Cfg<128, 256, 2, 4, 1, 2, A_KC, B_KC, ADD, false>>(a, s);
         default: return hipErrorInvalidValue;
     }
 }
@@ -169,16 +150,19 @@ Shape choose(const Problem& p) {
     return best;
 }
 
-hipError_t launch(const Problem& p, Shape shape, Family family, hipStream_t stream) {
+hipError_t launch(const Problem& p, Shape shape, hipStream_t stream) {
     if (shape == NONE) return hipErrorInvalidValue;
-    if (family != ACC)  // A stored m x k, B stored k x n, nothing added
-        return p.a_kc && !p.b_kc && !p.C ? launch_shape<true, false, false>(p, shape, family, stream)
-                                         : hipErrorInvalidValue;
-    if (p.a_kc)
-        return p.b_kc ? launch_shape<true, true, true>(p, shape, family, stream)
-                      : launch_shape<true, false, true>(p, shape, family, stream);
-    return p.b_kc ? launch_shape<false, true, true>(p, shape, family, stream)
-                  : launch_shape<false, false, true>(p, shape, family, stream);
+    if (p.a_kc && !p.b_kc)
+        return p.C ? launch_shape<true, false, true>(p, shape, stream)
+                   : launch_shape<true, false, false>(p, shape, stream);
+    if (p.a_kc) return launch_shape<true, true, true>(p, shape, stream);
+    return p.b_kc ? launch_shape<false, true, true>(p, shape, stream)
+                  : launch_shape<false, false, true>(p, shape, stream);
+}
+
+Form form(Shape shape) {
+    if (shape == NONE) return {0, 0, 0};
+    return {kCosts[shape].bm, kCosts[shape].bn, kCosts[shape].kg};
 }
 
 }  // namespace tile

@@ -31,15 +31,18 @@ struct Problem {
 // Workgroup tile and number of wave groups that share its k chunks.
 enum Shape { T64, T64_K2, T64_K4, T128x64, T128x64_K2, T128, T128_K2, T128x256, NONE };
 
-// The kernel the product is launched under (the same code).
-enum Family { BIG, REG, GENERAL, ACC };
-
 // The shape expected to be the fastest for this product, NONE if no shape
 // takes it (sizes or leading dimensions out of range, or fewer than four
 // values along an operand's contiguous m or n).
 Shape choose(const Problem& p);
 
-hipError_t launch(const Problem& p, Shape shape, Family family, hipStream_t stream);
+hipError_t launch(const Problem& p, Shape shape, hipStream_t stream);
+
+// Rows and columns of a shape's workgroup tile and its wave groups.
+struct Form {
+    int rows, cols, groups;
+};
+Form form(Shape shape);
 
 }  // namespace tile
 }  // namespace sgemm_emu

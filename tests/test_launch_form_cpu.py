@@ -1,0 +1,83 @@
+"""What a call launches, as the host-only queries report it (no GPU: the
+addresses are never read): the tile kernel and its form where an automatic
+call takes it, the named kernel for a named policy, and one translation unit
+per kernel name."""
+import ctypes
+import pathlib
+import re
+
+import pytest
+
+import bench
+import paper_2308_15152_amd as pkg
+
+ROOT = pathlib.Path(__file__).resolve().parents[1]
+PA, PB, PC, PD = (i << 44 for i in (1, 2, 3, 4))
+AUTO, REG = pkg.Policy(), pkg.Policy(pkg.FLOW_REG, 1, pkg.TILE_64x64)
+
+
+def gemm_form(m, n, k, batch=1, policy=None, lda=None, ldb=None, ldc=None, offset=0):
+    """(status, kernel, form) of a packed product (or with the given row
+    pitches), its bases `offset` floats off alignment."""
+    lda, ldb, ldc = lda or k, ldb or n, ldc or n
+    kern, form = ctypes.c_char_p(), (ctypes.c_int * 3)()
+    rc = pkg.load().sgemm_emu_launch_form(
+        m, n, k, PA + 4 * offset, lda, PB + 4 * offset, ldb, PC + 4 * offset, ldc, batch,
+        pkg.Stride(m * lda, k * ldb, m * ldc), None if policy is None else ctypes.byref(policy),
+        ctypes.byref(kern), form)
+    return rc, (kern.value or b"").decode(), tuple(form)
+
+
+def acc_form(m, n, k, batch=1, ta=0, tb=0, col=0, c=True, shape=pkg.SHAPE_32x32x16, ec=1, pad=0,
+             offset=0):
+    lda, ldb, ldd = (max(x, 1) + pad for x in (m if ta else k, k if tb else n, m if col else n))
+    st = pkg.Stride4(lda * (k if ta else m), ldb * (n if tb else k), ldd * (n if col else m),
+                     ldd * (n if col else m))
+    kern, form = ctypes.c_char_p(), (ctypes.c_int * 3)()
+    o = 4 * offset
+    rc = pkg.load().sgemm_emu_acc_launch_form(
+        ta, tb, col, m, n, k, PA + o, lda, PB + o, ldb, PC + o if c else None, ldd, PD + o, ldd,
+        batch, st, shape, ec, ctypes.byref(kern), form)
+    return rc, (kern.value or b"").decode(), tuple(form)
+
+
+def test_automatic_and_named_products():
+    assert gemm_form(1100, 1500, 2000) == (0, "gemm_tile_kernel", (128, 64, 2))
+    assert gemm_form(1100, 1500, 2000, policy=AUTO)[1] == "gemm_tile_kernel"
+    assert gemm_form(1100, 1500, 2000, policy=REG) == (0, "bgemm_reg_kernel", (64, 64, 1))
+    assert gemm_form(8192, 8192, 8192) == (0, "bgemm_big_kernel", (128, 256, 1))
+    assert gemm_form(256, 256, 256, 1024) == (0, "bgemm_big_stream_kernel", (256, 128, 1))
+    assert gemm_form(0, 4, 4) == (0, "", (0, 0, 0))
+    assert gemm_form(-1, 4, 4)[0] == -1
+    for m, n, k, batch in ((8192, 8192, 8192, 1), (1100, 1500, 2000, 1), (16, 16, 16, 9)):
+        named = pkg.Policy(pkg.FLOW_SPLIT, 1, pkg.TILE_128x128)
+        out, kern = pkg.Policy(), ctypes.c_char_p()
+        st = pkg.Stride(m * k, k * n, m * n)
+        assert pkg.load().sgemm_emu_resolve_policy(m, n, k, PA, k, PB, n, PC, n, batch, st,
+                                                   ctypes.byref(named), ctypes.byref(out),
+                                                   ctypes.byref(kern)) == 0
+        assert gemm_form(m, n, k, batch, policy=named)[1] == kern.value.decode()
+
+
+def test_accumulate():
+    assert acc_form(4096, 4096, 4096, tb=1) == (0, "gemm_tile_kernel", (128, 256, 1))
+    assert acc_form(512, 32, 256, batch=500, ta=1) == (0, "gemm_acc_kernel", (64, 64, 1))
+    assert acc_form(128, 128, 128, shape=pkg.SHAPE_16x16x32) == (0, "gemm_acc_kernel",
+                                                                 (32, 32, 1))
+    assert acc_form(128, 128, 128, ec=0)[1] == "gemm_acc_kernel"
+    assert acc_form(128, 128, 0)[1] == "gemm_acc_kernel"
+    assert acc_form(0, 4, 4) == (0, "", (0, 0, 0))
+    assert acc_form(4, 4, 4, ta=2)[0] == -8
+
+
+@pytest.mark.parametrize("name", sorted(bench.KERNEL_SOURCES))
+def test_one_translation_unit_per_kernel(name):
+    """A kernel's name stands for the code of one translation unit, the one
+    whose hash its counter runs are filed under."""
+    csrc = ROOT / "paper_2308_15152_amd" / "csrc"
+    named = {f.name for f in csrc.glob("*.hip")
+             if re.search(rf"\b{name}\s*\(", re.sub(r"//[^\n]*", "", f.read_text()))
+             and "__global__" in f.read_text()}
+    macros = {f.name for f in csrc.glob("*.hip")
+              if re.search(rf"KERNEL\w*\(\s*{name}\s*\)", f.read_text())}
+    assert named | macros == {bench.KERNEL_SOURCES[name]}, (name, named, macros)
