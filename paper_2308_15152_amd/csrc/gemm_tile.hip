@@ -62,7 +62,15 @@ double cost(const Cost& c, const Problem& p) {
     return (n > c.fit ? n : c.fit) * (steps * c.chunk + ends);
 }
 
+// Workgroups of the shape that one launch holds: it stays below 2^31
+// work-items.
+int64_t max_tasks(int threads) { return (int64_t(1) << 31) / threads - 1; }
+
 bool fits(const Cost& c, const Problem& p) {
+    // the tiles of one item go out in one launch
+    const int threads = 256 * c.kg * (c.bm * c.bn > 128 * 128 ? 2 : 1);
+    const int64_t tiles = (int64_t)cdiv(p.m, c.bm) * cdiv(p.n, c.bn);
+    if (tiles > max_tasks(threads)) return false;
     // only the smallest tile has an EDGE form
     if (c.bm + c.bn > 128 && (p.m < c.bm || p.n < c.bn)) return false;
     return offsets_fit(p.a_kc, c.bm, p.lda) && offsets_fit(p.b_kc, c.bn, p.ldb) &&
@@ -91,10 +99,8 @@ hipError_t launch_cfg(const Problem& a, hipStream_t stream) {
     p.tiles_m = cdiv(a.m, CF::BM);
     p.tiles_n = cdiv(a.n, CF::BN);
     const int64_t tiles = (int64_t)p.tiles_m * p.tiles_n;
-    // one launch stays below 2^31 work-items
-    const int64_t max_tasks = (int64_t(1) << 31) / CF::NT - 1;
-    if (tiles > max_tasks) return hipErrorInvalidConfiguration;
-    const int64_t items_per_launch = max_tasks / tiles;
+    if (tiles > max_tasks(CF::NT)) return hipErrorInvalidConfiguration;
+    const int64_t items_per_launch = max_tasks(CF::NT) / tiles;
     for (int64_t i0 = 0; i0 < a.batch; i0 += items_per_launch) {
         const int64_t items = a.batch - i0 < items_per_launch ? a.batch - i0 : items_per_launch;
         p.ntasks = (int)(items * tiles);

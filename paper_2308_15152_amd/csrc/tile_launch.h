@@ -32,8 +32,9 @@ struct Problem {
 enum Shape { T64, T64_K2, T64_K4, T128x64, T128x64_K2, T128, T128_K2, T128x256, NONE };
 
 // The shape expected to be the fastest for this product, NONE if no shape
-// takes it (sizes or leading dimensions out of range, or fewer than four
-// values along an operand's contiguous m or n).
+// takes it (sizes or leading dimensions out of range, more tiles in an item
+// than one launch holds, or fewer than four values along an operand's
+// contiguous m or n).
 Shape choose(const Problem& p);
 
 hipError_t launch(const Problem& p, Shape shape, hipStream_t stream);

@@ -17,7 +17,7 @@ import torch
 import oracle
 import paper_2308_15152_amd as pkg
 import synth
-from gpu_util import device, gate, gate_applies, to_np
+from gpu_util import assert_periodic, device, gate, gate_applies, periodic_batch, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -116,6 +116,29 @@ def test_far_rows():
         ref = oracle.gemm(A[:, :, :kk].contiguous().numpy(), B[:, :kk].contiguous().numpy())
         gate(to_np(C), ref, kk, f"tile, far rows k={kk}")
     del buf, C
+    torch.cuda.empty_cache()
+
+
+@pytest.mark.parametrize("k", [4, 5])
+def test_tall_products(k):
+    """One item of more 64 x 64 tiles than a launch of the tile kernel holds
+    (8,388,607): the calls take the kernels that split it, accumulate and
+    unaligned products alike.  P rows checked against the oracle repeat down
+    the matrix; every output row must equal its own bitwise."""
+    P, n, m = 1021, 4, 64 * 8388607 + 71
+    print(f"case tall m={m} n={n} k={k}", flush=True)
+    g = synth.rng(40 + k)
+    A, B = synth.uniform((P, k), g), synth.uniform((k, n), g)
+    Ad, Bd = periodic_batch(A.to(device()), m), B.to(device())
+    D = torch.full((m, n), float("nan"), device=device())
+    if k == 4:
+        pkg.sgemm_emu_batched_acc(Ad, Bd, None, D)
+    else:
+        pkg.sgemm_emu_batched(Ad, Bd, D)
+    ref = {key: v[0] for key, v in oracle.gemm(A[None].numpy(), B[None].numpy()).items()}
+    gate(to_np(D[:P]), ref, k, f"tall k={k}", max_gate=False)
+    assert_periodic(D, P, "tall rows")
+    del Ad, D
     torch.cuda.empty_cache()
 
 

@@ -81,3 +81,20 @@ def test_one_translation_unit_per_kernel(name):
     macros = {f.name for f in csrc.glob("*.hip")
               if re.search(rf"KERNEL\w*\(\s*{name}\s*\)", f.read_text())}
     assert named | macros == {bench.KERNEL_SOURCES[name]}, (name, named, macros)
+
+
+def test_items_of_more_tiles_than_a_launch_holds():
+    """A launch holds 2^31 / 256 - 1 = 8,388,607 workgroups of 256 threads.  An
+    item of more 64 x 64 tiles (narrow matrices take no other) goes to the
+    kernels that split it over launches or walk it, as does one of 2^30 rows."""
+    last = 64 * 8388607
+    for k in (4, 20):
+        assert acc_form(last, 4, k)[:2] == (0, "gemm_tile_kernel")
+        assert acc_form(last + 1, 4, k)[:2] == (0, "gemm_acc_kernel")
+        assert acc_form(4, last, k, ta=1, tb=1, col=1)[:2] == (0, "gemm_tile_kernel")
+        assert acc_form(4, last + 1, k, ta=1, tb=1, col=1)[:2] == (0, "gemm_acc_kernel")
+    assert gemm_form(last, 4, 5)[:2] == (0, "gemm_tile_kernel")
+    assert gemm_form(last + 1, 4, 5)[:2] == (0, "bgemm_emu_kernel")
+    assert gemm_form((1 << 30) + 8, 4, 5)[:2] == (0, "bgemm_emu_kernel")
+    # wide enough for 128 x 64 tiles, the same rows are fewer tiles
+    assert acc_form(last + 1, 64, 4) == (0, "gemm_tile_kernel", (128, 64, 1))
