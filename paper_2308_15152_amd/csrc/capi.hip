@@ -256,6 +256,11 @@ tile::Shape tile_form(const sgemm_emu::GemmArgs& a, Kernel kern, int resolved, t
             // interior and edges in one launch, whatever the alignment (8000^3
             // in three launches 3.39 ms against 2.83, 6000 x 6000 x 960 282 us
             // / 219, 2 x 2600 x 2600 x 2560 351 / 219)
+            // With C rows of 2^22 floats and more the 128 x 256 tile stores
+            // through 64-bit pointers (4100 x 4300 x 2060, rows of 2^22 and of
+            // 2^23 floats, 267 and 261 us; on the 64 x 64 tile, whose offsets
+            // reach further, 363, on the register flow 675).
+            if (const tile::Shape far = tile::far_rows(p); far != tile::NONE) return far;
             break;
         case K_REG:
             // The register flow stays where it waits for HBM: a short k, small
@@ -310,7 +315,7 @@ int resolve_launch(int m, int n, int k, const float* A, int lda, const float* B,
     int rc = resolve_gemm(m, n, k, A, lda, B, ldb, C, ldc, batch, st, flow, ec, tile, l.a, l.kern);
     if (rc != SGEMM_EMU_OK) return rc;
     l.shape = automatic && l.kern != K_NONE ? tile_form(l.a, l.kern, tile, l.p) : tile::NONE;
-    if (l.kern == K_TILED && l.shape == tile::NONE) {  // C rows too far apart for the tile kernel
+    if (l.kern == K_TILED && l.shape == tile::NONE) {  // rows too far apart for the tile kernel
         l.kern = K_REG;
         flow = SGEMM_EMU_FLOW_REG;
         tile = SGEMM_EMU_TILE_64x64;

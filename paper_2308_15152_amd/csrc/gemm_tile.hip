@@ -156,7 +156,17 @@ Shape choose(const Problem& p) {
     return best;
 }
 
+Shape far_rows(const Problem& p) {
+    const Cost& c = kCosts[T128x256];
+    if (p.C != nullptr || !p.a_kc || p.b_kc || offsets_fit(true, c.bm, p.ldd + c.bn)) return NONE;
+    Problem near = p;
+    near.ldd = p.n;
+    return choose(near) != NONE && fits(c, near) ? T128x256_FAR : NONE;
+}
+
 hipError_t launch(const Problem& p, Shape shape, hipStream_t stream) {
+    if (shape == T128x256_FAR)
+        return launch_cfg<Cfg<128, 256, 2, 4, 1, 2, true, false, false, false, true>>(p, stream);
     if (shape == NONE) return hipErrorInvalidValue;
     if (p.a_kc && !p.b_kc)
         return p.C ? launch_shape<true, false, true>(p, shape, stream)
@@ -168,6 +178,7 @@ hipError_t launch(const Problem& p, Shape shape, hipStream_t stream) {
 
 Form form(Shape shape) {
     if (shape == NONE) return {0, 0, 0};
+    if (shape == T128x256_FAR) shape = T128x256;
     return {kCosts[shape].bm, kCosts[shape].bn, kCosts[shape].kg};
 }
 

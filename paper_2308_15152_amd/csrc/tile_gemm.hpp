@@ -79,13 +79,15 @@ struct Params {
 
 // BM x BN tiles, KG groups of WAVES_M x WAVES_N waves that share the tile's
 // chunks, at least W waves per SIMD; A_KC / B_KC: the operand is K-contiguous;
-// ADD: C is added; EDGE: m < BM or n < BN.
+// ADD: C is added; EDGE: m < BM or n < BN; FAR: D's rows are too far apart for
+// 32-bit offsets (nothing is added then).
 template <int BM_, int BN_, int WAVES_M_, int WAVES_N_, int KG_, int W_, bool A_KC_, bool B_KC_,
-          bool ADD_, bool EDGE_>
+          bool ADD_, bool EDGE_, bool FAR_ = false>
 struct Cfg {
     static constexpr int BM = BM_, BN = BN_, KG = KG_;
     static constexpr int WAVES_M = WAVES_M_, WAVES_N = WAVES_N_, W = W_;
-    static constexpr bool A_KC = A_KC_, B_KC = B_KC_, ADD = ADD_, EDGE = EDGE_;
+    static constexpr bool A_KC = A_KC_, B_KC = B_KC_, ADD = ADD_, EDGE = EDGE_, FAR = FAR_;
+    static_assert(!(ADD && FAR), "C would need 64-bit offsets too");
     static constexpr int GROUP = 64 * WAVES_M * WAVES_N;  // threads of a group
     static constexpr int NT = KG * GROUP;
     static constexpr int WM = BM / WAVES_M, WN = BN / WAVES_N;
@@ -540,6 +542,20 @@ __device__ __forceinline__ void run(const Params& p, unsigned char* smem) {
     // 174 / 192).  Otherwise the pieces of a line meet in the L2 (8 x 1001 x 999
     // x 1003 64 against 56 us, 174 x 651 x 2213 x 128 611 / 488).
     float* const Di = p.D + it * p.sd + (int64_t)(m0 + wrow) * p.ldd + n0 + wcol;
+    if constexpr (CF::FAR) {
+#pragma unroll
+        for (int tm = 0; tm < CF::TM; ++tm)
+#pragma unroll
+            for (int tn = 0; tn < CF::TN; ++tn)
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const int r = 32 * tm + 4 * g + 8 * (e >> 2) + (e & 3), c = 32 * tn + j;
+                    const int row = m0 + wrow + r, col = n0 + wcol + c;
+                    if ((col >= n_own) & (col < p.n) & (row >= m_own) & (row < p.m))
+                        Di[r * p.ldd + c] = acc[tm][tn][e];
+                }
+        return;
+    }
     const __amdgpu_buffer_rsrc_t rd =
         __builtin_amdgcn_make_buffer_rsrc(Di, 0, (int)kPastEnd, 0x00020000);
     const bool lines = ((uintptr_t)Di % 128 == 0) & (p.ldd % 32 == 0);

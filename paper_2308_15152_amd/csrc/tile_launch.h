@@ -29,13 +29,17 @@ struct Problem {
 };
 
 // Workgroup tile and number of wave groups that share its k chunks.
-enum Shape { T64, T64_K2, T64_K4, T128x64, T128x64_K2, T128, T128_K2, T128x256, NONE };
+enum Shape { T64, T64_K2, T64_K4, T128x64, T128x64_K2, T128, T128_K2, T128x256, NONE, T128x256_FAR };
 
 // The shape expected to be the fastest for this product, NONE if no shape
 // takes it (sizes or leading dimensions out of range, more tiles in an item
 // than one launch holds, or fewer than four values along an operand's
 // contiguous m or n).
 Shape choose(const Problem& p);
+
+// T128x256_FAR for a product whose D rows are too far apart for the 32-bit
+// offsets of T128x256 and that takes that shape otherwise, else NONE.
+Shape far_rows(const Problem& p);
 
 hipError_t launch(const Problem& p, Shape shape, hipStream_t stream);
 

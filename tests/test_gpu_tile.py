@@ -102,19 +102,51 @@ def test_integers_exact():
     assert np.array_equal(C, ref.astype(np.float32))
 
 
-def test_far_rows():
-    """C rows further apart than the tile kernel's 32-bit offsets reach (64
-    rows of 2^23 floats): the calls take the kernels that address with 64-bit
-    pointers."""
-    m, n, k = 66, 68, 80
+# Row pitches (floats) on both sides of the tile kernel's 32-bit offsets: 64
+# rows of C reach 2^31 bytes at pitch 2^23 (less a tile's columns).
+@pytest.mark.parametrize("ldc", [(1 << 23) - 72, (1 << 23) - 64, 1 << 23])
+@pytest.mark.parametrize("k", [320, 319])
+def test_far_rows(k, ldc):
+    """C rows on both sides of the reach of the tile kernel's offsets: past it
+    the calls take the kernels that address with 64-bit pointers (the register
+    flow, and for unaligned rows the general kernel)."""
+    m, n = 66, 68
+    print(f"case tile far rows k={k} ldc={ldc}", flush=True)
     A, B = synth.gemm_inputs(1, m, n, k, seed=6)
-    buf = torch.full(((m - 1) * (1 << 23) + n,), float("nan"), device=device())
-    C = buf.as_strided((1, m, n), (0, 1 << 23, 1))
-    ref = oracle.gemm(A.numpy(), B.numpy())
-    for kk in (80, 79):
-        pkg.sgemm_emu_batched(A[:, :, :kk].to(device()), B[:, :kk].to(device()), C)
-        ref = oracle.gemm(A[:, :, :kk].contiguous().numpy(), B[:, :kk].contiguous().numpy())
-        gate(to_np(C), ref, kk, f"tile, far rows k={kk}")
+    Ad, Bd = A.to(device()), B.to(device())
+    buf = torch.full(((m - 1) * ldc + n,), float("nan"), device=device())
+    C = buf.as_strided((1, m, n), (0, ldc, 1))
+    kernel, _ = pkg.sgemm_emu_launch_form(Ad, Bd, C)
+    far = "bgemm_reg_kernel" if k % 4 == 0 else "bgemm_emu_kernel"
+    assert kernel == ("gemm_tile_kernel" if ldc < (1 << 23) - 64 else far)
+    pkg.sgemm_emu_batched(Ad, Bd, C)
+    gate(to_np(C), oracle.gemm(A.numpy(), B.numpy()), k, f"tile, far rows k={k}")
+    del buf, C
+    torch.cuda.empty_cache()
+
+
+def test_far_rows_of_large_products():
+    """A large product of nearly whole tiles with C rows past the 128 x 256
+    tile's 32-bit offsets (its 64-bit stores): outputs sampled on all seams
+    and corners, and nothing written between the rows."""
+    m, n, k, ldc = 4100, 4300, 2060, (1 << 22) + 4
+    print(f"case tile far rows large {m}x{n}x{k} ldc={ldc}", flush=True)
+    A, B = synth.gemm_inputs(1, m, n, k, seed=7)
+    Ad, Bd = A.to(device()), B.to(device())
+    buf = torch.full(((m - 1) * ldc + n,), float("nan"), device=device())
+    C = buf.as_strided((1, m, n), (0, ldc, 1))
+    assert pkg.sgemm_emu_launch_form(Ad, Bd, C) == ("gemm_tile_kernel", (128, 256, 1))
+    pkg.sgemm_emu_batched(Ad, Bd, C)
+    body = to_np(C[0].contiguous())
+    assert np.isfinite(body).all()
+    assert torch.isnan(buf.as_strided((m - 1, 64), (ldc, 1), n)).all()
+    assert torch.isnan(buf.as_strided((m - 1, 64), (ldc, 1), ldc - 64)).all()
+    g = np.random.default_rng(3)
+    rows = np.unique([0, 127, 128, 3971, 3972, 4095, 4096, m - 1, *g.integers(0, m, 12)])
+    cols = np.unique([0, 255, 256, 4043, 4044, 4095, 4096, n - 1, *g.integers(0, n, 12)])
+    rr, cc = (x.ravel() for x in np.meshgrid(rows, cols, indexing="ij"))
+    ref = oracle.dots(A[0].numpy()[rr], np.ascontiguousarray(B[0].numpy()[:, cc].T))
+    gate(body[rr, cc], ref, k, "tile, far rows, large")
     del buf, C
     torch.cuda.empty_cache()
 

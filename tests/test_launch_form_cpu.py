@@ -98,3 +98,17 @@ def test_items_of_more_tiles_than_a_launch_holds():
     assert gemm_form((1 << 30) + 8, 4, 5)[:2] == (0, "bgemm_emu_kernel")
     # wide enough for 128 x 64 tiles, the same rows are fewer tiles
     assert acc_form(last + 1, 64, 4) == (0, "gemm_tile_kernel", (128, 64, 1))
+
+
+def test_far_rows():
+    """Large products of nearly whole tiles keep the 128 x 256 tile however far
+    apart C's rows are; operand rows past its 32-bit offsets leave it."""
+    shape = (4100, 4300, 2060)
+    for ldc in (4300, (1 << 22) - 260, 1 << 22, (1 << 23) + 4, 1 << 30):
+        assert gemm_form(*shape, ldc=ldc) == (0, "gemm_tile_kernel", (128, 256, 1)), ldc
+    assert gemm_form(*shape, ldb=(1 << 24) - 16)[1] == "gemm_tile_kernel"
+    assert gemm_form(*shape, ldb=1 << 24) == (0, "bgemm_reg_kernel", (64, 64, 1))
+    assert gemm_form(*shape, ldb=1 << 24, ldc=1 << 23) == (0, "bgemm_reg_kernel", (64, 64, 1))
+    # other products with far rows go to the kernels with 64-bit addresses
+    assert gemm_form(300, 300, 400, ldc=1 << 23)[1] == "bgemm_reg_kernel"
+    assert gemm_form(300, 300, 401, ldc=1 << 23)[1] == "bgemm_emu_kernel"
