@@ -245,7 +245,7 @@ namespace tile = sgemm_emu::tile;
 // it resolves to, NONE to run that kernel itself.
 tile::Shape tile_form(const sgemm_emu::GemmArgs& a, Kernel kern, int resolved, tile::Problem& p) {
     p = {a.m,  a.n,   a.k,  a.A, a.lda, a.sa,  true,  a.B,  a.ldb,
-         a.sb, false, nullptr, 0,   0,     a.C, a.ldc, a.sc, a.batch};
+         a.sb, false, nullptr, 0,   0,     a.C, a.ldc, a.sc, a.batch, false};
     const int64_t tiles64 = (int64_t)((a.m + 63) / 64) * ((a.n + 63) / 64);
     switch (kern) {
         case K_LDS:
@@ -366,15 +366,31 @@ tile::Shape acc_tile_form(const sgemm_emu::AccArgs& a, tile::Problem& p) {
     // 64 x 64 tile is empty (A^T B: 64 x 4096 x 32 x 1024 206 us against 236, 500
     // x 512 x 32 x 256 68 / 76; A^T B^T: 222 / 245, 71 / 72.  With fewer tiles,
     // 20 x 1730 x 32 x 788, 69 / 31; 33 columns, 200 x 1000 x 33 x 500, 142 / 111).
-    if (a.a_trans && !a.cd_col && (a.n <= 32 || (!a.b_trans && a.m <= 32)) &&
-        (int64_t)((a.m + 63) / 64) * ((a.n + 63) / 64) * a.batch >= 2048)
+    const int64_t tiles64 = (int64_t)((a.m + 63) / 64) * ((a.n + 63) / 64) * a.batch;
+    if (a.a_trans && !a.cd_col && (a.n <= 32 || (!a.b_trans && a.m <= 32)) && tiles64 >= 2048)
+        return tile::NONE;
+    // A^T B in large batches of small items whose whole 32-column blocks fill
+    // D's 128-byte lines, which wait for HBM too, where the tile shapes compute
+    // much twice or leave it out: 64 or 96 columns (500 x 768 x 96 x 64 75 us against
+    // 103, 1741 x 384 x 64 x 96 81 / 96, 11647 x 100 x 96 x 52 249 / 311, 8192 x 96^3
+    // 281 / 284), 128 or 192 rows and columns (2500 x 192^3 312 / 377), and 128 x 128
+    // in place (4096 x 128^3 187 / 201; apart 189 / 189, and without C 11367 x
+    // 128^3 394 / 381).  Not with fewer tiles (1399 x 96^3 125%, 2417 x 96^3 115%, 946 x
+    // 192^3 106%), other columns (8145 x 128 x 94 x 64 in unaligned rows 124%), a
+    // short k (14479 x 128 x 64 x 20 115%) or a long one.
+    const bool lines = (uintptr_t)a.D % 128 == 0 && a.ldd % 32 == 0 && a.sd % 32 == 0;
+    const bool narrow = a.m >= 96 && (a.n == 64 || a.n == 96) && tiles64 >= 12288;
+    const bool square = (a.m == 128 || a.m == 192) && (a.n == 128 || a.n == 192) &&
+                        (a.m != a.n || a.m == 192 || a.C == a.D) && tiles64 >= 9216;
+    if (a.a_trans && !a.b_trans && !a.cd_col && a.k >= 48 && a.k <= 256 && lines &&
+        (narrow || square))
         return tile::NONE;
     if (!a.cd_col)
         p = {a.m,  a.n,       a.k, a.A,   a.lda, a.sa, !a.a_trans, a.B,  a.ldb,
-             a.sb, a.b_trans, a.C, a.ldc, a.sc,  a.D,  a.ldd,      a.sd, a.batch};
+             a.sb, a.b_trans, a.C, a.ldc, a.sc,  a.D,  a.ldd,      a.sd, a.batch, true};
     else  // D^T = op(B)^T op(A)^T, and D^T is row-major
         p = {a.n,  a.m,        a.k, a.B,   a.ldb, a.sb, a.b_trans, a.A,  a.lda,
-             a.sa, !a.a_trans, a.C, a.ldc, a.sc,  a.D,  a.ldd,     a.sd, a.batch};
+             a.sa, !a.a_trans, a.C, a.ldc, a.sc,  a.D,  a.ldd,     a.sd, a.batch, true};
     return tile::choose(p);
 }
 

@@ -158,7 +158,7 @@ Shape choose(const Problem& p) {
 
 Shape far_rows(const Problem& p) {
     const Cost& c = kCosts[T128x256];
-    if (p.C != nullptr || !p.a_kc || p.b_kc || offsets_fit(true, c.bm, p.ldd + c.bn)) return NONE;
+    if (p.acc || !p.a_kc || p.b_kc || offsets_fit(true, c.bm, p.ldd + c.bn)) return NONE;
     Problem near = p;
     near.ldd = p.n;
     return choose(near) != NONE && fits(c, near) ? T128x256_FAR : NONE;
@@ -168,8 +168,9 @@ hipError_t launch(const Problem& p, Shape shape, hipStream_t stream) {
     if (shape == T128x256_FAR)
         return launch_cfg<Cfg<128, 256, 2, 4, 1, 2, true, false, false, false, true>>(p, stream);
     if (shape == NONE) return hipErrorInvalidValue;
+    if (!p.acc && (!p.a_kc || p.b_kc || p.C)) return hipErrorInvalidValue;
     if (p.a_kc && !p.b_kc)
-        return p.C ? launch_shape<true, false, true>(p, shape, stream)
+        return p.acc ? launch_shape<true, false, true>(p, shape, stream)
                    : launch_shape<true, false, false>(p, shape, stream);
     if (p.a_kc) return launch_shape<true, true, true>(p, shape, stream);
     return p.b_kc ? launch_shape<false, true, true>(p, shape, stream)

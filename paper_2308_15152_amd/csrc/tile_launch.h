@@ -26,6 +26,7 @@ struct Problem {
     float* D;
     int64_t ldd, sd;
     int batch;
+    bool acc;  // accumulate form: its instances, also where C is null
 };
 
 // Workgroup tile and number of wave groups that share its k chunks.

@@ -189,6 +189,39 @@ def test_batch_past_one_launch():
     assert_periodic(D, P, "acc batch")
 
 
+# The products the automatic choice leaves to this kernel in its 32x32x16 form
+# with error correction: A transposed and at most 32 columns or rows, and large
+# batches of small items (their tests on the host name the limits).
+ROUTED = [(2048, 50, 17, 33), (1100, 65, 32, 100), (2100, 20, 33, 40), (6144, 100, 64, 60),
+          (2100, 160, 96, 50), (2050, 192, 128, 64), (2050, 128, 192, 77), (1366, 192, 192, 256)]
+
+
+@pytest.mark.parametrize("shape", ROUTED, ids=lambda s: "x".join(map(str, s)))
+def test_products_left_to_this_kernel(shape):
+    """C apart, in place (the same bits) and none, against the oracle on items
+    over the batch, every output written."""
+    batch, m, n, k = shape
+    print(f"case acc routed {shape}", flush=True)
+    dev = device()
+    g = synth.rng(sum(shape))
+    A, B, C = (synth.uniform((batch, r, c), g) for r, c in ((k, m), (k, n), (m, n)))
+    Ad, Bd, Cd = A.to(dev), B.to(dev), C.to(dev)
+    D = nan_output((batch, m, n))
+    assert pkg.sgemm_emu_acc_launch_form(Ad, Bd, Cd, D, op_a=pkg.OP_T)[0] == "gemm_acc_kernel"
+    pkg.sgemm_emu_batched_acc(Ad, Bd, Cd, D, op_a=pkg.OP_T)
+    assert_all_finite(D, f"acc routed {shape}")
+    items = spread_items(batch, 16)
+    it = torch.from_numpy(items).to(dev)
+    ref = oracle.gemm_acc(A[items].numpy(), B[items].numpy(), C[items].numpy(), "T", "N")
+    gate(to_np(D[it]), ref, k, f"acc routed {shape}", max_gate=gate_applies(ref))
+    assert pkg.sgemm_emu_acc_launch_form(Ad, Bd, Cd, Cd, op_a=pkg.OP_T)[0] == "gemm_acc_kernel"
+    pkg.sgemm_emu_batched_acc(Ad, Bd, Cd, Cd, op_a=pkg.OP_T)
+    assert torch.equal(Cd, D)
+    pkg.sgemm_emu_batched_acc(Ad, Bd, None, D, op_a=pkg.OP_T)
+    ref = oracle.gemm(A[items].numpy().transpose(0, 2, 1).copy(), B[items].numpy())
+    gate(to_np(D[it]), ref, k, f"acc routed, no C {shape}", max_gate=gate_applies(ref))
+
+
 def _random_shapes(n, seed):
     g = np.random.default_rng(seed)
     return [(int(g.integers(1, 4)), int(g.integers(1, 200)), int(g.integers(1, 200)),

@@ -36,7 +36,8 @@ def acc_form(m, n, k, batch=1, ta=0, tb=0, col=0, c=True, shape=pkg.SHAPE_32x32x
     kern, form = ctypes.c_char_p(), (ctypes.c_int * 3)()
     o = 4 * offset
     rc = pkg.load().sgemm_emu_acc_launch_form(
-        ta, tb, col, m, n, k, PA + o, lda, PB + o, ldb, PC + o if c else None, ldd, PD + o, ldd,
+        ta, tb, col, m, n, k, PA + o, lda, PB + o, ldb,
+        None if not c else PD + o if c == "D" else PC + o, ldd, PD + o, ldd,
         batch, st, shape, ec, ctypes.byref(kern), form)
     return rc, (kern.value or b"").decode(), tuple(form)
 
@@ -112,3 +113,23 @@ def test_far_rows():
     # other products with far rows go to the kernels with 64-bit addresses
     assert gemm_form(300, 300, 400, ldc=1 << 23)[1] == "bgemm_reg_kernel"
     assert gemm_form(300, 300, 401, ldc=1 << 23)[1] == "bgemm_emu_kernel"
+
+
+@pytest.mark.parametrize("m,n,k,batch,apart,in_place", [
+    (128, 128, 128, 2304, 0, 1), (128, 128, 128, 2303, 0, 0),   # 9216 tiles of 64 x 64
+    (192, 192, 256, 1024, 1, 1), (192, 192, 256, 1023, 0, 0), (192, 192, 257, 1400, 0, 0),
+    (192, 224, 128, 1400, 0, 0), (224, 192, 128, 1400, 0, 0), (192, 128, 128, 2100, 1, 1),
+    (160, 160, 100, 8000, 0, 0), (224, 96, 128, 1536, 1, 1), (224, 96, 128, 1535, 0, 0),
+    (4000, 64, 48, 200, 1, 1), (4000, 64, 47, 200, 0, 0), (95, 64, 100, 8000, 0, 0),
+    (96, 64, 100, 8000, 1, 1), (128, 80, 100, 8000, 0, 0)])
+def test_accumulate_route_of_transposed_batches(m, n, k, batch, apart, in_place):
+    """Large batches of small A^T B products stay on the kernel written with
+    the fragment interface, by sizes, by the alignment of D and by whether C is
+    D; with B transposed or column-major D they don't."""
+    name = ("gemm_tile_kernel", "gemm_acc_kernel")
+    assert acc_form(m, n, k, batch, ta=1)[1] == name[apart]
+    assert acc_form(m, n, k, batch, ta=1, c=False)[1] == name[apart]
+    assert acc_form(m, n, k, batch, ta=1, c="D")[1] == name[in_place]
+    for kw in ({"tb": 1}, {"col": 1}, {"pad": 4}, {"offset": 1}):
+        assert acc_form(m, n, k, batch, ta=1, c="D", **kw)[1] == "gemm_tile_kernel"
+    assert acc_form(m, n, k, batch, c="D")[1] == "gemm_tile_kernel"
