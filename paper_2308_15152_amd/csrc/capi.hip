@@ -281,6 +281,24 @@ tile::Shape tile_form(const sgemm_emu::GemmArgs& a, Kernel kern, int resolved, t
                 if (tiles128 >= 256 && (a.m <= 32 || (a.m <= 128 && a.n <= 128)))
                     return tile::NONE;
             }
+            // And where its waves move rows of 512 bytes (B, C) and the device is
+            // filled several times over.  Products between one and two 64 x 64
+            // tiles wide or high, which the tile kernel computes twice, up to k =
+            // 319 (9911 x 116^3 360 us against 550, 1045 x 110 x 1024 x 64 187 / 306,
+            // 237 x 71 x 2044 x 308 216 / 315; by k, 64 to 319, 0.73 to 0.93 of the time,
+            // beyond 0.96 to 1.1; with 512 to 1535 tiles 0.93 to 1.3).  Others up to
+            // k = 127 if C's rows are no whole 128-byte lines and all of C stays in
+            // the last-level cache (15 x 2938 x 768 x 64 35 / 46, 60 x 356 x 1432 x 128
+            // 54 / 60; 0.87 to 0.95, beyond k = 127 0.95 to 1.2; 47 x 351 x 3832 x 92,
+            // 253 MB of C, 139 / 100).
+            if (a.vec_b && a.n % 4 == 0 && tiles64 * a.batch >= 1536) {
+                const int side = a.m < a.n ? a.m : a.n;
+                const bool lines =
+                    (uintptr_t)a.C % 128 == 0 && a.ldc % 32 == 0 && a.sc % 32 == 0;
+                const bool cached = (double)a.m * a.n * a.batch <= 56e6;  // 224 MB
+                if (side > 64 && (side < 128 ? a.k < 320 : a.k < 128 && !lines && cached))
+                    return tile::NONE;
+            }
             break;
         case K_BIG: {
             // Up to two rounds of full tiles: smaller ones, or waves that

@@ -133,3 +133,21 @@ def test_accumulate_route_of_transposed_batches(m, n, k, batch, apart, in_place)
     for kw in ({"tb": 1}, {"col": 1}, {"pad": 4}, {"offset": 1}):
         assert acc_form(m, n, k, batch, ta=1, c="D", **kw)[1] == "gemm_tile_kernel"
     assert acc_form(m, n, k, batch, c="D")[1] == "gemm_tile_kernel"
+
+
+@pytest.mark.parametrize("m,n,k,batch,register_flow", [
+    (116, 116, 128, 384, True), (116, 116, 128, 383, False),      # 1536 tiles of 64 x 64
+    (116, 116, 316, 1000, True), (116, 116, 320, 1000, False), (110, 1024, 316, 100, True),
+    (64, 1024, 100, 100, False), (128, 1024, 100, 100, False), (1024, 104, 124, 100, True),
+    (2025, 2300, 124, 11, True), (2025, 2300, 128, 11, False), (2025, 2304, 64, 11, False),
+    (1000, 300, 88, 186, True), (1000, 300, 88, 187, False), (1000, 302, 88, 40, False),
+    (1000, 301, 88, 40, False)])
+def test_short_products_left_to_the_register_flow(m, n, k, batch, register_flow):
+    """Ragged products of short k that fill the device, with 16-byte rows of B,
+    by sizes and by the alignment of C's rows."""
+    expect = "bgemm_reg_kernel" if register_flow else "gemm_tile_kernel"
+    assert gemm_form(m, n, k, batch)[1] == expect
+    if register_flow:
+        assert gemm_form(m, n, k, batch) == (0, expect, (128, 128, 1))
+        # unaligned operands go to the tile kernel
+        assert gemm_form(m, n, k, batch, offset=1)[1] == "gemm_tile_kernel"
