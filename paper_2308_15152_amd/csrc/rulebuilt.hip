@@ -403,7 +403,8 @@ struct Rows {
     }
 };
 
-template <class Rule, int CB, bool PAIR, bool FAR, bool LINES>
+// AHEAD: see below.
+template <class Rule, int CB, bool PAIR, bool FAR, bool LINES, bool AHEAD = CB == 1>
 __device__ __forceinline__ void rule64_group(const RuleParams& p, const Rule& rule, int64_t item,
                                              int c0) {
     const int l = threadIdx.x & 63;
@@ -413,10 +414,11 @@ __device__ __forceinline__ void rule64_group(const RuleParams& p, const Rule& ru
     C.init(p.C + item * p.sc + c0, p.ldc, 4 * (l >> 5), p.ncols - c0);
 
     // B of the whole group: lane l holds rows 16 s + 8 (l / 32) + e of k step s.
-    // With one block all of it goes out ahead of the products (the scheduling
-    // barrier keeps it there: 262,144 items of 24 columns 585 us against 621);
-    // with two the scheduler's order, one k step at a time, is the better one
-    // (64 columns 1536 us against 1663).
+    // With one block (AHEAD) all of it goes out ahead of the products (the
+    // scheduling barrier keeps it there: 262,144 items of 24 columns 585 us
+    // against 621); with two the scheduler's order, one k step at a time, is the
+    // better one (64 columns 1536 us against 1663), and for a last group of one
+    // block beside waves with two (32,336 items of 95 columns 309 against 369).
     float x[4][CB][8];
 #pragma unroll
     for (int s = 0; s < 4; ++s)
@@ -427,7 +429,7 @@ __device__ __forceinline__ void rule64_group(const RuleParams& p, const Rule& ru
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb) x[s][cb][e] = v[cb];
         }
-    if constexpr (CB == 1) __builtin_amdgcn_sched_barrier(0);
+    if constexpr (AHEAD) __builtin_amdgcn_sched_barrier(0);
 
     f32x16_t acc[2][CB], cor[2][CB];
 #pragma unroll
@@ -470,8 +472,10 @@ __device__ inline int xcd_blocks(int b, int G) {
     return (b | 255) < G ? (b & ~255) + (b & 7) * 32 + ((b & 255) >> 3) : b;
 }
 
-// CB: 32-column blocks of a wave's group; a last group of up to 32 columns
-// takes one.
+// CB: 32-column blocks of a wave's group.  A last group of up to 32 columns
+// takes one block, unless its rows are read in pairs: those pieces of B and C
+// lines are best moved in the same step as their neighbours (32,680 items of
+// 94 columns 306 us, with one block 441).
 template <class Rule, int CB, bool PAIR, bool FAR, bool LINES>
 __device__ __forceinline__ void rule64_body(const RuleParams& p, unsigned char* lds) {
     // wave index as a wave-uniform (scalar) value, so that the per-item base
@@ -490,7 +494,8 @@ __device__ __forceinline__ void rule64_body(const RuleParams& p, unsigned char* 
     const int64_t item = local + p.item0;
     Rule rule;
     rule.init(p, item, lds);
-    if (CB > 1 && p.ncols - c0 <= 32) rule64_group<Rule, 1, false, FAR, LINES>(p, rule, item, c0);
+    if (CB > 1 && !PAIR && p.ncols - c0 <= 32)
+        rule64_group<Rule, 1, false, FAR, LINES, false>(p, rule, item, c0);
     else rule64_group<Rule, CB, PAIR, FAR, LINES>(p, rule, item, c0);
 }
 
@@ -548,13 +553,26 @@ bool whole_lines(const RuleParams& p) {
            p.ldc % 32 == 0 && p.sb % 32 == 0 && p.sc % 32 == 0 && p.ncols % 32 == 0;
 }
 
+// Bytes of B and C.
+double bytes(const RuleParams& p, int64_t batch) {
+    return 256.0 * p.ncols * (batch + (p.sb ? batch : 1));
+}
+
+// Whether the columns of an even number are read in pairs: not where the
+// second group of 65 to 96 columns, half empty in pairs, comes from the caches
+// (614 items of 80 columns, 24 MB, 7.3 us against 8.0 in pairs; 1228 items,
+// 48 MB, 12.5 / 12.3).
+bool pairs(const RuleParams& p, int64_t batch) {
+    return p.ncols % 2 == 0 && !(p.ncols > 64 && p.ncols <= 96 && bytes(p, batch) <= 40e6);
+}
+
 // Launches KERNEL(CB, PAIR, FAR, LINES), a kernel instance, by shape and
 // strides.
 #define SGEMM_EMU_RULE_LAUNCH(KERNEL)                                                          \
     (!near(p)           ? launch_rule(KERNEL(2, false, true, false), 64, p, batch, stream)     \
      : p.ncols <= 32    ? launch_rule(KERNEL(1, false, false, false), 32, p, batch, stream)    \
      : whole_lines(p)   ? launch_rule(KERNEL(2, true, false, true), 64, p, batch, stream)      \
-     : p.ncols % 2 == 0 ? launch_rule(KERNEL(2, true, false, false), 64, p, batch, stream)     \
+     : pairs(p, batch)  ? launch_rule(KERNEL(2, true, false, false), 64, p, batch, stream)     \
                         : launch_rule(KERNEL(2, false, false, false), 64, p, batch, stream))
 
 // The rotation planes (i, j) with a compile-time instance of the Givens

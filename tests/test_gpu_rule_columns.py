@@ -13,7 +13,7 @@ import torch
 import oracle
 import paper_2308_15152_amd as pkg
 import synth
-from gpu_util import device, gate, to_np
+from gpu_util import assert_all_finite, device, gate, nan_output, spread_items, to_np
 
 pytestmark = pytest.mark.gpu
 
@@ -61,6 +61,30 @@ def test_columns(ncols, pad, offset):
             pkg.givens_emu_batched(i, j, c.to(device()), s.to(device()), Bv, C, mode=mode)
             _untouched(fc, whole, ncols, offset)
             gate(to_np(C), ref, 2, f"givens {ncols} columns", max_gate=False)
+
+
+@pytest.mark.parametrize("mb", [39, 41])
+@pytest.mark.parametrize("ncols", [65, 66, 94, 96, 98, 158])
+def test_last_groups(ncols, mb):
+    """Batches on both sides of the 40 MB up to which 65 to 96 columns are not
+    read in pairs: items over the batch, every output written."""
+    batch = mb * 10 ** 6 // (512 * ncols)
+    print(f"case rule last group {ncols} batch={batch}", flush=True)
+    u, B = synth.householder_inputs(batch, 64, ncols, seed=400 + ncols)
+    c, s, _ = synth.givens_inputs(batch, 64, 1, seed=401 + ncols)
+    Bd, C = B.to(device()), nan_output((batch, 64, ncols))
+    items = spread_items(batch, 40)
+    it = torch.from_numpy(items).to(device())
+    pkg.householder_emu_batched(u.to(device()), Bd, C)
+    assert_all_finite(C, f"householder {ncols} columns")
+    gate(to_np(C[it]), oracle.householder(u[items].numpy(), B[items].numpy()), 64,
+         f"householder {ncols} columns", max_gate=False)
+    for i, j in ((5, 37), (62, 17)):
+        C.fill_(float("nan"))
+        pkg.givens_emu_batched(i, j, c.to(device()), s.to(device()), Bd, C)
+        assert_all_finite(C, f"givens {ncols} columns")
+        ref = oracle.givens(i, j, c[items].numpy(), s[items].numpy(), B[items].numpy())
+        gate(to_np(C[it]), ref, 2, f"givens {ncols} columns", max_gate=False)
 
 
 @pytest.mark.parametrize("ld", [(1 << 22) - 1, 1 << 22, (1 << 22) + 1])
