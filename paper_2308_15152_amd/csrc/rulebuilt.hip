@@ -334,10 +334,10 @@ constexpr uint32_t kPastEnd = 0x80000000;  // no buffer offset in use reaches th
 
 // One B or C item from column c0 on: rows ld apart, the lane's first column
 // (and, PAIR, its neighbour) or both of its columns.
-template <int CB, bool PAIR, bool FAR, bool LINES>
+template <int CB, bool PAIR, bool FAR, int STREAM>
 struct Rows {
-    // streaming accesses: neither B nor C is touched twice
-    static constexpr int kCache = LINES ? 2 : 0;
+    // cache policies: nontemporal, as neither B nor C is touched twice here
+    static constexpr int kLoad = STREAM == 2 ? 2 : 0, kStore = STREAM ? 2 : 0;
 
     float* p;
     int64_t ld;
@@ -373,14 +373,14 @@ struct Rows {
             }
         } else if constexpr (PAIR) {
             const f32x2 v = __builtin_bit_cast(
-                f32x2, __builtin_amdgcn_raw_buffer_load_b64(rsrc(), off[0], s, kCache));
+                f32x2, __builtin_amdgcn_raw_buffer_load_b64(rsrc(), off[0], s, kLoad));
             x[0] = v[0];
             x[1] = v[1];
         } else {
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb)
                 x[cb] = __builtin_bit_cast(
-                    float, __builtin_amdgcn_raw_buffer_load_b32(rsrc(), off[cb], s, kCache));
+                    float, __builtin_amdgcn_raw_buffer_load_b32(rsrc(), off[cb], s, kLoad));
         }
     }
 
@@ -393,22 +393,22 @@ struct Rows {
                 if (ok[cb]) p[row * ld + off[PAIR ? 0 : cb] + (PAIR ? cb : 0)] = x[cb];
         } else if constexpr (PAIR) {
             __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, f32x2{x[0], x[1]}),
-                                                  rsrc(), off[0], s, kCache);
+                                                  rsrc(), off[0], s, kStore);
         } else {
 #pragma unroll
             for (int cb = 0; cb < CB; ++cb)
                 __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x[cb]), rsrc(),
-                                                      off[cb], s, kCache);
+                                                      off[cb], s, kStore);
         }
     }
 };
 
 // AHEAD: see below.
-template <class Rule, int CB, bool PAIR, bool FAR, bool LINES, bool AHEAD = CB == 1>
+template <class Rule, int CB, bool PAIR, bool FAR, int STREAM, bool AHEAD = CB == 1>
 __device__ __forceinline__ void rule64_group(const RuleParams& p, const Rule& rule, int64_t item,
                                              int c0) {
     const int l = threadIdx.x & 63;
-    Rows<CB, PAIR, FAR, LINES> B, C;
+    Rows<CB, PAIR, FAR, STREAM> B, C;
     // operand rows 8 (l / 32) + .., accumulator rows 4 (l / 32) + ..
     B.init(const_cast<float*>(p.B + item * p.sb + c0), p.ldb, 8 * (l >> 5), p.ncols - c0);
     C.init(p.C + item * p.sc + c0, p.ldc, 4 * (l >> 5), p.ncols - c0);
@@ -476,7 +476,7 @@ __device__ inline int xcd_blocks(int b, int G) {
 // takes one block, unless its rows are read in pairs: those pieces of B and C
 // lines are best moved in the same step as their neighbours (32,680 items of
 // 94 columns 306 us, with one block 441).
-template <class Rule, int CB, bool PAIR, bool FAR, bool LINES>
+template <class Rule, int CB, bool PAIR, bool FAR, int STREAM>
 __device__ __forceinline__ void rule64_body(const RuleParams& p, unsigned char* lds) {
     // wave index as a wave-uniform (scalar) value, so that the per-item base
     // pointers live in SGPRs
@@ -495,31 +495,31 @@ __device__ __forceinline__ void rule64_body(const RuleParams& p, unsigned char* 
     Rule rule;
     rule.init(p, item, lds);
     if (CB > 1 && !PAIR && p.ncols - c0 <= 32)
-        rule64_group<Rule, 1, false, FAR, LINES, false>(p, rule, item, c0);
-    else rule64_group<Rule, CB, PAIR, FAR, LINES>(p, rule, item, c0);
+        rule64_group<Rule, 1, false, FAR, STREAM, false>(p, rule, item, c0);
+    else rule64_group<Rule, CB, PAIR, FAR, STREAM>(p, rule, item, c0);
 }
 
 // One block per wave leaves registers for four waves per SIMD.
-template <int CB, bool PAIR, bool FAR, bool LINES>
+template <int CB, bool PAIR, bool FAR, int STREAM>
 __global__ __launch_bounds__(64 * kWaves, CB == 1 ? 4 : 2) void householder64_kernel(RuleParams p) {
-    rule64_body<HouseholderRule, CB, PAIR, FAR, LINES>(p, nullptr);
+    rule64_body<HouseholderRule, CB, PAIR, FAR, STREAM>(p, nullptr);
 }
 
-template <int CB, bool PAIR, bool FAR, bool LINES>
+template <int CB, bool PAIR, bool FAR, int STREAM>
 __global__ __launch_bounds__(64 * kWaves, 2) void householder64_lds_kernel(RuleParams p) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[kWaves][2 * 64 * 128];
-    rule64_body<HouseholderLdsRule, CB, PAIR, FAR, LINES>(p, lds[threadIdx.x >> 6]);
+    rule64_body<HouseholderLdsRule, CB, PAIR, FAR, STREAM>(p, lds[threadIdx.x >> 6]);
 }
 
-template <class Rule, int CB, bool PAIR, bool FAR, bool LINES>
+template <class Rule, int CB, bool PAIR, bool FAR, int STREAM>
 __global__ __launch_bounds__(64 * kWaves, CB == 1 ? 4 : 2) void givens64_kernel(RuleParams p) {
-    rule64_body<Rule, CB, PAIR, FAR, LINES>(p, nullptr);
+    rule64_body<Rule, CB, PAIR, FAR, STREAM>(p, nullptr);
 }
 
-template <int CB, bool PAIR, bool FAR, bool LINES>
+template <int CB, bool PAIR, bool FAR, int STREAM>
 __global__ __launch_bounds__(64 * kWaves, 2) void givens64_lds_kernel(RuleParams p) {
     __shared__ __attribute__((aligned(16))) unsigned char lds[kWaves][2 * 64 * 128];
-    rule64_body<GivensLdsRule, CB, PAIR, FAR, LINES>(p, lds[threadIdx.x >> 6]);
+    rule64_body<GivensLdsRule, CB, PAIR, FAR, STREAM>(p, lds[threadIdx.x >> 6]);
 }
 
 // Launch `kernel` over the batch in pieces below 2^31 work-items (the
@@ -545,17 +545,24 @@ hipError_t launch_rule(K kernel, int cols, RuleParams p, int64_t batch, hipStrea
 // Byte offsets of 64 rows and 64 columns below kPastEnd.
 bool near(const RuleParams& p) { return p.ldb < (1 << 22) && p.ldc < (1 << 22); }
 
-// Whether B's and C's rows are whole 128-byte lines: they are then streamed
-// past the caches.  Otherwise the pieces of a line meet there (40,000 items of
-// 444 columns 1690 us against 2263 streamed).
-bool whole_lines(const RuleParams& p) {
-    return ((uintptr_t)p.B % 128 == 0) && ((uintptr_t)p.C % 128 == 0) && p.ldb % 32 == 0 &&
-           p.ldc % 32 == 0 && p.sb % 32 == 0 && p.sc % 32 == 0 && p.ncols % 32 == 0;
-}
-
 // Bytes of B and C.
 double bytes(const RuleParams& p, int64_t batch) {
     return 256.0 * p.ncols * (batch + (p.sb ? batch : 1));
+}
+
+// What of B and C is streamed past the caches where their rows are whole
+// 128-byte lines (otherwise the pieces of a line meet there: 40,000 items of 444
+// columns 1690 us against 2263 streamed).  0: nothing; 1: the stores, up to the
+// 256 MiB of the last-level cache, which may hold B from the kernel that wrote
+// it (1536 items of 64 columns, 48 MB: B in the cache 8.4 us, with streaming loads
+// 10.4, nothing streamed 9.5; B not there 12.0 / 11.5 / 13.8; 7680 items, 240 MB,
+// 38 / 46 / 38 and 49 / 51 / 53); 2: the loads too beyond (320 MB 62 us against
+// 71 with nothing streamed).
+int streams(const RuleParams& p, int64_t batch) {
+    const bool lines = ((uintptr_t)p.B % 128 == 0) && ((uintptr_t)p.C % 128 == 0) &&
+                       p.ldb % 32 == 0 && p.ldc % 32 == 0 && p.sb % 32 == 0 && p.sc % 32 == 0 &&
+                       p.ncols % 32 == 0;
+    return !lines ? 0 : bytes(p, batch) > double(1 << 28) ? 2 : 1;
 }
 
 // Whether the columns of an even number are read in pairs: not where the
@@ -566,14 +573,15 @@ bool pairs(const RuleParams& p, int64_t batch) {
     return p.ncols % 2 == 0 && !(p.ncols > 64 && p.ncols <= 96 && bytes(p, batch) <= 40e6);
 }
 
-// Launches KERNEL(CB, PAIR, FAR, LINES), a kernel instance, by shape and
+// Launches KERNEL(CB, PAIR, FAR, STREAM), a kernel instance, by shape and
 // strides.
-#define SGEMM_EMU_RULE_LAUNCH(KERNEL)                                                          \
-    (!near(p)           ? launch_rule(KERNEL(2, false, true, false), 64, p, batch, stream)     \
-     : p.ncols <= 32    ? launch_rule(KERNEL(1, false, false, false), 32, p, batch, stream)    \
-     : whole_lines(p)   ? launch_rule(KERNEL(2, true, false, true), 64, p, batch, stream)      \
-     : pairs(p, batch)  ? launch_rule(KERNEL(2, true, false, false), 64, p, batch, stream)     \
-                        : launch_rule(KERNEL(2, false, false, false), 64, p, batch, stream))
+#define SGEMM_EMU_RULE_LAUNCH(KERNEL)                                                           \
+    (!near(p)                 ? launch_rule(KERNEL(2, false, true, 0), 64, p, batch, stream)    \
+     : p.ncols <= 32          ? launch_rule(KERNEL(1, false, false, 0), 32, p, batch, stream)   \
+     : streams(p, batch) == 2 ? launch_rule(KERNEL(2, true, false, 2), 64, p, batch, stream)    \
+     : streams(p, batch) == 1 ? launch_rule(KERNEL(2, true, false, 1), 64, p, batch, stream)    \
+     : pairs(p, batch)        ? launch_rule(KERNEL(2, true, false, 0), 64, p, batch, stream)    \
+                              : launch_rule(KERNEL(2, false, false, 0), 64, p, batch, stream))
 
 // The rotation planes (i, j) with a compile-time instance of the Givens
 // kernel.
@@ -581,7 +589,7 @@ bool pairs(const RuleParams& p, int64_t batch) {
 
 template <class Rule>
 hipError_t launch_givens(const RuleParams& p, int64_t batch, hipStream_t stream) {
-#define SGEMM_EMU_KERNEL(CB, PAIR, FAR, LINES) givens64_kernel<Rule, CB, PAIR, FAR, LINES>
+#define SGEMM_EMU_KERNEL(CB, PAIR, FAR, STREAM) givens64_kernel<Rule, CB, PAIR, FAR, STREAM>
     return SGEMM_EMU_RULE_LAUNCH(SGEMM_EMU_KERNEL);
 #undef SGEMM_EMU_KERNEL
 }
@@ -608,8 +616,8 @@ hipError_t launch_householder64(const HouseholderArgs& a, hipStream_t stream) {
     p.ldc = a.ldc;
     p.sc = a.sc;
     const int64_t batch = a.batch;
-#define SGEMM_EMU_KERNEL(CB, PAIR, FAR, LINES) householder64_kernel<CB, PAIR, FAR, LINES>
-#define SGEMM_EMU_LDS_KERNEL(CB, PAIR, FAR, LINES) householder64_lds_kernel<CB, PAIR, FAR, LINES>
+#define SGEMM_EMU_KERNEL(CB, PAIR, FAR, STREAM) householder64_kernel<CB, PAIR, FAR, STREAM>
+#define SGEMM_EMU_LDS_KERNEL(CB, PAIR, FAR, STREAM) householder64_lds_kernel<CB, PAIR, FAR, STREAM>
     if (a.mode == SGEMM_EMU_HOUSEHOLDER_LDS) return SGEMM_EMU_RULE_LAUNCH(SGEMM_EMU_LDS_KERNEL);
     return SGEMM_EMU_RULE_LAUNCH(SGEMM_EMU_KERNEL);
 #undef SGEMM_EMU_KERNEL
@@ -638,7 +646,7 @@ hipError_t launch_givens64(const GivensArgs& a, hipStream_t stream) {
 #undef SGEMM_EMU_GIVENS_CASE
         return hipErrorInvalidValue;
     }
-#define SGEMM_EMU_LDS_KERNEL(CB, PAIR, FAR, LINES) givens64_lds_kernel<CB, PAIR, FAR, LINES>
+#define SGEMM_EMU_LDS_KERNEL(CB, PAIR, FAR, STREAM) givens64_lds_kernel<CB, PAIR, FAR, STREAM>
     if (a.mode == SGEMM_EMU_GIVENS_LDS) return SGEMM_EMU_RULE_LAUNCH(SGEMM_EMU_LDS_KERNEL);
 #undef SGEMM_EMU_LDS_KERNEL
     return launch_givens<GivensArgRule>(p, batch, stream);

@@ -87,6 +87,26 @@ def test_last_groups(ncols, mb):
         gate(to_np(C[it]), ref, 2, f"givens {ncols} columns", max_gate=False)
 
 
+@pytest.mark.parametrize("batch", [8192, 8193])
+def test_streamed_rows(batch):
+    """64 columns on both sides of the 256 MiB up to which B is read through
+    the caches: all forms give what a padded call, never streamed, gives."""
+    print(f"case rule streamed batch={batch}", flush=True)
+    u, B = synth.householder_inputs(batch, 64, 64, seed=500)
+    c, s, _ = synth.givens_inputs(batch, 64, 1, seed=501)
+    ud, cd, sd, Bd = (x.to(device()) for x in (u, c, s, B))
+    padded = torch.empty((batch, 64, 65), device=device())[:, :, :64]
+    for call in (lambda C: pkg.householder_emu_batched(ud, Bd, C),
+                 lambda C: pkg.givens_emu_batched(5, 37, cd, sd, Bd, C),
+                 lambda C: pkg.givens_emu_batched(62, 17, cd, sd, Bd, C)):
+        C = nan_output((batch, 64, 64))
+        call(C)
+        call(padded)
+        assert torch.equal(C, padded)
+    ref = oracle.givens(62, 17, c[-9:].numpy(), s[-9:].numpy(), B[-9:].numpy())
+    gate(to_np(C[-9:]), ref, 2, "givens, streamed", max_gate=False)
+
+
 @pytest.mark.parametrize("ld", [(1 << 22) - 1, 1 << 22, (1 << 22) + 1])
 def test_far_rows(ld):
     """Row pitches on both sides of the 32-bit reach, on B and on C alone."""
