@@ -34,7 +34,8 @@
 // lane offset, which for a lane without a column lies past the descriptor's
 // end (its loads return zero, its stores are dropped).  Row pitches of 2^22
 // floats and more, which 32-bit offsets don't reach, take 64-bit pointers
-// (FAR).
+// (FAR; 20,000 items side by side in such rows of B, 32 / 64 / 94 / 65 columns 67 /
+// 133 / 214 / 191 us, two blocks of single columns for all 89 / 136 / 231 / 191).
 #include "internal.h"
 #include "mfmae/frag.hpp"
 #include "mfmae/tcec.hpp"
@@ -332,6 +333,8 @@ struct HouseholderLdsRule : LdsOperand {
 // ---------------------------------------------------------------------------
 constexpr uint32_t kPastEnd = 0x80000000;  // no buffer offset in use reaches this
 
+typedef f32x2 far_x2 __attribute__((aligned(4)));  // a pair in rows of any alignment
+
 // One B or C item from column c0 on: rows ld apart, the lane's first column
 // (and, PAIR, its neighbour) or both of its columns.
 template <int CB, bool PAIR, bool FAR, int STREAM>
@@ -341,7 +344,8 @@ struct Rows {
 
     float* p;
     int64_t ld;
-    uint32_t off[CB];  // bytes from the item's corner to (lane row, column); FAR: floats
+    uint32_t off[CB];  // bytes from the item's corner to (lane row, column)
+    int64_t far[CB];   // FAR: the same in floats
     bool ok[CB];
 
     // The lane's rows are `row` and what a scalar row offset adds to it.
@@ -353,10 +357,11 @@ struct Rows {
         for (int cb = 0; cb < CB; ++cb) {
             const int col = PAIR ? 2 * j : 32 * cb + j;
             ok[cb] = col < ncols;
-            if constexpr (FAR) off[cb] = (uint32_t)col;
+            // a lane without a column reads the last one (and stores nothing),
+            // without a branch; with two single columns a test per load is faster
+            if constexpr (FAR) far[cb] = row * ld + (ok[cb] ? col : ncols - (PAIR ? 2 : 1));
             else off[cb] = ok[cb] ? (uint32_t)(row * ld + col) * 4u : kPastEnd;
         }
-        if constexpr (FAR) p += row * ld;
     }
 
     __device__ __amdgpu_buffer_rsrc_t rsrc() const {
@@ -367,9 +372,15 @@ struct Rows {
         const int s = (int)((uint32_t)ld * 4u * (uint32_t)row);
         if constexpr (FAR) {
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb) {
-                const float* q = p + row * ld + off[PAIR ? 0 : cb] + (PAIR ? cb : 0);
-                x[cb] = ok[cb] ? *q : 0.0f;
+            for (int cb = 0; cb < CB; cb += PAIR ? 2 : 1) {
+                const float* q = (p + row * ld) + far[cb];
+                if constexpr (PAIR) {
+                    const far_x2 v = *reinterpret_cast<const far_x2*>(q);
+                    x[0] = v[0];
+                    x[1] = v[1];
+                } else {
+                    x[cb] = CB == 1 || ok[cb] ? *q : 0.0f;
+                }
             }
         } else if constexpr (PAIR) {
             const f32x2 v = __builtin_bit_cast(
@@ -389,8 +400,12 @@ struct Rows {
         const int s = (int)((uint32_t)ld * 4u * (uint32_t)row);
         if constexpr (FAR) {
 #pragma unroll
-            for (int cb = 0; cb < CB; ++cb)
-                if (ok[cb]) p[row * ld + off[PAIR ? 0 : cb] + (PAIR ? cb : 0)] = x[cb];
+            for (int cb = 0; cb < CB; cb += PAIR ? 2 : 1) {
+                float* q = (p + row * ld) + far[cb];
+                if (!ok[cb]) continue;
+                if constexpr (PAIR) *reinterpret_cast<far_x2*>(q) = far_x2{x[0], x[1]};
+                else *q = x[cb];
+            }
         } else if constexpr (PAIR) {
             __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(u32x2, f32x2{x[0], x[1]}),
                                                   rsrc(), off[0], s, kStore);
@@ -575,13 +590,17 @@ bool pairs(const RuleParams& p, int64_t batch) {
 
 // Launches KERNEL(CB, PAIR, FAR, STREAM), a kernel instance, by shape and
 // strides.
-#define SGEMM_EMU_RULE_LAUNCH(KERNEL)                                                           \
-    (!near(p)                 ? launch_rule(KERNEL(2, false, true, 0), 64, p, batch, stream)    \
-     : p.ncols <= 32          ? launch_rule(KERNEL(1, false, false, 0), 32, p, batch, stream)   \
-     : streams(p, batch) == 2 ? launch_rule(KERNEL(2, true, false, 2), 64, p, batch, stream)    \
-     : streams(p, batch) == 1 ? launch_rule(KERNEL(2, true, false, 1), 64, p, batch, stream)    \
-     : pairs(p, batch)        ? launch_rule(KERNEL(2, true, false, 0), 64, p, batch, stream)    \
+#define SGEMM_EMU_RULE_LAUNCH(KERNEL)                                                             \
+    (!near(p)                 ? SGEMM_EMU_RULE_FAR(KERNEL)                                        \
+     : p.ncols <= 32          ? launch_rule(KERNEL(1, false, false, 0), 32, p, batch, stream)     \
+     : streams(p, batch) == 2 ? launch_rule(KERNEL(2, true, false, 2), 64, p, batch, stream)      \
+     : streams(p, batch) == 1 ? launch_rule(KERNEL(2, true, false, 1), 64, p, batch, stream)      \
+     : pairs(p, batch)        ? launch_rule(KERNEL(2, true, false, 0), 64, p, batch, stream)      \
                               : launch_rule(KERNEL(2, false, false, 0), 64, p, batch, stream))
+#define SGEMM_EMU_RULE_FAR(KERNEL)                                                                \
+    (p.ncols <= 32            ? launch_rule(KERNEL(1, false, true, 0), 32, p, batch, stream)      \
+     : p.ncols % 2 == 0       ? launch_rule(KERNEL(2, true, true, 0), 64, p, batch, stream)       \
+                              : launch_rule(KERNEL(2, false, true, 0), 64, p, batch, stream))
 
 // The rotation planes (i, j) with a compile-time instance of the Givens
 // kernel.

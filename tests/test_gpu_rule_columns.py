@@ -107,16 +107,19 @@ def test_streamed_rows(batch):
     gate(to_np(C[-9:]), ref, 2, "givens, streamed", max_gate=False)
 
 
+@pytest.mark.parametrize("ncols", [24, 65, 70])
 @pytest.mark.parametrize("ld", [(1 << 22) - 1, 1 << 22, (1 << 22) + 1])
-def test_far_rows(ld):
-    """Row pitches on both sides of the 32-bit reach, on B and on C alone."""
-    print(f"case rule far rows ld={ld}", flush=True)
-    ncols = 70
+def test_far_rows(ld, ncols):
+    """Row pitches on both sides of the 32-bit reach, on B and on C alone, from
+    an odd base: one block, pairs and single columns through 64-bit pointers,
+    nothing written between the rows."""
+    print(f"case rule far rows ld={ld} ncols={ncols}", flush=True)
     u, B = synth.householder_inputs(1, 64, ncols, seed=300)
     c, s, _ = synth.givens_inputs(1, 64, 1, seed=301)
     dev = device()
-    far = torch.full((63 * ld + ncols,), float("nan"), device=dev)
-    farv = far.as_strided((1, 64, ncols), (0, ld, 1))
+    far = torch.full((63 * ld + ncols + 2,), float("nan"), device=dev)
+    farv = far.as_strided((1, 64, ncols), (0, ld, 1), 1)
+    between = (far.as_strided((64,), (ld,), 0), far.as_strided((64,), (ld,), ncols + 1))
     ref = oracle.householder(u.numpy(), B.numpy())
     refg = oracle.givens(3, 60, c.numpy(), s.numpy(), B.numpy())
     near = torch.empty((1, 64, ncols), device=dev)
@@ -124,6 +127,7 @@ def test_far_rows(ld):
     gate(to_np(farv), ref, 64, "householder, far C", max_gate=False)
     pkg.givens_emu_batched(3, 60, c.to(dev), s.to(dev), B.to(dev), farv)
     gate(to_np(farv), refg, 2, "givens, far C", max_gate=False)
+    assert all(bool(torch.isnan(x).all()) for x in between)
     farv.copy_(B)
     pkg.householder_emu_batched(u.to(dev), farv, near)
     gate(to_np(near), ref, 64, "householder, far B", max_gate=False)
