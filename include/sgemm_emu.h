@@ -403,7 +403,8 @@ int givens_emu_batched(int n, int i, int j,
  * totals.  X: rows x len, row stride ldx >= max(1, len); Y likewise with
  * ldy.  Y may be X itself (ldy == ldx) for an in-place scan; any other
  * overlap is an error.  Rows are independent; a wavefront scans 1 to 4 whole
- * rows, except that fewer than 512 rows of more than 15 blocks are cut into
+ * rows, or 32 rows of at most 32 values at a time (as the segments of one
+ * block), except that fewer than 512 rows of more than 15 blocks are cut into
  * parts scanned by a wavefront each (three launches on the stream, Y holding
  * the parts' totals in between).  Any alignment, at the same speed.  Any
  * number of rows: more than 33,554,428 wavefronts take several launches.

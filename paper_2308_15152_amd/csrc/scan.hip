@@ -24,8 +24,8 @@
 // a wave's whole rows form one sequence with the loads of the next kBuf
 // blocks in flight while the current one is multiplied.
 //
-// Rows (scan_kernel, one wave per 1 to 4 whole rows) fill the device when
-// there are many of them.  A few long rows are cut into parts instead, one
+// Rows (scan_kernel, one wave per 1 to 4 whole rows; scan_short_kernel, 32 rows
+// of up to 32 values at a time) fill the device when there are many of them.  A few long rows are cut into parts instead, one
 // wave each, in three launches on the stream that need no memory but Y:
 //   scan_total_kernel  each part's plain FP32 sum, left in the part's last
 //                      output;
@@ -121,13 +121,19 @@ __device__ inline void to_operand(const Raw& r, float* buf, Block& b) {
     }
 }
 
-// y = carry + scan of the block; carry becomes the row's running total
-// after it.  Accumulator element e of lane (n, g) is block value
-// 32 n + 8 (e / 4) + 4 g + e % 4.
-__device__ inline void scan_block(const Block& b, const half8_t (&Ut)[2], float& carry,
-                                  float (&y)[16]) {
-    const int l = threadIdx.x & 63;
-    const int n = l & 31;
+// U^T's diagonal block for k step s: element (i, kk) is [16 s + kk <= i];
+// hi only (lo is 0 for 0 and 1).
+__device__ inline void upper_ones(half8_t (&Ut)[2]) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+        mfmae::foreach_ij<FragA>([&](int e, int i, int kk) {
+            Ut[s][e] = (16 * s + kk <= i) ? (_Float16)1.0f : (_Float16)0.0f;
+        });
+}
+
+// Scans within the block's segments: accumulator element e of lane (n, g) is
+// value 8 (e / 4) + 4 g + e % 4 of segment n.
+__device__ inline void scan_segments(const Block& b, const half8_t (&Ut)[2], float (&z)[16]) {
     f32x16_t acc, cor;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
@@ -141,10 +147,19 @@ __device__ inline void scan_block(const Block& b, const half8_t (&Ut)[2], float&
         acc = __builtin_amdgcn_mfma_f32_32x32x16_f16(Ut[s], xh, acc, 0, 0, 0);
         cor = __builtin_amdgcn_mfma_f32_32x32x16_f16(Ut[s], xl, cor, 0, 0, 0);
     }
-    // scans within the segments
-    float z[16];
 #pragma unroll
     for (int e = 0; e < 16; ++e) z[e] = __builtin_fmaf(cor[e], mfmae::tcec::kLoScaleInv, acc[e]);
+}
+
+// y = carry + scan of the block; carry becomes the row's running total
+// after it.  Accumulator element e of lane (n, g) is block value
+// 32 n + 8 (e / 4) + 4 g + e % 4.
+__device__ inline void scan_block(const Block& b, const half8_t (&Ut)[2], float& carry,
+                                  float (&y)[16]) {
+    const int l = threadIdx.x & 63;
+    const int n = l & 31;
+    float z[16];
+    scan_segments(b, Ut, z);
     // segment totals: the last value of segment n is element 15 of lane
     // 32 + n; inclusive scan of the totals over n (both half-waves hold it)
     float incl = __shfl(z[15], 32 + n, 64);
@@ -190,14 +205,8 @@ __device__ inline void store_block(float* p, int count, const float (&y)[16], fl
 // wait before each block covers that block's loads only.
 __device__ __forceinline__ void scan_rows(const float* x, int64_t ldx, float* y, int64_t ldy, int nrows,
                                  int len, float carry0, float* sb) {
-    // U^T's diagonal block for k step s: element (i, kk) is [16 s + kk <= i];
-    // hi only (lo is 0 for 0 and 1).
     half8_t Ut[2];
-#pragma unroll
-    for (int s = 0; s < 2; ++s)
-        mfmae::foreach_ij<FragA>([&](int e, int i, int kk) {
-            Ut[s][e] = (16 * s + kk <= i) ? (_Float16)1.0f : (_Float16)0.0f;
-        });
+    upper_ones(Ut);
 
     const int nb = (len - 1) / kBlock + 1;  // blocks per run
     const int64_t nf = (int64_t)nrows * nb;
@@ -259,6 +268,69 @@ __global__ __launch_bounds__(64 * kWaves, 4) void scan_kernel(ScanArgs p, int ro
     if (r0 >= p.rows) return;  // whole wave; no barrier below
     scan_rows(p.X + r0 * p.ldx, p.ldx, p.Y + r0 * p.ldy, p.ldy,
               (int)min((int64_t)rows_per_wave, p.rows - r0), p.len, 0.0f, stage[wave]);
+}
+
+// Rows of at most one segment: 32 rows are the segments of one block, so a
+// wave scans them with the four products of a block and nothing crosses the
+// segments (1,000,000 rows of 1 / 8 / 32 values 13 / 16 / 44 us, a block per row
+// 431 / 424 / 426).  Loads and stores
+// go straight between memory and the operand and accumulator layouts, lane
+// (n, g) of row n, in 16-byte pieces of 4-byte alignment; what a piece holds of
+// the next row is dropped, and the descriptor ends with the last row.
+constexpr int kShort = 32;
+
+// Byte offsets of 32 rows stay below 2^31.
+inline bool short_rows(const ScanArgs& a) {
+    return a.len <= kShort && a.ldx < (1 << 24) && a.ldy < (1 << 24);
+}
+
+__global__ __launch_bounds__(64 * kWaves) void scan_short_kernel(ScanArgs p, int groups) {
+    constexpr uint32_t kPastEnd = 0x80000000;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int l = threadIdx.x & 63, n = l & 31, g = l >> 5;
+    half8_t Ut[2];
+    upper_ones(Ut);
+    for (int i = 0; i < groups; ++i) {
+        const int64_t r0 = (((int64_t)blockIdx.x * kWaves + wave) * groups + i) * 32;
+        if (r0 >= p.rows) return;
+        const int rows = (int)min((int64_t)32, p.rows - r0);
+        const bool row = n < rows;
+        const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
+            const_cast<float*>(p.X + r0 * p.ldx), 0, (int)(4 * ((rows - 1) * p.ldx + p.len)),
+            0x00020000);
+        Block b;
+#pragma unroll
+        for (int s = 0; s < 2; ++s)
+#pragma unroll
+            for (int h = 0; h < 2; ++h) {
+                const int c = 16 * s + 8 * g + 4 * h;
+                const f32x4 v = __builtin_bit_cast(
+                    f32x4, __builtin_amdgcn_raw_buffer_load_b128(
+                               rx, row && c < p.len ? 4 * (uint32_t)(n * p.ldx + c) : kPastEnd, 0,
+                               0));
+#pragma unroll
+                for (int e = 0; e < 4; ++e) b.x[s][4 * h + e] = c + e < p.len ? v[e] : 0.0f;
+            }
+        float z[16];
+        scan_segments(b, Ut, z);
+        const __amdgpu_buffer_rsrc_t ry = __builtin_amdgcn_make_buffer_rsrc(
+            p.Y + r0 * p.ldy, 0, (int)(4 * ((rows - 1) * p.ldy + p.len)), 0x00020000);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            const int c = 8 * q + 4 * g;
+            const uint32_t at = 4 * (uint32_t)(n * p.ldy + c);
+            // (0 + z: the offset of a row's first segment)
+            const u32x4 v = __builtin_bit_cast(u32x4, f32x4{0.0f + z[4 * q], 0.0f + z[4 * q + 1],
+                                                            0.0f + z[4 * q + 2],
+                                                            0.0f + z[4 * q + 3]});
+            const bool whole = row && c + 4 <= p.len;
+            __builtin_amdgcn_raw_buffer_store_b128(v, ry, whole ? at : kPastEnd, 0, 0);
+#pragma unroll
+            for (int e = 0; e < 3; ++e)
+                __builtin_amdgcn_raw_buffer_store_b32(
+                    v[e], ry, row && !whole && c + e < p.len ? at + 4 * e : kPastEnd, 0, 0);
+        }
+    }
 }
 
 // Part `part` of a row cut into parts of `blocks` blocks: its first value and
@@ -346,19 +418,39 @@ __global__ __launch_bounds__(64 * kWaves, 4) void scan_part_kernel(ScanArgs p, i
 
 }  // namespace
 
-// Rows a wave takes.  Short rows share the wave's set-up, and two rows of two
-// blocks fill its buffers; longer rows are better spread over more waves
-// (131,072 rows, 1 / 2 / 4 rows per wave: 100 values 72 / 70 / 59 us, 512
-// 82 / 80 / 77, 1000 175 / 187 / 192, 1500 278 / 290 / 310, 2048
-// 375 / 361 / 367; 65,536 rows of 4096: 362 / 366 / 407).
+// Rows a wave takes.  Short rows share the wave's set-up, and two rows that fill
+// two blocks its buffers; other rows are better spread over more waves
+// (131,072 rows, 1 / 2 / 4 rows per wave: 100 values 66 / 68 / 59 us, 512 88 /
+// 84 / 79, 1000 170 / 187 / 192, 1537 297 / 322 / 333, 1920 351 / 358, 1984
+// 359 / 358, 2000 372 / 369, 2040 407 / 435, 2048 369 to 382 / 360 to 363 / 364;
+// 65,536 rows of 4096: 362 / 366 / 407).
 static int64_t rows_per_wave(int64_t rows, int len) {
-    const int64_t best = len <= 512 ? 4 : len > 1536 && len <= 2048 ? 2 : 1;
+    const int64_t best = len <= 512 ? 4 : len > 2 * kBlock - kBlock / 16 && len <= 2 * kBlock ? 2 : 1;
     const int64_t fill = rows / 8192;  // and at least that many waves
     return fill < 1 ? 1 : fill < best ? fill : best;
 }
 
 hipError_t launch_scan(const ScanArgs& a, hipStream_t stream) {
     const int64_t nb = (a.len - 1) / kBlock + 1;
+    if (short_rows(a)) {
+        // up to 4 groups of 32 rows per wave, and at least 8192 waves
+        const int64_t all = (a.rows + 31) / 32;
+        const int64_t groups = all < 2 * 8192 ? 1 : all < 4 * 8192 ? 2 : 4;
+        // one launch stays below 2^31 work-items
+        const int64_t max_rows = ((int64_t(1) << 31) / (64 * kWaves) - 1) * kWaves * groups * 32;
+        for (int64_t r0 = 0; r0 < a.rows; r0 += max_rows) {
+            ScanArgs c = a;
+            c.rows = a.rows - r0 < max_rows ? a.rows - r0 : max_rows;
+            c.X = a.X + r0 * a.ldx;
+            c.Y = a.Y + r0 * a.ldy;
+            const int64_t per = 32 * groups * kWaves;
+            hipLaunchKernelGGL(scan_short_kernel, dim3((unsigned)((c.rows + per - 1) / per)),
+                               dim3(64 * kWaves), 0, stream, c, (int)groups);
+            const hipError_t e = hipGetLastError();
+            if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+    }
     // A wave takes about 1 us per block of its row whatever the others do, so
     // nb us for whole rows until they fill the device; in parts a scan takes
     // 16 us (three launches) or 1.5 times the whole rows' memory time, if

@@ -96,6 +96,42 @@ def test_values_outside_the_split(rows, value):
         assert np.array_equal(out[len(at) + 1:], plain[len(at) + 1:])
 
 
+@pytest.mark.parametrize("rows", [1, 31, 32, 33, 129, 5000, 600001])
+@pytest.mark.parametrize("length", [1, 2, 5, 7, 8, 9, 16, 17, 30, 32, 33])
+def test_short_rows(rows, length):
+    """Rows of at most one 32-value segment, 32 of them to a block (and the
+    first length past it), with padded rows off 16-byte alignment, in place
+    too: against the oracle, bit for bit the scan of whole blocks (which rows
+    2^24 floats apart still take), nothing written between the rows."""
+    print(f"case scan short rows={rows} len={length}", flush=True)
+    X = synth.uniform((rows, length), synth.rng(rows + 37 * length))
+    pitch = length + 3
+    xbuf = torch.full((rows * pitch + 1,), 7.0, device=device())
+    Xv = xbuf[1:].view(rows, pitch)[:, :length]
+    Xv.copy_(X)
+    ybuf = torch.full((rows * (pitch + 1) + 2,), 5.0, device=device())
+    Yv = ybuf[2:].view(rows, pitch + 1)[:, :length]
+    pkg.sgemm_emu_scan(Xv, Yv)
+    some = spread_items(rows, 2000) if rows > 2000 else np.arange(rows)
+    ref = oracle.scan(X[some].numpy())
+    gate(to_np(Yv[torch.from_numpy(some).to(device())]), ref, _k_eff(length),
+         f"scan {rows}x{length}", max_gate=False)
+    assert bool((ybuf[2:].view(rows, pitch + 1)[:, length:] == 5.0).all())
+    assert bool((ybuf[:2] == 5.0).all())
+    kept = Yv.clone()
+    pkg.sgemm_emu_scan(Xv, Xv)
+    assert torch.equal(Xv, kept)
+    assert bool((xbuf[1:].view(rows, pitch)[:, length:] == 7.0).all())
+    if rows in (33, 129) and length in (1, 9, 32):
+        far = torch.empty((rows - 1) * (1 << 24) + length, device=device())
+        Z = far.as_strided((rows, length), (1 << 24, 1))
+        Z.copy_(X)
+        pkg.sgemm_emu_scan(Z, Z)
+        assert torch.equal(Z, kept)
+        del far, Z
+        torch.cuda.empty_cache()
+
+
 @pytest.mark.parametrize("length", [3000, 4096])
 def test_integer_exact_and_in_place(length):
     X = synth.integer_matrix((70, length), synth.rng(5), -1000, 1000)
@@ -163,14 +199,16 @@ def test_workload_scan_sampled():
     print(f"scan_2048: err {e[0]:.3e} fp32 running sum {e[1]:.3e}")
 
 
-def test_rows_past_one_launch():
-    """More rows than one launch holds: a wave scans 8 rows, four waves a
-    workgroup, so a launch takes at most (2^31 / 256 - 1) * 32 = 268,435,424
-    rows and this scan needs two.  A pool of P rows is checked against the
-    oracle and repeated down the rows; every output row must equal its pool
-    row bitwise."""
-    P, length = 1021, 5
-    per_launch = ((1 << 31) // 256 - 1) * 32
+# A launch holds 2^31 / 256 - 1 workgroups of four waves, a wave 4 whole rows, or
+# 128 rows of at most 32 values.
+@pytest.mark.parametrize("length,per_wave", [(33, 4), (1, 128)])
+def test_rows_past_one_launch(length, per_wave):
+    """More rows than one launch holds.  A pool of P rows is checked against the
+    oracle and repeated down the rows; the rows on both sides of every launch
+    boundary are held to the bar and every output row must equal its pool row
+    bitwise."""
+    P = 1021
+    per_launch = ((1 << 31) // 256 - 1) * 4 * per_wave
     rows = per_launch + 2 * P + 7
     print(f"case scan rows={rows} len={length}", flush=True)
     X = synth.uniform((P, length), synth.rng(99))
@@ -179,8 +217,9 @@ def test_rows_past_one_launch():
     pkg.sgemm_emu_scan(Xd, Y)
     ref = oracle.scan(X.numpy())
     gate(to_np(Y[:P]), ref, _k_eff(length), "scan pool", max_gate=False)
-    gate_repeated(Y, ref, P, [per_launch - 1, per_launch, per_launch + 1, rows - 1],
+    bounds = range(per_launch, rows, per_launch)
+    gate_repeated(Y, ref, P, [r + d for r in bounds for d in (-1, 0, 1)] + [rows - 1],
                   _k_eff(length), "scan, launch boundary")
-    assert_periodic(Y, P, "scan rows")
+    assert_periodic(Y, P, "scan rows", slab_items=1 << 26)
     del Xd, Y
     torch.cuda.empty_cache()
