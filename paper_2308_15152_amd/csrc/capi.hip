@@ -129,13 +129,13 @@ int tile_cols(int tile) {
     return tile == SGEMM_EMU_TILE_128x256 ? 256 : tile == SGEMM_EMU_TILE_64x64 ? 64 : 128;
 }
 
-// Interior of whole tiles and whole 32-deep k chunks.
+// The part of C that whole tiles cover.
 struct Interior {
-    int m, n, k;
+    int m, n;
 };
 
 Interior interior(const sgemm_emu::GemmArgs& a, int tile) {
-    return {a.m - a.m % tile_rows(tile), a.n - a.n % tile_cols(tile), a.k - a.k % 32};
+    return {a.m - a.m % tile_rows(tile), a.n - a.n % tile_cols(tile)};
 }
 
 // Validate, then resolve the policy (flow and tile, AUTO replaced by the
@@ -182,12 +182,12 @@ int resolve_gemm(int m, int n, int k, const float* A, int lda, const float* B, i
                 sgemm_emu::big_supported(a, t, SGEMM_EMU_FLOW_SPLIT, ec == 1))
                 big_tile = t;
         const double work = (double)batch * m * n * k;  // multiply-adds (no overflow)
-        const double kDecompose = 34359738368.0;         // 2^35
+        const double kLarge = 34359738368.0;             // 2^35
         // nearly whole tiles: covering at least 95% of C, at least one per CU
         int tiled = SGEMM_EMU_TILE_AUTO;
         if (big_tile == SGEMM_EMU_TILE_AUTO && ec == 1 && tile == SGEMM_EMU_TILE_AUTO &&
             a.vec_a && a.vec_b && m > 1024 && n > 1024 && k >= 32 &&
-            work >= kDecompose && sgemm_emu::reg_flow_supported(a, SGEMM_EMU_TILE_64x64)) {
+            work >= kLarge && sgemm_emu::reg_flow_supported(a, SGEMM_EMU_TILE_64x64)) {
             for (int t : {order[0], order[1]}) {
                 const Interior in = interior(a, t);
                 const int64_t ntiles =
@@ -206,7 +206,7 @@ int resolve_gemm(int m, int n, int k, const float* A, int lda, const float* B, i
                 reg_tile = SGEMM_EMU_TILE_64x64;
         } else if (sgemm_emu::reg_flow_supported(a, SGEMM_EMU_TILE_128x128)) {
             reg_tile = SGEMM_EMU_TILE_128x128;
-        } else if (work < kDecompose && sgemm_emu::reg_flow_supported(a, SGEMM_EMU_TILE_64x64)) {
+        } else if (work < kLarge && sgemm_emu::reg_flow_supported(a, SGEMM_EMU_TILE_64x64)) {
             reg_tile = SGEMM_EMU_TILE_64x64;
         }
         if (tile != SGEMM_EMU_TILE_AUTO && tile != reg_tile) reg_tile = SGEMM_EMU_TILE_AUTO;
@@ -758,8 +758,6 @@ int sgemm_emu_scan(int64_t rows, int len, const float* X, int64_t ldx, float* Y,
     a.ldx = ldx;
     a.Y = Y;
     a.ldy = ldy;
-    // 16-byte loads of X and 16-byte stores of Y
-    a.vec = ((uintptr_t)X % 16 == 0) && ldx % 4 == 0 && ((uintptr_t)Y % 16 == 0) && ldy % 4 == 0;
     hipError_t e = sgemm_emu::launch_scan(a, stream);
     return e == hipSuccess ? SGEMM_EMU_OK : hip_fail(e);
 }
