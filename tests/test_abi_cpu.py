@@ -168,8 +168,8 @@ def test_resolve_policy():
     # ragged small products: register-direct 128x128
     assert _resolve(130, 132, 100, 8, (130 * 100, 100 * 132, 130 * 132)) == (
         0, (pkg.FLOW_REG, 1, pkg.TILE_128x128))
-    # large and ragged: whole tiles of the interior on the full-tile kernel,
-    # the edge strips on the register-flow kernel
+    # large and ragged: the class of nearly whole tiles (one launch of the tile
+    # kernel, sgemm_emu_launch_form)
     assert _resolve(8192 - 64, 8192, 8192) == (0, (pkg.FLOW_SPLIT, 1, pkg.TILE_128x256))
     assert _resolve.kernel == "bgemm_big_kernel+bgemm_reg_kernel"
     assert _resolve(8000, 8000, 8008) == (0, (pkg.FLOW_SPLIT, 1, pkg.TILE_128x256))  # k tail 8

@@ -1,13 +1,15 @@
-"""Parity of D = op(A).op(B) + C computed by the kernel written with the
-fragment interface (mfmae/wmma_tcec.hpp: load_matrix_sync, mma_sync,
-store_matrix_sync; Sec. 2.3.1 and Sec. 4.4), against the accumulate-form
-oracle:
+"""Parity of D = op(A).op(B) + C (Sec. 2.3.1 and Sec. 4.4) against the
+accumulate-form oracle, through the automatic choice of kernel.  The 16x16x32
+shape, products without error correction, k = 0 and the products in ROUTED run
+on the kernel written with the fragment interface (mfmae/wmma_tcec.hpp:
+load_matrix_sync, mma_sync, store_matrix_sync); the other 32x32x16 ones, unless
+an operand's contiguous side is shorter than 4, on the tile kernel:
 
 * every combination of instruction shape, operand transposes and C/D
   layout, on ragged sizes (partial tiles in m, n and k) and on full tiles
   (the 16-byte access path);
 * in-place accumulation (C is D), no C, k = 0, broadcast operands and
-  unaligned bases (the element-wise path);
+  unaligned bases;
 * integer inputs give the exact result;
 * the error-correction policy: off computes the hi.hi product (plus C) and
   is at the fp16 error level, on is at the FP32 level.
@@ -164,40 +166,43 @@ def test_error_correction_policy(s):
     assert np.all(np.abs(off - hh) <= 130 * 2.0 ** -23 * ref["n64"])
 
 
-def test_batch_past_one_launch():
-    """A batch larger than one launch holds: each wave takes one item of at
-    most 64 x 64, four waves a workgroup, so a launch takes at most
-    (2^31 / 256 - 1) * 4 = 33,554,428 items and this batch needs two.  A pool
-    of P items (k with a tail after one full step) is checked against the
-    oracle and repeated across the batch; every item of D must equal its pool
-    item bitwise."""
-    P, m, n, k = 1021, 2, 3, 20
-    per_launch = ((1 << 31) // 256 - 1) * 4
+@pytest.mark.parametrize("s,kernel,per_launch", [
+    ("s16", "gemm_acc_kernel", ((1 << 31) // 256 - 1) * 4),   # a wave per item
+    ("s32", "gemm_tile_kernel", (1 << 31) // 256 - 1)])       # a workgroup per item
+def test_batch_past_one_launch(s, kernel, per_launch):
+    """A batch larger than one launch of each kernel holds (workgroups of four
+    waves, below 2^31 work-items).  A pool of P items (k with a tail after one
+    full step) is checked against the oracle and repeated across the batch; the
+    items on both sides of every launch boundary are held to the bar and every
+    item of D must equal its pool item bitwise."""
+    P, m, n, k = 1021, 2, 4, 20
     batch = per_launch + 2 * P + 7
-    print(f"case acc batch={batch} m={m} n={n} k={k}", flush=True)
+    print(f"case acc batch={batch} m={m} n={n} k={k} {s}", flush=True)
     dev = device()
     A, B, C = _draw(P, m, n, k, seed=89)
     Ad = periodic_batch(A.to(dev), batch)
     Bd = periodic_batch(B.to(dev), batch)
     Cd = periodic_batch(C.to(dev), batch)
     D = torch.full((batch, m, n), float("nan"), device=dev)
-    pkg.sgemm_emu_batched_acc(Ad, Bd, Cd, D)
+    assert pkg.sgemm_emu_acc_launch_form(Ad, Bd, Cd, D, shape=SHAPES[s])[0] == kernel
+    pkg.sgemm_emu_batched_acc(Ad, Bd, Cd, D, shape=SHAPES[s])
     ref = oracle.gemm_acc(A.numpy(), B.numpy(), C.numpy())
     gate(to_np(D[:P]), ref, k, "acc pool")
-    gate_repeated(D, ref, P, [per_launch - 1, per_launch, per_launch + 1, batch - 1], k,
+    bounds = range(per_launch, batch, per_launch)
+    gate_repeated(D, ref, P, [b + d for b in bounds for d in (-1, 0, 1)] + [batch - 1], k,
                   "acc, launch boundary")
     assert_periodic(D, P, "acc batch")
 
 
-# The products the automatic choice leaves to this kernel in its 32x32x16 form
-# with error correction: A transposed and at most 32 columns or rows, and large
+# The products the automatic choice leaves to the kernel written with the
+# fragment interface in its 32x32x16 form with error correction: A transposed and at most 32 columns or rows, and large
 # batches of small items (their tests on the host name the limits).
 ROUTED = [(2048, 50, 17, 33), (1100, 65, 32, 100), (2100, 20, 33, 40), (6144, 100, 64, 60),
           (2100, 160, 96, 50), (2050, 192, 128, 64), (2050, 128, 192, 77), (1366, 192, 192, 256)]
 
 
 @pytest.mark.parametrize("shape", ROUTED, ids=lambda s: "x".join(map(str, s)))
-def test_products_left_to_this_kernel(shape):
+def test_products_left_to_the_fragment_kernel(shape):
     """C apart, in place (the same bits) and none, against the oracle on items
     over the batch, every output written."""
     batch, m, n, k = shape

@@ -8,11 +8,11 @@ the C ABI on the GPU.
 * edge cases: k = 0, empty problems, a single element, broadcast operands
   (zero batch stride), padded leading dimensions, leading dimensions at and
   just past the full-tile kernel's offset limit, unaligned pointers (the
-  scalar-load path);
+  general kernel's scalar loads);
 * exactness on integer inputs in binary16 range;
 * the error-correction-off control must be visibly worse (the correction
   terms are live);
-* determinism (no atomics, no split-k);
+* determinism (no atomics);
 * the full-size workloads in the launch configuration the benchmark times:
   every output written (NaN beforehand, finite after) and 4096 or more
   outputs spread over every item held to the parity bar.
@@ -24,8 +24,8 @@ import torch
 import oracle
 import paper_2308_15152_amd as pkg
 import synth
-from gpu_util import (assert_periodic, device, gate, gate_applies, gate_repeated, gemm_sampled,
-                      nan_output, periodic_batch, to_np)
+from gpu_util import (assert_all_finite, assert_periodic, device, gate, gate_applies,
+                      gate_repeated, gemm_sampled, nan_output, periodic_batch, to_np)
 
 pytestmark = pytest.mark.gpu
 
@@ -370,6 +370,15 @@ def test_unaligned_pointers_take_scalar_path():
     C = to_np(pkg.sgemm_emu_batched(Ad, Bd))
     ref = oracle.gemm(A.numpy(), B.numpy())
     gate(C, ref, 67, "unaligned")
+    # the scalar path itself: the general kernel, which the automatic policy
+    # leaves to the tile kernel's unaligned buffer loads
+    for flow in (pkg.FLOW_SPLIT, pkg.FLOW_DIRECT, pkg.FLOW_STAGED):
+        for tile in (pkg.TILE_64x64, pkg.TILE_128x128):
+            named = pkg.Policy(flow, 1, tile)
+            out = nan_output((2, 65, 66))
+            assert pkg.sgemm_emu_launch_form(Ad, Bd, out, policy=named)[0] == "bgemm_emu_kernel"
+            pkg.sgemm_emu_batched(Ad, Bd, out, policy=named)
+            gate(to_np(out), ref, 67, f"unaligned, flow {flow} tile {tile}")
 
 
 def test_deterministic():
@@ -430,60 +439,77 @@ def test_workload_paper_sweep_sampled(k):
     torch.cuda.empty_cache()
 
 
-# Large ragged products: interior of whole tiles on the full-tile kernel, a
-# k tail added in place, edge strips on the register-flow kernel.
-TILED_SHAPES = [(1, 4100, 4300, 2060),   # 128 x 256 interior, k tail of 12, both strips
+# Large products of nearly whole tiles (the class resolve_policy reports as
+# "bgemm_big_kernel+bgemm_reg_kernel"): one launch of the tile kernel, edges
+# and k tail included.
+TILED_SHAPES = [(1, 4100, 4300, 2060),   # k tail of 12, both edges
                 (2, 2600, 2600, 2560),   # whole k chunks, batch of 2
-                (1, 6000, 6000, 960),    # 256 x 128 interior
-                (1, 4096, 4200, 2048),   # right strip only
-                (1, 4200, 4096, 2048)]   # bottom strip only
-# Ragged products on the register-direct flow (below 2^35 multiply-adds or
-# without a nearly full interior): many tiles and long k; n odd takes the
-# 64 x 64 tiles.
+                (1, 6000, 6000, 960),
+                (1, 4096, 4200, 2048),   # right edge only
+                (1, 4200, 4096, 2048)]   # bottom edge only
+# Other large ragged products: many tiles and long k (the tile kernel under the
+# automatic policy, the register flow where it is named; n odd has no 128 x 128
+# tile there), and of short k (the register flow under both).
 REG_SHAPES = [(1, 2100, 2300, 1000), (2, 1500, 1800, 1024), (3, 1200, 1300, 1000),
-              (1, 3300, 3500, 3000), (1, 1100, 1101, 512)]
+              (1, 3300, 3500, 3000), (1, 1100, 1101, 512), (3, 2025, 2300, 92),
+              (2, 3000, 3333, 60), (50, 1030, 100, 300)]
 
 
 def _seams(m, n, bm, bn, seed):
+    """Rows and columns around the first and the last tile boundaries, where
+    whole tiles end and where the last tile begins if it is moved back, and
+    random ones."""
     mi, ni = m - m % bm, n - n % bn
     g = np.random.default_rng(seed)
-    rows = np.unique(np.concatenate([[0, bm - 1, bm, mi - 1, min(mi, m - 1), m - 1],
-                                     g.integers(0, m, 10)]))
-    cols = np.unique(np.concatenate([[0, bn - 1, bn, ni - 1, min(ni, n - 1), n - 1],
-                                     g.integers(0, n, 10)]))
+    rows = [0, bm - 1, bm, mi - 1, mi, m - bm - 1, m - bm, m - 1, *g.integers(0, m, 10)]
+    cols = [0, bn - 1, bn, ni - 1, ni, n - bn - 1, n - bn, n - 1, *g.integers(0, n, 10)]
+    rows = np.unique(np.clip(rows, 0, m - 1))
+    cols = np.unique(np.clip(cols, 0, n - 1))
     rr, cc = np.meshgrid(rows, cols, indexing="ij")
     return rr.ravel(), cc.ravel()
 
 
-def _check_sampled(shape, expect_kernel, label):
+def _check_sampled(shape, expect_kernel, label, policy=None):
+    """Outputs on all seams of the tiles that run, every output written."""
     batch, m, n, k = shape
     print(f"case {label} {shape}", flush=True)
     dev = device()
     A, B = synth.gemm_inputs(batch, m, n, k, seed=71 + m + k)
     Ad, Bd = A.to(dev), B.to(dev)
     C = torch.full((batch, m, n), float("nan"), device=dev)
-    pol, kern = pkg.sgemm_emu_resolve_policy(Ad, Bd, C)
+    kern, (bm, bn, _) = pkg.sgemm_emu_launch_form(Ad, Bd, C, policy=policy)
     assert kern == expect_kernel, kern
-    pkg.sgemm_emu_batched(Ad, Bd, C)
-    bm = 256 if pol.tile == pkg.TILE_256x128 else 64 if pol.tile == pkg.TILE_64x64 else 128
-    bn = 256 if pol.tile == pkg.TILE_128x256 else 64 if pol.tile == pkg.TILE_64x64 else 128
+    pkg.sgemm_emu_batched(Ad, Bd, C, policy=policy)
     rr, cc = _seams(m, n, bm, bn, m + n + k)
-    for b in range(batch):
+    for b in range(batch if batch < 4 else 2):
         Cb = C[b].cpu().numpy()
         assert np.isfinite(Cb).all()
         An, Bn = A[b].numpy(), B[b].numpy()
         ref = oracle.dots(An[rr], np.ascontiguousarray(Bn[:, cc].T))
         gate(Cb[rr, cc], ref, k, f"{label} {shape} item {b}")
+    assert_all_finite(C, label)
 
 
 @pytest.mark.parametrize("shape", TILED_SHAPES, ids=lambda s: "x".join(map(str, s)))
 def test_tiled_ragged_large(shape):
-    _check_sampled(shape, "bgemm_big_kernel+bgemm_reg_kernel", "tiled")
+    batch, m, n, k = shape
+    dev = device()
+    ops = [torch.empty(s, device=dev) for s in ((batch, m, k), (batch, k, n), (batch, m, n))]
+    assert pkg.sgemm_emu_resolve_policy(*ops)[1] == "bgemm_big_kernel+bgemm_reg_kernel"
+    del ops
+    _check_sampled(shape, "gemm_tile_kernel", "tiled")
 
 
 @pytest.mark.parametrize("shape", REG_SHAPES, ids=lambda s: "x".join(map(str, s)))
 def test_register_flow_ragged_large(shape):
-    _check_sampled(shape, "bgemm_reg_kernel", "register flow")
+    """On the register flow by name, in both of its tiles, and under the
+    automatic policy."""
+    automatic = "bgemm_reg_kernel" if shape in REG_SHAPES[-3:] else "gemm_tile_kernel"
+    _check_sampled(shape, automatic, "ragged")
+    tiles = [pkg.TILE_64x64] + ([pkg.TILE_128x128] if shape[2] % 2 == 0 else [])
+    for tile in tiles:
+        _check_sampled(shape, "bgemm_reg_kernel", f"register flow, tile {tile}",
+                       policy=pkg.Policy(pkg.FLOW_REG, 1, tile))
 
 
 def test_register_flow_batch_past_one_launch():

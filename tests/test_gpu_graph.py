@@ -16,9 +16,13 @@ from gpu_util import device, to_np
 
 pytestmark = pytest.mark.gpu
 
-# register-direct 64 x 64, full-tile 128 x 128, full-tile 256 x 128 (persistent
-# stream form), register-direct 128 x 128 on a ragged product
-SHAPES = [(16, 64, 64, 64), (8, 128, 128, 128), (2, 256, 256, 128), (3, 100, 90, 70)]
+# the tile kernel on whole tiles, on ragged ones and with four wave groups, the
+# register flow (short k), the full-tile kernel (more than two rounds of tiles)
+# and its persistent stream form
+SHAPES = [(16, 64, 64, 64), (3, 100, 90, 70), (1, 65, 70, 2051), (3, 100, 90, 60),
+          (520, 128, 128, 128), (300, 256, 256, 128)]
+KERNELS = ["gemm_tile_kernel", "gemm_tile_kernel", "gemm_tile_kernel", "bgemm_reg_kernel",
+           "bgemm_big_kernel", "bgemm_big_stream_kernel"]
 
 
 def _capture(fn):
@@ -37,13 +41,15 @@ def _bits(x):
     return np.asarray(x, dtype=np.float32).view(np.uint32)
 
 
-@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
-def test_gemm_graph_replays_match_eager(shape):
+@pytest.mark.parametrize("shape,kernel", zip(SHAPES, KERNELS),
+                         ids=["x".join(map(str, s)) for s in SHAPES])
+def test_gemm_graph_replays_match_eager(shape, kernel):
     dev = device()
     A, B = synth.gemm_inputs(*shape, seed=500 + shape[1])
     Ad, Bd = A.to(dev), B.to(dev)
     eager = to_np(pkg.sgemm_emu_batched(Ad, Bd))
     C = torch.full(eager.shape, float("nan"), device=dev)
+    assert pkg.sgemm_emu_launch_form(Ad, Bd, C)[0] == kernel
     g = _capture(lambda: pkg.sgemm_emu_batched(Ad, Bd, C))
     for _ in range(3):
         C.fill_(float("nan"))
@@ -55,9 +61,12 @@ def test_gemm_graph_replays_match_eager(shape):
         assert np.array_equal(_bits(other), _bits(eager))
 
 
-def test_scan_and_householder_graph_replays_match_eager():
+@pytest.mark.parametrize("rows,length", [(300, 2048), (5, 40000), (3000, 20)],
+                         ids=["whole", "parts", "short"])
+def test_scan_and_householder_graph_replays_match_eager(rows, length):
+    """Whole rows, rows in parts (three launches) and short rows."""
     dev = device()
-    X = synth.uniform((300, 2048), synth.rng(510)).to(dev)
+    X = synth.uniform((rows, length), synth.rng(510)).to(dev)
     u, B = synth.householder_inputs(40, 64, 64, seed=511)
     ud, Bd = u.to(dev), B.to(dev)
     y_eager = to_np(pkg.sgemm_emu_scan(X))
@@ -79,3 +88,19 @@ def test_scan_and_householder_graph_replays_match_eager():
         assert np.array_equal(_bits(to_np(Y)), _bits(y_eager))
         assert np.array_equal(_bits(to_np(H)), _bits(h_eager))
         assert np.array_equal(_bits(to_np(pkg.sgemm_emu_scan(X))), _bits(y_eager))
+
+
+def test_accumulate_graph_replays_match_eager():
+    """D += A^T B in place: every replay adds once more."""
+    dev = device()
+    A, B = synth.gemm_inputs(4, 321, 70, 333, seed=512)
+    Ad, Bd = A.transpose(1, 2).contiguous().to(dev), B.to(dev)
+    C = synth.uniform((4, 321, 70), synth.rng(513)).to(dev)
+    D = C.clone()
+    g = _capture(lambda: pkg.sgemm_emu_batched_acc(Ad, Bd, D, D, op_a=pkg.OP_T))
+    D.copy_(C)
+    for _ in range(3):
+        eager = to_np(pkg.sgemm_emu_batched_acc(Ad, Bd, D.clone(), op_a=pkg.OP_T))
+        g.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(_bits(to_np(D)), _bits(eager))

@@ -2,12 +2,13 @@
 upper-triangular all-ones U built from its rule by foreach_ij (Sec. 4.1,
 eq. scan-mat), in emulated FP32 (Sec. 4.4), against the scan oracle.
 
-* row counts around the 8-row share of a wave (1, 7, 8, 9, 100) and
-  lengths around the 1024-value block and the 32-value segment (1, 31, 33,
-  1000, 1024, 1025, 3072), on both the whole-block path (lengths that are
-  multiples of 1024, aligned rows) and the element-wise path;
+* row counts around the 1 to 4 rows of a wave and the 32 of a short one
+  (1, 7, 8, 9, 100) and lengths around the 1024-value block and the 32-value
+  segment (1, 31, 33, 1000, 1024, 1025, 3072);
+* few long rows in parts, short rows 32 to a block, and their limits;
 * integer inputs give the exact running sums; a unit impulse gives a step;
-* in place, padded row strides, unaligned bases (the element-wise path);
+* in place, padded row strides, unaligned bases;
+* values outside the range of the split;
 * the full-size workload on sampled rows.
 
 Tolerance: an output sums at most 32 split values inside its segment
@@ -68,6 +69,23 @@ def test_rows_in_parts(shape, in_place):
     pkg.sgemm_emu_scan(Xd, Y)
     ref = oracle.scan(X.numpy())
     gate(to_np(Y), ref, _k_eff(length), f"scan {rows}x{length}", max_gate=False)
+
+
+@pytest.mark.parametrize("rows,length", [(3, 20 * 1024 + 5), (40, 100001)])
+def test_padded_rows_in_parts(rows, length):
+    """Row pitches of X and Y that differ, off 16-byte alignment: nothing is
+    written between the rows, neither by the totals nor by the parts."""
+    X = synth.uniform((rows, length), synth.rng(rows))
+    xbuf = torch.full((rows * (length + 5) + 1,), 7.0, device=device())
+    Xv = xbuf[1:].view(rows, length + 5)[:, :length]
+    Xv.copy_(X)
+    ybuf = torch.full((rows * (length + 12) + 3,), 5.0, device=device())
+    whole = ybuf[3:].view(rows, length + 12)
+    pkg.sgemm_emu_scan(Xv, whole[:, :length])
+    gate(to_np(whole[:, :length]), oracle.scan(X.numpy()), _k_eff(length), "scan padded parts",
+         max_gate=False)
+    assert bool((whole[:, length:] == 5.0).all()) and bool((ybuf[:3] == 5.0).all())
+    assert torch.equal(pkg.sgemm_emu_scan(X.to(device())), whole[:, :length])
 
 
 @pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan"), 65520.0, -1e30])
@@ -170,8 +188,7 @@ def test_padded_and_unaligned(offset, length, pitch):
 
 
 def test_unaligned_output_only():
-    """X aligned, Y one element off 16-byte alignment: the 16-byte stores of
-    the whole-block path must not be used."""
+    """X aligned, Y one element off 16-byte alignment."""
     dev = device()
     X = synth.uniform((9, 2048), synth.rng(7)).to(dev)
     ybuf = torch.full((9 * 2048 + 1,), 5.0, device=dev)

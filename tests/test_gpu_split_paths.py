@@ -220,13 +220,15 @@ def test_accumulate_kernel_reproduces_the_split(shape, side):
     assert_bits(to_np(D), expected(x, True), f"gemm_acc {shape} {side}")
 
 
-@pytest.mark.parametrize("length", [2048, 1000])
-def test_scan_reproduces_the_split(length):
+@pytest.mark.parametrize("rows,length", [(4096, 2048), (4096, 1000), (4096, 32), (4096, 7),
+                                         (300, 16 * 1024 + 5)])
+def test_scan_reproduces_the_split(rows, length):
     """Rows with one nonzero value v: the inclusive scan is 0 before it and
     fl32(hi(v) + lo(v) 2^-11) from it on (U's entries are 0 and 1; every
-    carry adds that value to zeros).  Aligned rows of whole 1024-value
-    blocks take the whole-block path, 1000 the element-wise one."""
-    rows = 4096
+    carry adds that value to zeros), for whole rows and for short ones.  300
+    rows of 16 blocks are scanned in parts of 4096 values: their totals are
+    plain FP32 sums, so from the end of v's part on it is v itself."""
+    part = 4096
     g = np.random.default_rng(3000 + length)
     v = split_probe_values(rows, 3001 + length)
     pos = g.integers(0, length, rows)
@@ -237,9 +239,12 @@ def test_scan_reproduces_the_split(length):
     Y = torch.full_like(Xd, float("nan"))
     print(f"case split-path scan rows={rows} len={length}", flush=True)
     pkg.sgemm_emu_scan(Xd, Y)
-    want = np.where(np.arange(length)[None, :] >= pos[:, None],
-                    expected(v, True)[:, None], np.float32(0)).astype(np.float32)
-    assert_bits(to_np(Y), want, f"scan len {length}")
+    j = np.arange(length)[None, :]
+    want = np.where(j >= pos[:, None], expected(v, True)[:, None], np.float32(0))
+    if rows < 512:
+        end = np.minimum((pos // part + 1) * part, length) - 1
+        want = np.where(j >= end[:, None], v[:, None], want)
+    assert_bits(to_np(Y), want.astype(np.float32), f"scan {rows} x {length}")
 
 
 @pytest.mark.parametrize("mode", [pkg.HOUSEHOLDER_RULE, pkg.HOUSEHOLDER_LDS], ids=["rule", "lds"])

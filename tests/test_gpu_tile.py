@@ -50,8 +50,7 @@ def _check_untouched(flat, body, c, offset):
 # batch, m, n, k, row padding, offset of the bases: tiles moved back by one line
 # and by all but one, one tile exactly and one line more, matrices smaller than
 # a tile in m, n or both, k of one chunk, one value more or less and of odd and
-# even numbers of chunks per wave group, and grids that take each tile shape
-# (64 x 64 with one, two and four groups, 128 x 64, 128 x 128, 128 x 256)
+# even numbers of chunks per wave group (FORMS below has every tile shape)
 SHAPES = [
     (1, 64, 64, 66, 0, 0), (3, 65, 65, 65, 0, 0), (2, 127, 129, 95, 0, 1), (1, 63, 200, 97, 3, 2),
     (2, 200, 61, 130, 1, 0), (5, 33, 35, 129, 2, 3), (4, 1, 4, 70, 1, 1), (2, 3, 300, 31, 0, 0),
@@ -78,6 +77,73 @@ def test_products(shape):
                                     policy=pkg.Policy(pkg.FLOW_SPLIT, 1, pkg.TILE_64x64))
     N = torch.bmm(A.abs().to(device()).double(), B.abs().to(device()).double())
     assert bool(((C.double() - general).abs() <= 2 * (k + 2) * 2.0 ** -23 * N).all())
+
+
+# One ragged product per form of the kernel (rows and columns of the workgroup
+# tile, wave groups): tiles moved back in m and n, a k tail, several items, and
+# for 64 x 64 a matrix smaller than the tile as well.
+FORMS = {(64, 64, 1): [(2, 65, 70, 67), (3, 33, 40, 67)],
+         (64, 64, 2): [(1, 65, 70, 515), (2, 33, 40, 515)],
+         (64, 64, 4): [(1, 65, 70, 2051), (1, 33, 40, 2050)],
+         (128, 64, 1): [(60, 390, 70, 331)], (128, 64, 2): [(60, 130, 70, 331)],
+         (128, 128, 1): [(40, 200, 271, 67)], (128, 128, 2): [(60, 130, 141, 701)],
+         (128, 256, 1): [(60, 200, 271, 67)]}
+ACC_FORMS = {**FORMS, (128, 64, 1): [(60, 390, 70, 330)], (128, 64, 2): [(60, 130, 70, 330)],
+             (128, 128, 1): [(40, 200, 270, 67)], (128, 128, 2): [(60, 130, 140, 700)],
+             (128, 256, 1): [(40, 130, 700, 33)]}
+
+
+def _cases(forms):
+    return [(f, s) for f, shapes in forms.items() for s in shapes]
+
+
+def _fid(c):
+    return "x".join(map(str, c[0])) + "-" + "x".join(map(str, c[1]))
+
+
+@pytest.mark.parametrize("case", _cases(FORMS), ids=_fid)
+def test_every_form(case):
+    form, (b, m, n, k) = case
+    print(f"case tile form {case}", flush=True)
+    A, B = synth.gemm_inputs(b, m, n, k, seed=3 * m + n + k)
+    flat, body, C = _output(b, m, n, 0, 0)
+    Ad, Bd = A.to(device()), B.to(device())
+    assert pkg.sgemm_emu_launch_form(Ad, Bd, C) == ("gemm_tile_kernel", form)
+    pkg.sgemm_emu_batched(Ad, Bd, C)
+    _check_untouched(flat, body, n, 0)
+    items = sorted({0, b // 2, b - 1})
+    ref = oracle.gemm(A[items].numpy(), B[items].numpy())
+    gate(to_np(C[items]), ref, k, f"tile form {case}", max_gate=gate_applies(ref))
+    general = pkg.sgemm_emu_batched(Ad, Bd, policy=pkg.Policy(pkg.FLOW_SPLIT, 1, pkg.TILE_64x64))
+    N = torch.bmm(A.abs().to(device()).double(), B.abs().to(device()).double())
+    assert bool(((C.double() - general).abs() <= 2 * (k + 2) * 2.0 ** -23 * N).all())
+
+
+@pytest.mark.parametrize("k", [70, 1030])
+@pytest.mark.parametrize("value", [float("inf"), float("-inf"), float("nan"), 65520.0, 3e38])
+def test_operands_outside_the_split(value, k):
+    """A value of A or B whose split is not finite makes its row or column of C
+    non-finite, as in the general kernel, and nothing else: not what tiles
+    that overlap compute twice, not what the k tail or the wave groups share."""
+    m, n = 150, 141
+    A, B = synth.gemm_inputs(1, m, n, k, seed=9)
+    clean = to_np(pkg.sgemm_emu_batched(A.to(device()), B.to(device())))
+    rows, cols = [0, 21, 63, 64, 86, m - 1], [0, 63, 77, 128, n - 1]
+    for i, r in enumerate(rows):
+        A[0, r, (i * 37 + k - 1) % k] = value  # the k tail among them
+    for i, c in enumerate(cols):
+        B[0, (i * 29 + k - 1) % k, c] = value
+    Ad, Bd = A.to(device()), B.to(device())
+    C = to_np(pkg.sgemm_emu_batched(Ad, Bd))
+    assert pkg.sgemm_emu_launch_form(Ad, Bd, torch.empty(1, m, n, device=device()))[0] == (
+        "gemm_tile_kernel")
+    general = to_np(pkg.sgemm_emu_batched(
+        Ad, Bd, policy=pkg.Policy(pkg.FLOW_SPLIT, 1, pkg.TILE_64x64)))
+    hit = np.zeros((1, m, n), dtype=bool)
+    hit[:, rows, :] = True
+    hit[:, :, cols] = True
+    assert not np.isfinite(C[hit]).any() and not np.isfinite(general[hit]).any()
+    assert np.array_equal(C[~hit], clean[~hit])
 
 
 def test_shared_operands():
@@ -179,12 +245,26 @@ ACC_SHAPES = [(1, 64, 64, 96, 0, 0), (2, 65, 66, 67, 1, 1), (3, 130, 63, 300, 0,
               (30, 270, 520, 130, 1, 2), (2, 4, 4, 9, 0, 0), (1, 2050, 1030, 97, 0, 0)]
 
 
+@pytest.mark.parametrize("case", _cases(ACC_FORMS), ids=_fid)
+@pytest.mark.parametrize("ta", [0, 1])
+@pytest.mark.parametrize("tb", [0, 1])
+def test_every_accumulate_form(case, ta, tb):
+    form, (b, m, n, k) = case
+    _accumulate((b, m, n, k, 1, 0), ta, tb, 0, form)
+
+
 @pytest.mark.parametrize("shape", ACC_SHAPES, ids=lambda s: "x".join(map(str, s)))
 @pytest.mark.parametrize("ta", [0, 1])
 @pytest.mark.parametrize("tb", [0, 1])
 @pytest.mark.parametrize("col", [0, 1])
 def test_accumulate(shape, ta, tb, col):
-    """Every operand and output layout; C apart, C in place and no C."""
+    """Every operand and output layout."""
+    _accumulate(shape, ta, tb, col)
+
+
+def _accumulate(shape, ta, tb, col, form=None):
+    """C apart, C in place and no C, against the oracle; with `form`, on that
+    form of the tile kernel."""
     b, m, n, k, pad, offset = shape
     print(f"case tile acc {shape} ta={ta} tb={tb} col={col}", flush=True)
     g = synth.rng(m + n + k)
@@ -201,7 +281,12 @@ def test_accumulate(shape, ta, tb, col):
     an, bn, cn = A[items].numpy(), B[items].numpy(), C[items].numpy()
     ref = oracle.gemm_acc(an, bn, cn)
     flat, body, D = _output(b, r, c, pad, offset)
-    pkg.sgemm_emu_batched_acc(Ad, Bd, _strided(Cs, pad, offset), D, **kw)
+    Cd = _strided(Cs, pad, offset)
+    if form:
+        for addend in (Cd, D, None):
+            assert pkg.sgemm_emu_acc_launch_form(Ad, Bd, addend, D, **kw) == ("gemm_tile_kernel",
+                                                                              form)
+    pkg.sgemm_emu_batched_acc(Ad, Bd, Cd, D, **kw)
     _check_untouched(flat, body, c, offset)
     gate(logical(D), ref, k, f"tile acc {shape}", max_gate=gate_applies(ref))
     apart = D.clone()
