@@ -567,17 +567,18 @@ double bytes(const RuleParams& p, int64_t batch) {
 
 // What of B and C is streamed past the caches where their rows are whole
 // 128-byte lines (otherwise the pieces of a line meet there: 40,000 items of 444
-// columns 1690 us against 2263 streamed).  0: nothing; 1: the stores, up to the
-// 256 MiB of the last-level cache, which may hold B from the kernel that wrote
-// it (1536 items of 64 columns, 48 MB: B in the cache 8.4 us, with streaming loads
-// 10.4, nothing streamed 9.5; B not there 12.0 / 11.5 / 13.8; 7680 items, 240 MB,
-// 38 / 46 / 38 and 49 / 51 / 53); 2: the loads too beyond (320 MB 62 us against
-// 71 with nothing streamed).
+// columns 1690 us against 2263 streamed).  2: loads and stores; 1: the stores
+// alone, from 96 MB to the 256 MiB of the last-level cache, which may hold B from
+// the kernel that wrote it.  Reflectors of 256 columns, streamed / stores streamed
+// / nothing streamed, B in the cache: 88 MB 14.4 / 14.7 / 17.9 us (rotations 13.0 /
+// 14.9 / 18.7), 96 MB 16.8 / 15.5 / 18.7, 160 MB 29.7 / 24.5 / 29.4; B not there:
+// 88 MB 19.8 / 20.6 / 23.8, 160 MB 32.2 / 32.8 / 36.9; 64 columns, 320 MB 62 / - / 71.
 int streams(const RuleParams& p, int64_t batch) {
     const bool lines = ((uintptr_t)p.B % 128 == 0) && ((uintptr_t)p.C % 128 == 0) &&
                        p.ldb % 32 == 0 && p.ldc % 32 == 0 && p.sb % 32 == 0 && p.sc % 32 == 0 &&
                        p.ncols % 32 == 0;
-    return !lines ? 0 : bytes(p, batch) > double(1 << 28) ? 2 : 1;
+    const double size = bytes(p, batch);
+    return !lines ? 0 : size >= 96e6 && size <= double(1 << 28) ? 1 : 2;
 }
 
 // Whether the columns of an even number are read in pairs: not where the

@@ -87,10 +87,10 @@ def test_last_groups(ncols, mb):
         gate(to_np(C[it]), ref, 2, f"givens {ncols} columns", max_gate=False)
 
 
-@pytest.mark.parametrize("batch", [8192, 8193])
+@pytest.mark.parametrize("batch", [2929, 2930, 8192, 8193])
 def test_streamed_rows(batch):
-    """64 columns on both sides of the 256 MiB up to which B is read through
-    the caches: all forms give what a padded call, never streamed, gives."""
+    """64 columns on both sides of the 96 MB from which and the 256 MiB up to
+    which B is read through the caches: all forms give what a padded call, never streamed, gives."""
     print(f"case rule streamed batch={batch}", flush=True)
     u, B = synth.householder_inputs(batch, 64, 64, seed=500)
     c, s, _ = synth.givens_inputs(batch, 64, 1, seed=501)
