@@ -366,12 +366,14 @@ int householder_emu_batched_ex(int n, const float* u, int64_t stride_u,
  * traffic.  mode selects how (Sec. 4.3.1 compares these):
  *   SGEMM_EMU_GIVENS_AUTO      EMBEDDED when (i, j) has a compiled
  *                              instance, else MAP.
- *   SGEMM_EMU_GIVENS_MAP       fragments zero-filled, then 1, c, s and -s
- *                              set through the element map with (i, j)
- *                              passed as kernel arguments.
- *   SGEMM_EMU_GIVENS_EMBEDDED  as MAP with (i, j) fixed at compile time;
- *                              compiled for n = 64 and (i, j) in
- *                              {(5,37), (37,5), (0,1), (31,32), (62,63)};
+ *   SGEMM_EMU_GIVENS_MAP       (i, j) passed as kernel arguments; each lane
+ *                              finds the entries of the operand rows it
+ *                              holds at run time.
+ *   SGEMM_EMU_GIVENS_EMBEDDED  (i, j) fixed at compile time: fragments
+ *                              zero-filled, then 1, c, s and -s set through
+ *                              the element map; compiled for n = 64 and
+ *                              (i, j) in {(5,37), (37,5), (0,1), (31,32),
+ *                              (62,63)};
  *                              other planes give SGEMM_EMU_ERR_UNSUPPORTED.
  *   SGEMM_EMU_GIVENS_LDS       baseline: each wave writes G to LDS and
  *                              loads its fragments from there.

@@ -288,8 +288,8 @@ tile::Shape tile_form(const sgemm_emu::GemmArgs& a, Kernel kern, int resolved, t
             // 237 x 71 x 2044 x 308 216 / 315; by k, 64 to 319, 0.73 to 0.93 of the time,
             // beyond 0.96 to 1.1; with 512 to 1535 tiles 0.93 to 1.3).  Others up to
             // k = 127 if C's rows are no whole 128-byte lines and all of C stays in
-            // the last-level cache (15 x 2938 x 768 x 64 35 / 46, 60 x 356 x 1432 x 128
-            // 54 / 60; 0.87 to 0.95, beyond k = 127 0.95 to 1.2; 47 x 351 x 3832 x 92,
+            // the last-level cache (15 x 2938 x 768 x 64 35 / 46;
+            // 0.87 to 0.95, beyond k = 127 0.95 to 1.2; 47 x 351 x 3832 x 92,
             // 253 MB of C, 139 / 100).
             if (a.vec_b && a.n % 4 == 0 && tiles64 * a.batch >= 1536) {
                 const int side = a.m < a.n ? a.m : a.n;
@@ -671,7 +671,7 @@ int householder_emu_batched_ex(int n, const float* u, int64_t stride_u, const fl
     if (ldb < (ncols > 1 ? ncols : 1) || ldc < (ncols > 1 ? ncols : 1)) return SGEMM_EMU_ERR_LD;
     if (n == 0 || ncols == 0 || batch == 0) return SGEMM_EMU_OK;
     if (n != 64) return SGEMM_EMU_ERR_UNSUPPORTED;
-    // the kernel forms 8 * ldb + column as a 32-bit lane offset
+    // the row pitch the entry point is declared for
     if (ldb >= (1 << 27)) return SGEMM_EMU_ERR_UNSUPPORTED;
     if (u == nullptr || B == nullptr || C == nullptr) return SGEMM_EMU_ERR_NULL;
     if (stride_u < 0 || stride_b < 0 || stride_c < 0) return SGEMM_EMU_ERR_STRIDE;
@@ -706,7 +706,7 @@ int givens_emu_batched(int n, int i, int j, const float* c, const float* s, int6
     if (n == 0 || ncols == 0 || batch == 0) return SGEMM_EMU_OK;
     if (i < 0 || j < 0 || i >= n || j >= n || i == j) return SGEMM_EMU_ERR_DIM;
     if (n != 64) return SGEMM_EMU_ERR_UNSUPPORTED;
-    // the kernel forms 8 * ldb + column as a 32-bit lane offset
+    // the row pitch the entry point is declared for
     if (ldb >= (1 << 27)) return SGEMM_EMU_ERR_UNSUPPORTED;
     if (mode == SGEMM_EMU_GIVENS_AUTO)
         mode = sgemm_emu::givens_embedded(i, j) ? SGEMM_EMU_GIVENS_EMBEDDED : SGEMM_EMU_GIVENS_MAP;

@@ -12,12 +12,13 @@
 //     forms every entry once into LDS and loads the fragments from there.
 //   Givens (Sec. 4.3.1; map of Sec. 4.3):
 //     C = G(i, j, theta) B with G the identity except G_ii = G_jj = c,
-//     G_ij = -s, G_ji = s.  The fragments are filled with zeros and the
-//     nonzero entries are set through map(): (row, col) -> (lane, element).
-//     With (i, j) kernel arguments the lane and element of c and s are found
-//     at run time (a compare and select per element the lane holds); with
-//     (i, j) embedded at compile time every map() folds to a constant.  The
-//     baseline writes G to LDS and loads the fragments from there.
+//     G_ij = -s, G_ji = s.  With (i, j) embedded at compile time the fragments
+//     are filled with zeros and the nonzero entries are set through map():
+//     (row, col) -> (lane, element), which folds to constants.  With (i, j)
+//     kernel arguments each lane asks instead which words of the two rows it
+//     holds take an entry (a compare and a select per word; map() at run time
+//     took a select per element of every entry).  The baseline writes G to LDS
+//     and loads the fragments from there.
 //
 // One wavefront handles one batch item and up to 64 columns of B, in two
 // 32-column blocks, or in one if at most 32 columns are left (CB): products of
@@ -33,9 +34,10 @@
 // stores are buffer accesses on the item's corner: a scalar row offset and a
 // lane offset, which for a lane without a column lies past the descriptor's
 // end (its loads return zero, its stores are dropped).  Row pitches of 2^22
-// floats and more, which 32-bit offsets don't reach, take 64-bit pointers
-// (FAR; 20,000 items side by side in such rows of B, 32 / 64 / 94 / 65 columns 67 /
-// 133 / 214 / 191 us, two blocks of single columns for all 89 / 136 / 231 / 191).
+// floats and more, which 32-bit offsets don't reach, take 64-bit pointers (FAR,
+// up to the 2^27 floats of B that the entry points take; 20,000 items side by
+// side in such rows of B, 32 / 64 / 94 / 65 columns 67 / 133 / 214 / 191 us, two
+// blocks of single columns for all 89 / 136 / 231 / 191).
 #include "internal.h"
 #include "mfmae/frag.hpp"
 #include "mfmae/tcec.hpp"
@@ -177,8 +179,8 @@ struct GivensMapRule {
 // rows it holds (r = 32 tm + l % 32): the diagonal entry, 1 or c, and in rows
 // i and j one more, -s or s.  An operand row is 32 words of two halves, word
 // 8 s + 4 (l / 32) + w in the lane's registers of k step s, so placing an
-// entry is one compare and one select per word (a select per element of every
-// entry took 1995 vector instructions per wave).
+// entry is one compare and one select per word: 560 vector instructions per
+// wave with 64 columns, 1270 with a select per element of every entry.
 struct GivensArgRule {
     uint32_t diag[2], diag_lo[2];  // the entry's hi and lo, in their half of the word
     uint32_t off[2], off_lo[2];

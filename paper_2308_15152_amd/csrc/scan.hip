@@ -25,8 +25,9 @@
 // blocks in flight while the current one is multiplied.
 //
 // Rows (scan_kernel, one wave per 1 to 4 whole rows; scan_short_kernel, 32 rows
-// of up to 32 values at a time) fill the device when there are many of them.  A few long rows are cut into parts instead, one
-// wave each, in three launches on the stream that need no memory but Y:
+// of up to 32 values at a time) fill the device when there are many of them.  A
+// few long rows are cut into parts instead, one wave each, in three launches on
+// the stream that need no memory but Y:
 //   scan_total_kernel  each part's plain FP32 sum, left in the part's last
 //                      output;
 //   scan_chain_kernel  those sums scanned along each row, which makes them
@@ -273,10 +274,10 @@ __global__ __launch_bounds__(64 * kWaves, 4) void scan_kernel(ScanArgs p, int ro
 // Rows of at most one segment: 32 rows are the segments of one block, so a
 // wave scans them with the four products of a block and nothing crosses the
 // segments (1,000,000 rows of 1 / 8 / 32 values 13 / 16 / 44 us, a block per row
-// 431 / 424 / 426).  Loads and stores
-// go straight between memory and the operand and accumulator layouts, lane
-// (n, g) of row n, in 16-byte pieces of 4-byte alignment; what a piece holds of
-// the next row is dropped, and the descriptor ends with the last row.
+// 431 / 424 / 426).  Loads and stores go straight between memory and the operand
+// and accumulator layouts, lane (n, g) of row n, in 16-byte pieces of 4-byte
+// alignment; what a piece holds of the next row is dropped, and the descriptor
+// ends with the last row.
 constexpr int kShort = 32;
 
 // Byte offsets of 32 rows stay below 2^31.

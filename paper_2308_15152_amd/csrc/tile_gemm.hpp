@@ -1,8 +1,7 @@
 // The tile kernel: one BM x BN tile of D = op(A) op(B) (+ C) per workgroup,
 // for operands of any layout, size and alignment (Sec. 4.4; batched form of
-// Sec. 4.4.2).  Shared by the kernels of the register flow, the general split
-// flow and the accumulate form for products that fill no whole tiles of the
-// full-tile kernel.
+// Sec. 4.4.2).  Products without and with C, ragged, unaligned or too few
+// tiles for the full-tile kernel, run on it.
 //
 // Per k chunk of 32 every thread loads its part of both operands into
 // registers with 16-byte loads along the direction in which the operand is

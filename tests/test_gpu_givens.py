@@ -1,7 +1,7 @@
 """Parity of the batched Givens rotation C = G(i, j, theta) B with G built in
-registers through the element map (Sec. 4.3.1), in emulated FP32 (Sec. 4.4),
-for the three ways of building G: map with (i, j) as kernel arguments, map
-with (i, j) fixed at compile time, and G stored in LDS.
+registers (Sec. 4.3.1), in emulated FP32 (Sec. 4.4), for the three ways of
+building G: (i, j) as kernel arguments, the element map with (i, j) fixed at
+compile time, and G stored in LDS.
 
 * the entries the kernel places are G's, bit for bit: with B = I every
   output is one product g . 1, i.e. hi(g) + lo(g) 2^-11 rounded once, which
