@@ -18,18 +18,18 @@ __global__ __launch_bounds__(CF::NT, CF::W) void gemm_tile_kernel(Params p) {
     run<CF>(p, smem);
 }
 
-// What a shape costs, to rank the shapes by; not times.  A workgroup takes `first` per chunk
-// when it has a CU to itself, and `chunk` for each of those that share one
-// (at most `fit` do), plus `ends` for filling the pipeline and storing C.
-// Fitted to the order of the shapes' times (scaled as microseconds) on 160
-// products from 16 x 64^3 to 6000^2 x 960, odd sizes and transposed operands
-// among them: the shape chosen is 0.9% slower than the best one on average, 15%
-// at worst.  The estimate is below the time where all CUs run, whose clock falls
-// under the products, most of all for 128 x 256 (8 x 1001 x 999 x 1003 35 for
-// 57 us, 4096^3 with B stored n x k 317 for 370, 32 x 512^3 20 for 29).  (Without the shapes with k
-// groups 2%: the waves of one group go through reads, products and split in
-// step, and a second group fills the gaps: 1024^3 16.4 -> 13.9 us, 2048^3
-// 64 -> 55, 4 x 256 x 256 x 4096 54 -> 32.)
+// What a shape costs, to rank the shapes by; not times.  A workgroup takes
+// `first` per chunk when it has a CU to itself, and `chunk` for each of those
+// that share one (at most `fit` do), plus `ends` for filling the pipeline and
+// storing C.  Fitted to the order of the shapes' times (scaled as microseconds)
+// on 160 products from 16 x 64^3 to 6000^2 x 960, odd sizes and transposed
+// operands among them: the shape chosen is 0.9% slower than the best one on
+// average, 15% at worst.  The estimate is below the time where all CUs run, whose
+// clock falls under the products, most of all for 128 x 256 (8 x 1001 x 999 x
+// 1003 35 for 57 us, 4096^3 with B stored n x k 317 for 370, 32 x 512^3 20 for
+// 29).  (Without the shapes with k groups 2%: the waves of one group go through
+// reads, products and split in step, and a second group fills the gaps: 1024^3
+// 16.4 -> 13.9 us, 2048^3 64 -> 55, 4 x 256 x 256 x 4096 54 -> 32.)
 struct Cost {
     int bm, bn, kg, fit;
     double first, chunk, ends;
