@@ -288,9 +288,8 @@ tile::Shape tile_form(const sgemm_emu::GemmArgs& a, Kernel kern, int resolved, t
             // 237 x 71 x 2044 x 308 216 / 315; by k, 64 to 319, 0.73 to 0.93 of the time,
             // beyond 0.96 to 1.1; with 512 to 1535 tiles 0.93 to 1.3).  Others up to
             // k = 127 if C's rows are no whole 128-byte lines and all of C stays in
-            // the last-level cache (15 x 2938 x 768 x 64 35 / 46;
-            // 0.87 to 0.95, beyond k = 127 0.95 to 1.2; 47 x 351 x 3832 x 92,
-            // 253 MB of C, 139 / 100).
+            // the last-level cache (15 x 2938 x 768 x 64 35 / 46; 0.87 to 0.95,
+            // beyond k = 127 0.95 to 1.2; 47 x 351 x 3832 x 92, 253 MB of C, 139 / 100).
             if (a.vec_b && a.n % 4 == 0 && tiles64 * a.batch >= 1536) {
                 const int side = a.m < a.n ? a.m : a.n;
                 const bool lines =
@@ -391,15 +390,16 @@ tile::Shape acc_tile_form(const sgemm_emu::AccArgs& a, tile::Problem& p) {
     // D's 128-byte lines, which wait for HBM too, where the tile shapes compute
     // much twice or leave it out: 64 or 96 columns (500 x 768 x 96 x 64 75 us against
     // 103, 1741 x 384 x 64 x 96 81 / 96, 11647 x 100 x 96 x 52 249 / 311, 8192 x 96^3
-    // 281 / 284), 128 or 192 rows and columns (2500 x 192^3 312 / 377), and 128 x 128
-    // in place (4096 x 128^3 187 / 201; apart 189 / 189, and without C 11367 x
-    // 128^3 394 / 381).  Not with fewer tiles (1399 x 96^3 125%, 2417 x 96^3 115%, 946 x
+    // 281 / 284), 192 rows or columns by 128 or 192, one and a half of the larger
+    // tiles (2500 x 192^3 312 / 377), and whole such tiles, 128 x 128, only in place
+    // (4096 x 128^3 187 / 201; apart 189 / 189, and without C 11367 x 128^3 394 /
+    // 381).  Not with fewer tiles (1399 x 96^3 125%, 2417 x 96^3 115%, 946 x
     // 192^3 106%), other columns (8145 x 128 x 94 x 64 in unaligned rows 124%), a
     // short k (14479 x 128 x 64 x 20 115%) or a long one.
     const bool lines = (uintptr_t)a.D % 128 == 0 && a.ldd % 32 == 0 && a.sd % 32 == 0;
     const bool narrow = a.m >= 96 && (a.n == 64 || a.n == 96) && tiles64 >= 12288;
     const bool square = (a.m == 128 || a.m == 192) && (a.n == 128 || a.n == 192) &&
-                        (a.m != a.n || a.m == 192 || a.C == a.D) && tiles64 >= 9216;
+                        (a.m == 192 || a.n == 192 || a.C == a.D) && tiles64 >= 9216;
     if (a.a_trans && !a.b_trans && !a.cd_col && a.k >= 48 && a.k <= 256 && lines &&
         (narrow || square))
         return tile::NONE;
