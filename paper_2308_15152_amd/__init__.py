@@ -283,9 +283,9 @@ def _check_shape(t, shape, name: str) -> None:
         raise ValueError(f"{name} must have shape {tuple(shape)}, got {tuple(t.shape)}")
 
 
-def _matrix_view(t, name: str):
+def _matrix_view(t, name: str, vector: bool = False):
     """(batch, rows, cols, ld, batch_stride) of a 2-D or 3-D FP32 tensor whose
-    rows are contiguous."""
+    rows are contiguous; one row may come as a vector if ``vector``."""
     if t.dtype is not _load_torch().float32:
         raise TypeError(f"{name} must be float32, got {t.dtype}")
     if not t.is_cuda:
@@ -298,6 +298,9 @@ def _matrix_view(t, name: str):
         b = None
         rows, cols = shape
         ld, step = t.stride()
+    elif vector and len(shape) == 1:
+        b, rows, cols = None, 1, shape[0]
+        step, = t.stride()
     else:
         raise ValueError(f"{name} must be 2-D or 3-D")
     if step != 1 and cols > 1:
@@ -319,8 +322,7 @@ def _gemm_args(A, B, C):
         raise ValueError("batch sizes differ")
     if C is None:
         C = _torch.empty((batch, m, n), dtype=_torch.float32, device=A.device)
-    # one row may come as a vector
-    bc, mc, nc, ldc, sc = _matrix_view(C if len(C.shape) != 1 else C.unsqueeze(0), "C")
+    bc, mc, nc, ldc, sc = _matrix_view(C, "C", True)
     if mc != m or nc != n or (bc if bc is not None else 1) != batch:
         raise ValueError("C has the wrong shape")
     st = Stride(sa, sb, sc if batch > 1 else 0)
